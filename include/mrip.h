@@ -194,10 +194,11 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
 /* WAVE launch shape: replications per wavefront (1, 2 or 4; M/M/1 only)
  * and workgroup size (64, 256 or 1024) of the one-wavefront-per-replication
  * kernels, for runs and for plans (mrip_autotune later sets the plans'
- * alone). Outputs do not depend on it. Defaults 1 and 256. Runs of few
- * replications use workgroup-per-replication forms instead, whose size the
- * model fixes: the walk up to 2048 replications (16 lanes per walker), pi
- * below 4096 replications of at least 65536 points (2 to 16 wavefronts). */
+ * alone). Outputs do not depend on it. Defaults 1 and 256. Other forms
+ * have a size that the model fixes: the walk up to 2048 replications (16
+ * lanes per walker), pi from 4096 points (one or more workgroups of four
+ * wavefronts per replication; on taus88 streams, below 4096 replications of
+ * at least 65536 points, 2 to 16 wavefronts). */
 MRIP_API mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t reps_per_wave, uint32_t workgroup);
 
 /* Wavefronts per replication for mrip_run on an M/M/1 WAVE context: 1, 2,

@@ -668,6 +668,15 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     a.estimate = (float *)outp[1];
     a.rng = ctx->rng;
     a.taus = ctx->taus_tables.as<uint32_t>();
+    if (wave && pi_parts(n_reps, a.points, a.rng) > 1) {
+      // the replications' meeting slots: zero once, left zero by every run
+      const size_t need = n_reps * sizeof(uint64_t);
+      if (need > ctx->pi_slots.bytes) {
+        HIP_TRY(ctx, ctx->pi_slots.ensure(need));
+        HIP_TRY(ctx, launch_zero_u32(ctx->pi_slots.as<uint32_t>(), (uint32_t)(need / 4), s));
+      }
+      a.slots = ctx->pi_slots.as<uint64_t>();
+    }
     if (wave) HIP_TRY(ctx, launch_pi_wave(a, ctx->wg, s));
     else HIP_TRY(ctx, launch_pi_simt(a, ctx->mapping == MRIP_MAP_LANE0, s));
   } else {

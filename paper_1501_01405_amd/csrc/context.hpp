@@ -146,6 +146,7 @@ struct mrip_ctx_s {
   } bound[MAX_OUT];
   void *cur[MAX_OUT] = {};
   mrip::DevBuf scratch;
+  mrip::DevBuf pi_slots;        // where a replication's workgroups meet (pi_parts_kernel)
   mrip::DevBuf walker_scratch;  // the walk's per-walker bitmaps
   mrip::DevBuf taus_walk;       // the walk's taus88 jump tables (its steps are fixed)
   mrip::DevBuf taus_run;        // the M/M/1 runs' taus88 jump tables (customers are fixed)

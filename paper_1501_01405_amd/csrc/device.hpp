@@ -25,14 +25,20 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// One Philox4x32-10 block. The 32x32->64 products become one
-// v_mad_u64_u32 each; the xor with the counter word and the round key is a
-// single three-input bitop.
-__device__ __forceinline__ Block4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                         uint32_t k0, uint32_t k1) {
+// The multiplier of the counter's word 0.
+constexpr uint32_t PHILOX_M0 = 0xD2511F53u;
+
+// One Philox4x32-10 block whose first product p0 = PHILOX_M0 * c0 the caller
+// has: a loop over equally spaced draw indices c0 keeps p0 and adds a
+// constant to it (one 64-bit add instead of forming c0 and multiplying).
+// The 32x32->64 products become one v_mad_u64_u32 each; the xor with the
+// counter word and the round key is a single three-input bitop.
+__device__ __forceinline__ Block4 philox_from(uint64_t p0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                              uint32_t k0, uint32_t k1) {
+  uint32_t c0 = 0;
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
+    if (round > 0) p0 = (uint64_t)PHILOX_M0 * c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
     const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
@@ -44,6 +50,20 @@ __device__ __forceinline__ Block4 philox(uint32_t c0, uint32_t c1, uint32_t c2, 
     k1 += 0xBB67AE85u;
   }
   return Block4{c0, c1, c2, c3};
+}
+
+__device__ __forceinline__ Block4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                         uint32_t k0, uint32_t k1) {
+  return philox_from((uint64_t)PHILOX_M0 * c0, c1, c2, c3, k0, k1);
+}
+
+// A wave-uniform value kept in a vector register. Full-rate operations
+// (add, xor, three-input bitop) whose operands all come from vector
+// registers can share issue slots with the multiplies around them; with a
+// scalar or literal operand they take a slot of their own.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
+  asm("" : "+v"(v));
+  return v;
 }
 
 __device__ __forceinline__ uint32_t word_of(const Block4 &b, uint32_t j) {

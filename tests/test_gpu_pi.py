@@ -68,3 +68,25 @@ def test_pi_shared_out_over_wavefronts(gpu, R, rng):
     ctx.run(R, seed=31)
     ref = core.pi_many(31, R, N, threads=core.default_threads(), rng=rng)
     assert np.array_equal(ctx.output(0).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("points,R", [(4095, 5), (4096, 7), (4097, 33), (8191, 1), (16384, 3),
+                                      (16385, 40), (65537, 30), (98305, 300), (2000001, 40)])
+def test_pi_shared_replications_bit_exact(gpu, points, R):
+    # a replication over one or several workgroups: sizes around a
+    # wavefront's whole iterations, an odd last point, and enough points near
+    # the circle (2000001 x 40: a dozen iterations) for the exact recount;
+    # the workgroups' meeting slots are clean for the next run, for fewer
+    # replications and for more
+    announce("pi parts", points, R)
+    ctx, hits, est = _run(WAVE, points, R)
+    threads = core.default_threads()
+    ref = core.pi_many(42, R, points, threads=threads)
+    assert np.array_equal(hits, ref)
+    assert np.array_equal(est, (4.0 * ref / points).astype(np.float32))
+    if points > 100000:
+        return
+    for n, seed in ((max(1, R // 2), 7), (2 * R + 1, 8)):
+        ctx.run(n, seed=seed)
+        assert np.array_equal(ctx.output(0).cpu().numpy(),
+                              core.pi_many(seed, n, points, threads=threads))
