@@ -25,31 +25,37 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// The multiplier of the counter's word 0.
-constexpr uint32_t PHILOX_M0 = 0xD2511F53u;
+// The multipliers of counter words 0 and 2 and the key increments.
+constexpr uint32_t PHILOX_M0 = 0xD2511F53u, PHILOX_M1 = 0xCD9E8D57u;
+constexpr uint32_t PHILOX_W0 = 0x9E3779B9u, PHILOX_W1 = 0xBB67AE85u;
 
-// One Philox4x32-10 block whose first product p0 = PHILOX_M0 * c0 the caller
-// has: a loop over equally spaced draw indices c0 keeps p0 and adds a
-// constant to it (one 64-bit add instead of forming c0 and multiplying).
-// The 32x32->64 products become one v_mad_u64_u32 each; the xor with the
-// counter word and the round key is a single three-input bitop.
-__device__ __forceinline__ Block4 philox_from(uint64_t p0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1) {
-  uint32_t c0 = 0;
+// The rounds ROUND .. 9 of Philox4x32-10 from the counter words before round
+// ROUND (keys k0, k1 are the seed's). The 32x32->64 products become one
+// v_mad_u64_u32 each; the xor with the counter word and the round key is a
+// single three-input bitop.
+template <int ROUND>
+__device__ __forceinline__ Block4 philox_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                                uint32_t k0, uint32_t k1) {
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    if (round > 0) p0 = (uint64_t)PHILOX_M0 * c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+  for (int round = ROUND; round < 10; ++round) {
+    const uint64_t p0 = (uint64_t)PHILOX_M0 * c0;
+    const uint64_t p1 = (uint64_t)PHILOX_M1 * c2;
+    c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + (uint32_t)round * PHILOX_W0);
+    c2 = xor3((uint32_t)(p0 >> 32), c3, k1 + (uint32_t)round * PHILOX_W1);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
-    c0 = n0;
-    c2 = n2;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
   }
   return Block4{c0, c1, c2, c3};
+}
+
+// One block whose first product p0 = PHILOX_M0 * c0 the caller has: a loop
+// over equally spaced draw indices c0 keeps p0 and adds a constant to it
+// (one 64-bit add instead of forming c0 and multiplying).
+__device__ __forceinline__ Block4 philox_from(uint64_t p0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                              uint32_t k0, uint32_t k1) {
+  const uint64_t p1 = (uint64_t)PHILOX_M1 * c2;
+  return philox_rounds<1>(xor3((uint32_t)(p1 >> 32), c1, k0), (uint32_t)p1,
+                          xor3((uint32_t)(p0 >> 32), c3, k1), (uint32_t)p0, k0, k1);
 }
 
 __device__ __forceinline__ Block4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,

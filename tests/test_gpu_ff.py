@@ -70,3 +70,15 @@ def test_ff_edges(gpu, grid, p, f):
         assert np.array_equal(got, ref), mapping
     if p == 0.0:
         assert np.all(ref == 0)
+
+
+@pytest.mark.parametrize("grid,p,f", [(128, 0.03, 0.0), (64, 0.03, 2e-4), (128, 0.03, 4.9e-4),
+                                      (128, 0.03, 5.1e-4), (64, 0.5, 1.0), (64, 1.0, 4.9e-4),
+                                      (128, 0.0, 1e-4)])
+def test_ff_lightning_forms_bit_exact(gpu, grid, p, f):
+    # both forms of the lightning bits and the thresholds around their
+    # boundary: no strike at all, seldom, often, everywhere
+    announce("ff lightning", grid, p, f)
+    R, T = 9, 90
+    _, got = _run(WAVE, grid, T, R, p, f, seed=5)
+    assert np.array_equal(got, core.ff_many(5, R, grid, T, p, f, threads=core.default_threads()))
