@@ -198,7 +198,8 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
  * have a size that the model fixes: the walk up to 2048 replications (16
  * lanes per walker), pi from 4096 points (one or more workgroups of four
  * wavefronts per replication; on taus88 streams, below 4096 replications of
- * at least 65536 points, 2 to 16 wavefronts). */
+ * at least 65536 points, 2 to 16 wavefronts), and the forest fire (one to
+ * eight wavefronts per replication). */
 MRIP_API mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t reps_per_wave, uint32_t workgroup);
 
 /* Wavefronts per replication for mrip_run on an M/M/1 WAVE context: 1, 2,

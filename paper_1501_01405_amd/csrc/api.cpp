@@ -689,7 +689,7 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     a.n_reps = n_reps;
     a.burnt = (int32_t *)outp[0];
     if (wave) {
-      HIP_TRY(ctx, launch_ff_wave(a, ctx->wg, s));
+      HIP_TRY(ctx, launch_ff_wave(a, s));
     } else {
       HIP_TRY(ctx, ctx->scratch.ensure(n_reps * 2ull * a.grid * (a.grid / 32) * 4));
       a.state = ctx->scratch.as<uint32_t>();

@@ -10,17 +10,15 @@
 //     burning' = ignite,  tree' = (tree & ~ignite) | grow,  burnt += popcount(ignite)
 // and the random bits come one Philox block per 4 cells.
 //
-// WAVE mapping: one replication per wavefront. The whole 128x128 grid of a
-// replication fits in 16 VGPRs per lane (2 rows x 2 planes x 4 words); row
-// exchange with the lanes above and below goes through cross-lane shuffles,
-// so the grid never leaves the register file during the 2000 steps.
+// WAVE mapping: one replication per workgroup of one to eight wavefronts;
+// a thread keeps its words' trees in registers and trades burning words with
+// its neighbours through LDS, so the grid never leaves the compute unit
+// during the 2000 steps.
 //
 // SIMT mapping: one replication per lane. A 4 KiB grid per lane cannot stay
 // in registers; it lives in global memory laid out [plane][row][word][rep]
 // so that the 64 lanes of a wave touch 64 consecutive words, and is updated
 // in place one row at a time (old rows y-1 and 0 are kept in registers).
-#include <utility>
-
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -120,97 +118,111 @@ __device__ __forceinline__ uint32_t min16(const Words16 &w) {
   return m;
 }
 
-template <class F, int... I>
-__device__ __forceinline__ void for_words(F &&f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
+// The growth and lightning bits of the word whose first block is c (tp, tf:
+// the thresholds, tf_s the latter in a scalar register).
+template <bool RARE>
+__device__ __forceinline__ void word_masks(uint32_t c0_base, uint32_t c1, uint32_t c2, uint32_t c3,
+                                           uint32_t c, uint32_t k0, uint32_t k1, uint32_t tp,
+                                           uint32_t tf, uint32_t tf_s, uint32_t &ltp,
+                                           uint32_t &ltf) {
+  ltp = ltf = 0u;
+#pragma unroll
+  for (int half = 1; half >= 0; --half) {
+    const Words16 w = draw16(c0_base, c1, c2, c3, c + 4u * half, k0, k1);
+    ltp = less16(ltp, w, tp);
+    if (RARE) {
+      uint32_t low = 0u;
+      if (__builtin_amdgcn_ballot_w64(min16(w) < tf_s)) low = less16(0u, w, tf);
+      ltf |= half ? low << 16 : low;
+    } else {
+      ltf = less16(ltf, w, tf);
+    }
+  }
 }
 
-// One replication per wavefront, RPL rows per lane. Bound: vector-ALU issue
-// (one instruction per four cycles per SIMD), so the step is written for few
+// One replication over the THREADS = GRID * GRID / 32 / N threads of a
+// workgroup, N consecutive words of a row each. Bound: vector-ALU issue (one
+// instruction per four cycles per SIMD), so the step is written for few
 // instructions per cell: 11.4 where lightning is rare, 13.6 before.
-// 4096 x 128 x 128 x 500 steps: 11.75 ms before, 9.37 now (9.97 with scalar
-// round keys, 10.2 with every lightning bit built).
-//  * Round 1 of Philox is the same for a lane's blocks up to an xor with the
-//    block's number; rounds 2 and 3 share their products with word 2 and word
-//    0 across the blocks of a step. The round keys sit in vector registers.
+//  * Round 1 of Philox is the same for a thread's blocks up to an xor with
+//    the block's number; rounds 2 and 3 share their products with word 2 and
+//    word 0 across the blocks of a step. The round keys sit in vector
+//    registers (9.37 ms against 9.97 with scalar keys, 4096 x 128 x 128 x 500).
 //  * RARE: the lightning bits of 16 cells are built only if some lane has a
 //    word below tf among them, which the minimum of the words shows in half
 //    an instruction per cell instead of the two a bit costs.
-template <int GRID, bool RARE>
-__global__ __launch_bounds__(1024) void ff_wave_kernel(FfArgs a) {
-  constexpr int RPL = GRID / 64;  // rows per lane
-  constexpr int DW = GRID / 32;   // words per row
-  const int lane = threadIdx.x & 63;
-  const uint64_t r = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (r >= a.n_reps) return;  // wave-uniform
+//  * The burning plane lives in LDS, two copies by step parity, so one
+//    barrier a step suffices: a thread draws its words' random masks, waits
+//    for the others' burning words of the step before, applies the rule and
+//    stores its own new ones into the other copy, whose readers passed this
+//    barrier. The trees stay in registers.
+// Several wavefronts per replication fill the chip when replications are few
+// (alone on its SIMD a wavefront issues one instruction in five cycles) and
+// even out the last round of workgroups when they are many.
+// 128 x 128 x 200 steps, one wavefront per replication with 2 rows per lane
+// in registers / four wavefronts / eight: 30 replications 1.17 / 0.319 / 0.285
+// ms, 500 1.18 / 0.560 / 0.548, 700 1.18 / 0.778 / 0.787, 1500 2.00 / 1.42 /
+// 1.43, 4096 3.76 / 3.64 / 3.70. 64 x 64, one / two: 256 0.311 / 0.176 ms, 1000
+// 0.320 / 0.300, 1500 0.514 / 0.506, 2000 0.512 / 0.516, 4096 0.964 / 0.973.
+template <int GRID, int N, bool RARE>
+__global__ __launch_bounds__(GRID *GRID / 32 / N) void ff_wave_kernel(FfArgs a) {
+  constexpr int DW = GRID / 32, WORDS = GRID * DW, THREADS = WORDS / N;
+  static_assert(N <= DW && THREADS % 64 == 0, "whole wavefronts, words of one row per thread");
+  __shared__ uint32_t fire[2][WORDS];
+  __shared__ int sh_burnt[THREADS / 64];
+  const int tid = threadIdx.x, w0 = tid * N;  // the thread's first word, row-major
+  const int row = w0 / DW, col = w0 % DW;
+  const int above0 = ((row + GRID - 1) % GRID) * DW + col, below0 = ((row + 1) % GRID) * DW + col;
+  const int left = row * DW + (col + DW - 1) % DW, right = row * DW + (col + N) % DW;
+  const uint32_t rep = (uint32_t)a.rep0 + blockIdx.x;
   const uint32_t k0 = in_vgpr((uint32_t)a.seed), k1 = in_vgpr((uint32_t)(a.seed >> 32));
-  const uint32_t rep = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)r);
-  const int up_lane = (lane + 63) & 63, dn_lane = (lane + 1) & 63;
-  // round 1 from counter (t, q, rep, TAG_FF): the parts without t
   const uint64_t p1 = (uint64_t)PHILOX_M1 * rep;
   const uint32_t tp = in_vgpr(a.tp), tf = in_vgpr(a.tf);
-  uint32_t c0_base = xor3((uint32_t)(p1 >> 32), (uint32_t)lane * (RPL * GRID / 4), k0);
+  uint32_t c0_base = xor3((uint32_t)(p1 >> 32), (uint32_t)w0 * 8u, k0);
 
-  uint32_t T[RPL][DW], B[RPL][DW];
+  uint32_t T[N], B[N];
 #pragma unroll
-  for (int i = 0; i < RPL; ++i)
-#pragma unroll
-    for (int k = 0; k < DW; ++k) T[i][k] = B[i][k] = 0u;
+  for (int j = 0; j < N; ++j) {
+    T[j] = B[j] = 0u;
+    fire[0][w0 + j] = 0u;
+  }
   int burnt = 0;
-
   for (uint32_t t = 0; t < a.steps; ++t) {
     const uint64_t p0 = (uint64_t)PHILOX_M0 * t;
     const uint32_t c2 = xor3((uint32_t)(p0 >> 32), TAG_FF, k1), c3 = (uint32_t)p0;
-    // a new value to the compiler every step: else it hoists the first
-    // products of all of the lane's blocks, 128 registers
-    asm("" : "+v"(c0_base));
-    uint32_t up[DW], dn[DW];
+    asm("" : "+v"(c0_base));  // keeps the blocks' first products out of registers
+    uint32_t ltp[N], ltf[N];
 #pragma unroll
-    for (int k = 0; k < DW; ++k) {
-      up[k] = (uint32_t)__shfl((int)B[RPL - 1][k], up_lane, 64);
-      dn[k] = (uint32_t)__shfl((int)B[0][k], dn_lane, 64);
-    }
-    uint32_t nT[RPL][DW], nB[RPL][DW];
-    // word k of the lane's row i; unrolled by the template, so that the grid
-    // is indexed by constants and stays in registers
-    auto word = [&](auto wi) {
-      constexpr int i = decltype(wi)::value / DW, k = decltype(wi)::value % DW;
-      const uint32_t above = i == 0 ? up[k] : B[(i + RPL - 1) % RPL][k];
-      const uint32_t below = i == RPL - 1 ? dn[k] : B[(i + 1) % RPL][k];
-      const uint32_t nb = from_left(B[i][k], B[i][(k + DW - 1) % DW]) |
-                          from_right(B[i][(k + 1) % DW], B[i][k]) | above | below;
-      uint32_t ltp = 0u, ltf = 0u;
+    for (int j = 0; j < N; ++j)
+      word_masks<RARE>(c0_base, (uint32_t)p1, c2, c3, 8u * j, k0, k1, tp, tf, a.tf, ltp[j], ltf[j]);
+    __syncthreads();
+    const uint32_t *old = fire[t & 1];
+    uint32_t *now = fire[(t & 1) ^ 1];
+    const uint32_t lw = old[left], rw = old[right];
+    uint32_t nB[N];
 #pragma unroll
-      for (int half = 1; half >= 0; --half) {
-        const Words16 w = draw16(c0_base, (uint32_t)p1, c2, c3,
-                                 (uint32_t)(i * GRID / 4 + 8 * k + 4 * half), k0, k1);
-        ltp = less16(ltp, w, tp);
-        if (RARE) {
-          uint32_t low = 0u;
-          if (__builtin_amdgcn_ballot_w64(min16(w) < a.tf)) low = less16(0u, w, tf);
-          ltf |= half ? low << 16 : low;
-        } else {
-          ltf = less16(ltf, w, tf);
-        }
-      }
-      const uint32_t tree = T[i][k], burn = B[i][k];
-      const uint32_t ign = tree & (nb | ltf);
-      const uint32_t grow = ~(tree | burn) & ltp;
-      nB[i][k] = ign;
-      nT[i][k] = (tree & ~ign) | grow;
+    for (int j = 0; j < N; ++j) {
+      const uint32_t nb = from_left(B[j], j == 0 ? lw : B[j - 1]) |
+                          from_right(j == N - 1 ? rw : B[j + 1], B[j]) | old[above0 + j] |
+                          old[below0 + j];
+      const uint32_t ign = T[j] & (nb | ltf[j]);
+      const uint32_t grow = ~(T[j] | B[j]) & ltp[j];
+      nB[j] = ign;
+      T[j] = (T[j] & ~ign) | grow;
       burnt += __popc(ign);
-    };
-    for_words(word, std::make_integer_sequence<int, RPL * DW>{});
+      now[w0 + j] = ign;
+    }
 #pragma unroll
-    for (int i = 0; i < RPL; ++i)
-#pragma unroll
-      for (int k = 0; k < DW; ++k) {
-        T[i][k] = nT[i][k];
-        B[i][k] = nB[i][k];
-      }
+    for (int j = 0; j < N; ++j) B[j] = nB[j];
   }
   burnt = group_sum_i(burnt, 64);
-  if (lane == 0) a.burnt[r] = burnt;
+  if ((tid & 63) == 0) sh_burnt[tid >> 6] = burnt;
+  __syncthreads();
+  if (tid == 0) {
+    int total = 0;
+    for (int w = 0; w < THREADS / 64; ++w) total += sh_burnt[w];
+    a.burnt[blockIdx.x] = total;
+  }
 }
 
 // STRIDE = 1: one replication per lane; 64: one working lane per wavefront
@@ -270,14 +282,22 @@ __global__ void ff_simt_kernel(FfArgs a) {
 // 6.23 / 6.13).
 constexpr uint32_t RARE_TF = 2147484u;  // f < 5e-4
 
-template <int GRID>
-hipError_t wave_launch(const FfArgs &a, uint32_t wg, hipStream_t s) {
-  const uint32_t wpb = wg / 64;
-  const uint64_t blocks = (a.n_reps + wpb - 1) / wpb;
-  const dim3 g((uint32_t)blocks), b(wg);
-  if (a.tf < RARE_TF) hipLaunchKernelGGL((ff_wave_kernel<GRID, true>), g, b, 0, s, a);
-  else hipLaunchKernelGGL((ff_wave_kernel<GRID, false>), g, b, 0, s, a);
-  return hipGetLastError();
+template <int GRID, int N>
+hipError_t wave_launch(const FfArgs &a, hipStream_t s) {
+  // at most 2^22 workgroups, 2^31 lanes, per launch
+  constexpr uint64_t MOST = 1ull << 22;
+  for (uint64_t r0 = 0; r0 < a.n_reps; r0 += MOST) {
+    FfArgs b = a;
+    b.rep0 = a.rep0 + r0;
+    b.n_reps = a.n_reps - r0 < MOST ? a.n_reps - r0 : MOST;
+    b.burnt = a.burnt + r0;
+    const dim3 g((uint32_t)b.n_reps), t(GRID * GRID / 32 / N);
+    if (a.tf < RARE_TF) hipLaunchKernelGGL((ff_wave_kernel<GRID, N, true>), g, t, 0, s, b);
+    else hipLaunchKernelGGL((ff_wave_kernel<GRID, N, false>), g, t, 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <int GRID>
@@ -292,10 +312,11 @@ hipError_t simt_launch(const FfArgs &a, bool one_lane, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_ff_wave(const FfArgs &a, uint32_t wg, hipStream_t s) {
+hipError_t launch_ff_wave(const FfArgs &a, hipStream_t s) {
+  // one or two words per thread: the lines follow the times at ff_wave_kernel
   switch (a.grid) {
-    case 64: return wave_launch<64>(a, wg, s);
-    case 128: return wave_launch<128>(a, wg, s);
+    case 64: return a.n_reps <= 1500 ? wave_launch<64, 1>(a, s) : wave_launch<64, 2>(a, s);
+    case 128: return a.n_reps <= 512 ? wave_launch<128, 1>(a, s) : wave_launch<128, 2>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -124,8 +124,9 @@ struct FfArgs {
   uint64_t n_reps;
   int32_t *burnt;
   uint32_t *state;  // SIMT only: 2 planes * grid rows * grid/32 words * n_reps
+  uint64_t rep0;    // WAVE only: replication id of output 0
 };
-hipError_t launch_ff_wave(const FfArgs &a, uint32_t workgroup, hipStream_t s);
+hipError_t launch_ff_wave(const FfArgs &a, hipStream_t s);
 hipError_t launch_ff_simt(const FfArgs &a, bool one_lane, hipStream_t s);
 
 // ------------------------------------------------------------ Monte Carlo pi

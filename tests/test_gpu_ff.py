@@ -82,3 +82,17 @@ def test_ff_lightning_forms_bit_exact(gpu, grid, p, f):
     R, T = 9, 90
     _, got = _run(WAVE, grid, T, R, p, f, seed=5)
     assert np.array_equal(got, core.ff_many(5, R, grid, T, p, f, threads=core.default_threads()))
+
+
+@pytest.mark.parametrize("grid,R", [(128, 1), (128, 512), (128, 513), (64, 3), (64, 1500),
+                                    (64, 1501)])
+def test_ff_workgroup_shapes_bit_exact(gpu, grid, R):
+    # every number of wavefronts per replication, on both sides of each line;
+    # edge rows and columns wrap through the shared plane
+    announce("ff shapes", grid, R)
+    T, p, f = 40, 0.06, 2e-3
+    _, got = _run(WAVE, grid, T, R, p, f, seed=9)
+    ids = sorted({0, R // 2, R - 1})
+    ref = core.ff_many(9, ids, grid, T, p, f, threads=len(ids))
+    assert np.all(ref > 0)
+    assert np.array_equal(got[ids], ref)
