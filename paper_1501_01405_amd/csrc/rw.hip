@@ -1,9 +1,9 @@
 // Lattice random-walk replication engines (paper section 5.1, third model).
 //
 // WAVE mapping: one replication per wavefront, lane w = walker w. The
-// replication's visited-site bitmap (grid^2 bits, 512 B at 64x64) lives in
-// LDS and every move sets its bit with an LDS atomic or; at the end the
-// lanes popcount the bitmap and sum squared displacements across the wave.
+// replication's visited sites are a byte map in LDS (SiteMap) that every move
+// marks with one byte store; at the end the lanes count it and sum squared
+// displacements across the wave.
 //
 // With few replications that form leaves the chip idle and each wave walks
 // its 1000 steps one after the other. The walk is a prefix sum of
@@ -14,8 +14,9 @@
 // segment from there, marking the sites. Both forms give identical outputs;
 // the launcher picks by the number of replications.
 //
-// Optionally (PW) every walker also marks a bitmap of its own, in global
-// memory, and output 2 is the sum over walkers of their popcounts.
+// Optionally every walker also marks a bitmap of its own, in global memory,
+// and output 2 is the sum over walkers of their popcounts; those forms
+// (rw_sites_kernel, rw_seg_sites_kernel) keep the union as a bitmap in LDS.
 //
 // SIMT mapping: one replication per lane; the lane walks its walkers one
 // after the other and keeps the replication's bitmap in global memory, the
@@ -89,171 +90,186 @@ __device__ __forceinline__ void walk16(uint32_t word, uint32_t g, uint32_t steps
   }
 }
 
-// (a << SH) + b and (a << SH) | b as one instruction each (the compiler
-// splits the shift of a sign-extended field into two otherwise).
-template <int SH>
-__device__ __forceinline__ uint32_t lshl_add(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "i"(SH), "v"(b));
-  return r;
-}
-template <int SH>
-__device__ __forceinline__ uint32_t lshl_or(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "i"(SH), "v"(b));
-  return r;
-}
-
-// The 16 moves of a word as sign-extended 2-bit dx and dy fields, so that a
-// move's components are one bit-field extract each: d = 0 (+x) -> dx 01,
-// 1 (-x) -> dx 11, 2 (+y) -> dy 01, 3 (-y) -> dy 11, 0 elsewhere.
-__device__ __forceinline__ void split_moves(uint32_t word, uint32_t &DX, uint32_t &DY) {
-  constexpr uint32_t M = 0x55555555u;
-  const uint32_t L = word & M, H = (word >> 1) & M;  // low and high bit of each field
-  DX = (H ^ M) | ((L & ~H) << 1);
-  DY = H | ((H & L) << 1);
-}
-
-// Mark `mask` in the LDS word at byte address `addr`.
-__device__ __forceinline__ void lds_or(uint32_t addr, uint32_t mask) {
-  typedef __attribute__((address_space(3))) uint32_t lds_u32;
-  __atomic_fetch_or((lds_u32 *)(uintptr_t)addr, mask, __ATOMIC_RELAXED);
-}
-
-// Up to 16 moves of every lane of a wavefront whose lanes are all walkers,
-// on a GRID >= 32 torus, marking a row-major LDS bitmap (GRID / 32 words
-// per row) at LDS byte address `base`. The walker keeps X and YB = Y *
-// GRID / 8, the byte offset of its row (both unwrapped): a site's word is at
-// base | (YB & rows) | ((X >> 3) & cols), its bit X & 31. Marks gather in
-// the lane's pending word (paddr, pmask) while the walker stays in that
-// word (an x move does, 31 times in 32) and reach LDS, as one or, when it
-// leaves: about half the moves need no LDS operation.
-// LDS byte address of the bitmap word holding site (X, Y) of the lean
-// forms, from X and YB = Y * GRID / 8 (both unwrapped).
+// The walk's visited-site map of the forms without per-walker counts: one
+// byte per site in 64 KiB of LDS, so that a mark is a plain byte store and
+// its address costs one instruction. Byte 0 of the address holds x, byte 1
+// holds y, each in the top bits of its byte: a move adds +-(1 << SH) to one
+// of them and the torus wraps where the byte does. The low SH bits of the two
+// bytes are free: they number the wavefronts (replications) that share the
+// 64 KiB, so the space is full. Grids below 64 walk on the 64-torus and are
+// folded when counted (a site is its copies modulo the grid).
 template <int GRID>
-__device__ __forceinline__ uint32_t lean_word_addr(int X, int YB, uint32_t base) {
-  constexpr int ROWB = GRID / 8;
-  constexpr uint32_t ROWS = (uint32_t)(GRID * ROWB - 1) & ~(uint32_t)(ROWB - 1);
-  constexpr uint32_t COLS = (uint32_t)(ROWB - 1) & ~3u;
-  constexpr int LOG_COLW = GRID == 128 ? 2 : 1;
-  const uint32_t row = ((uint32_t)YB & ROWS) | base;
-  return COLS ? lshl_or<2>(__builtin_amdgcn_ubfe((uint32_t)X, 5, LOG_COLW), row) : row;
+struct SiteMap {
+  static constexpr int SH = GRID == 128 ? 1 : 2;  // free low bits per byte
+  static constexpr int TORUS = 256 >> SH;         // 128 or 64
+  static constexpr int REPS = 1 << (2 * SH);      // replications that fit
+  static constexpr uint32_t LOW = (1u << SH) - 1;
+  // byte 0 and byte 1 of the address of site (x, y) of replication slot i
+  // (in the low bytes; they run unwrapped above)
+  static __device__ __forceinline__ int byte0(int x, uint32_t i) {
+    return (int)((uint32_t)x << SH) | (int)(i & LOW);
+  }
+  static __device__ __forceinline__ int byte1(int y, uint32_t i) {
+    return (int)((uint32_t)y << SH) | (int)((i >> SH) & LOW);
+  }
+};
+
+// The address made of the low bytes of X and Y (which run unwrapped above).
+__device__ __forceinline__ uint32_t map_address(int X, int Y) {
+  return __builtin_amdgcn_perm((uint32_t)Y, (uint32_t)X, 0x0c0c0400u);
 }
 
+// Moves 0 .. n - 1 (n <= 16) of a word by one walker at (X, Y) (site << SH |
+// slot bits), each marked in the map. Full words take four moves' deltas at
+// once: the word's 2-bit fields, spread to bytes, select bytes of a table.
+template <int SH>
+__device__ __forceinline__ void walk_word(uint32_t word, uint32_t n, int &X, int &Y,
+                                          uint8_t *map) {
+  constexpr uint32_t P1 = 1u << SH, M1 = 256u - P1;  // +1 and -1 site, as bytes
+  constexpr uint32_t TX = P1 | M1 << 8, TY = P1 << 16 | M1 << 24;
+  if (n >= 16u) {
+    uint32_t dx[4], dy[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t sel = (word >> (2 * k)) & 0x03030303u;  // moves k, 4 + k, 8 + k, 12 + k
+      dx[k] = __builtin_amdgcn_perm(0u, TX, sel);
+      dy[k] = __builtin_amdgcn_perm(0u, TY, sel);
+    }
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      X += (int)(int8_t)(dx[m & 3] >> (8 * (m >> 2)));
+      Y += (int)(int8_t)(dy[m & 3] >> (8 * (m >> 2)));
+      map[map_address(X, Y)] = 1;
+    }
+  } else {
+    for (uint32_t m = 0; m < n; ++m) {
+      int ddx, ddy;
+      step_delta((word >> (2 * m)) & 3u, ddx, ddy);
+      X += ddx << SH;
+      Y += ddy << SH;
+      map[map_address(X, Y)] = 1;
+    }
+  }
+}
+
+__device__ __forceinline__ uint32_t moves_left(uint32_t g, uint32_t end) {
+  return g < end ? min(16u, end - g) : 0u;
+}
+
+// Moves g .. end - 1 (g a multiple of 64) of walker w of replication rep,
+// from Philox blocks.
+template <int SH>
+__device__ __forceinline__ void walk_blocks(uint32_t g, uint32_t end, uint32_t w, uint32_t rep,
+                                            uint32_t k0, uint32_t k1, int &X, int &Y,
+                                            uint8_t *map) {
+  for (; g + 64u <= end; g += 64) {
+    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
+    walk_word<SH>(b.x, 16u, X, Y, map);
+    walk_word<SH>(b.y, 16u, X, Y, map);
+    walk_word<SH>(b.z, 16u, X, Y, map);
+    walk_word<SH>(b.w, 16u, X, Y, map);
+  }
+  if (g < end) {
+    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
+    walk_word<SH>(b.x, moves_left(g, end), X, Y, map);
+    walk_word<SH>(b.y, moves_left(g + 16, end), X, Y, map);
+    walk_word<SH>(b.z, moves_left(g + 32, end), X, Y, map);
+    walk_word<SH>(b.w, moves_left(g + 48, end), X, Y, map);
+  }
+}
+
+// Marked sites of replication slot i among those thread j of n counts.
 template <int GRID>
-__device__ __forceinline__ void walk16_full(uint32_t word, uint32_t g, uint32_t steps, int &X,
-                                           int &YB, uint32_t base, uint32_t &paddr,
-                                           uint32_t &pmask) {
-  static_assert(GRID >= 32, "a row of the bitmap is at least one word");
-  constexpr int ROWB = GRID / 8;                           // bytes per row
-  constexpr int LOG_ROWB = GRID == 32 ? 2 : GRID == 64 ? 3 : 4;
-  constexpr uint32_t ROWS = (uint32_t)(GRID * ROWB - 1) & ~(uint32_t)(ROWB - 1);
-  constexpr uint32_t COLS = (uint32_t)(ROWB - 1) & ~3u;
-  constexpr int LOG_COLW = GRID == 128 ? 2 : 1;  // bits of the word index within a row
-  uint32_t DX, DY;
-  split_moves(word, DX, DY);
-  auto move = [&](int i) {
-    X += __builtin_amdgcn_sbfe((int)DX, 2 * i, 2);
-    YB = (int)lshl_add<LOG_ROWB>((uint32_t)__builtin_amdgcn_sbfe((int)DY, 2 * i, 2), (uint32_t)YB);
-    const uint32_t row = ((uint32_t)YB & ROWS) | base;
-    const uint32_t addr =
-        COLS ? lshl_or<2>(__builtin_amdgcn_ubfe((uint32_t)X, 5, LOG_COLW), row) : row;
-    if (addr != paddr) {
-      lds_or(paddr, pmask);
-      pmask = 0u;
-    }
-    paddr = addr;
-    pmask |= 1u << ((uint32_t)X & 31u);
-  };
-  if (g + 16u <= steps) {
+__device__ __forceinline__ int count_sites(const uint8_t *map, uint32_t i, int j, int n) {
+  using S = SiteMap<GRID>;
+  // a row is 256 bytes: 16 vectors of 16 (TORUS / 16 sites each)
+  constexpr int T = S::TORUS, COPIES = T / (GRID < T ? GRID : T);
+  constexpr int VROW = 16 / COPIES, VECS = VROW * GRID;
+  const uint32_t b = (i >> S::SH) & S::LOW;
+  uint32_t acc = 0;
+  for (int v = j; v < VECS; v += n) {
+    const int vx = v % VROW, y = v / VROW;
+    uint4 q = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) move(i);
-  } else {
-    for (int i = 0; g + (uint32_t)i < steps; ++i) move(i);
-  }
-}
-
-// The walk of a wavefront whose 64 lanes are all walkers, on Philox
-// streams, in the lean form (GRID >= 32, no per-walker bitmaps); false when
-// the form does not apply and nothing was done.
-template <int GRID, bool PW>
-__device__ __forceinline__ bool lean_walk(const RwArgs &a, uint64_t r, uint32_t w, uint32_t k0,
-                                          uint32_t k1, uint32_t *bm, int &X, int &Y) {
-  if constexpr (GRID >= 32 && !PW) {
-    if (a.walkers != 64u) return false;
-    if (r < a.n_reps) {
-      constexpr int LOG_ROWB = GRID == 32 ? 2 : GRID == 64 ? 3 : 4;
-      // the bitmap's LDS byte address (a multiple of its size, so the
-      // site's offset can be or-ed into it)
-      typedef __attribute__((address_space(3))) uint32_t lds_u32;
-      const uint32_t base = (uint32_t)(uintptr_t)(lds_u32 *)bm;
-      int YB = Y << LOG_ROWB;
-      // the start site is the first pending mark
-      const int c0 = Y * GRID + X;
-      uint32_t paddr = base + 4u * ((uint32_t)c0 >> 5), pmask = 1u << (c0 & 31);
-      for (uint32_t g = 0; g < a.steps; g += 64) {
-        const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
-        walk16_full<GRID>(b.x, g, a.steps, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.y, g + 16, a.steps, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.z, g + 32, a.steps, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.w, g + 48, a.steps, X, YB, base, paddr, pmask);
-      }
-      lds_or(paddr, pmask);
-      Y = YB >> LOG_ROWB;  // arithmetic shift: YB is Y times a power of two
-    }
-    return true;
-  } else {
-    (void)a, (void)r, (void)w, (void)k0, (void)k1, (void)bm, (void)X, (void)Y;
-    return false;
-  }
-}
-
-// Pass 2 of the segmented walk in the lean form (every lane one segment of
-// a walker, Philox, GRID >= 32, no per-walker bitmaps): the segment's moves
-// from its start (X, Y), marking through the lane's pending word, which
-// starts empty (the start site is the previous segment's last one, or the
-// walker's start, marked apart); false when the form does not apply and
-// nothing was done. `first`: the words of the segment's first 64 moves.
-template <int GRID, int RNG, bool PW>
-__device__ __forceinline__ bool lean_segment(const RwArgs &a, uint64_t r, uint32_t w, uint32_t k0,
-                                             uint32_t k1, uint32_t t0, uint32_t t1,
-                                             const uint32_t (&first)[4], uint32_t *bm, int X,
-                                             int Y) {
-  if constexpr (GRID >= 32 && !PW && RNG == RNG_PHILOX) {
-    if (a.walkers != 64u) return false;
-    constexpr int LOG_ROWB = GRID == 32 ? 2 : GRID == 64 ? 3 : 4;
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
-    const uint32_t base = (uint32_t)(uintptr_t)(lds_u32 *)bm;
-    int YB = (int)((uint32_t)Y << LOG_ROWB);
-    uint32_t paddr = lean_word_addr<GRID>(X, YB, base), pmask = 0u;
-    if (t0 < t1) {
+    for (int cy = 0; cy < COPIES; ++cy)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        walk16_full<GRID>(first[j], t0 + 16u * j, t1, X, YB, base, paddr, pmask);
-      for (uint32_t g = t0 + 64; g < t1; g += 64) {
-        const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
-        walk16_full<GRID>(b.x, g, t1, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.y, g + 16, t1, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.z, g + 32, t1, X, YB, base, paddr, pmask);
-        walk16_full<GRID>(b.w, g + 48, t1, X, YB, base, paddr, pmask);
+      for (int cx = 0; cx < COPIES; ++cx) {
+        const uint32_t at = ((uint32_t)((y + cy * GRID) << S::SH) | b) << 8;
+        const uint4 p = *(const uint4 *)(map + at + 16 * (vx + cx * VROW));
+        q.x |= p.x;
+        q.y |= p.y;
+        q.z |= p.z;
+        q.w |= p.w;
       }
+    acc += (q.x + q.y) + (q.z + q.w);  // byte sums: at most 4 x 32 a byte and thread
+  }
+  acc >>= 8u * (i & S::LOW);
+  if (S::SH == 1) return (int)((acc & 0xFFu) + ((acc >> 16) & 0xFFu));
+  return (int)(acc & 0xFFu);
+}
+
+__device__ __forceinline__ void start_site(uint32_t w, int grid, int &x0, int &y0) {
+  x0 = (int)(((w % 8u) * (grid / 8) + grid / 16) % grid);
+  y0 = (int)(((w / 8u) * (grid / 8) + grid / 16) % grid);
+}
+
+// One replication per wavefront, lane w = walker w (fewer than 64 walkers:
+// the other lanes are masked off for the whole walk). A move is 4.5
+// vector instructions (its share of the deltas' tables, two adds, the
+// address) and one byte store, where a bit map took 11.2 and one atomic or.
+// Bound: LDS, 6.8 cycles a store and compute unit, of which 4.8 are bank
+// conflicts of 64 walkers at random columns. 64 walkers x 1000 steps on 64 x
+// 64: 16384 replications 0.289 ms before, 0.204 now; 35 walkers x 700, 8192
+// replications 0.60 / 0.059 (no walkers' lanes marking a spare word).
+template <int GRID, int RNG, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void rw_map_kernel(RwArgs a) {
+  using S = SiteMap<GRID>;
+  static_assert(WAVES <= S::REPS, "one map slot per wavefront");
+  __shared__ __attribute__((aligned(16))) uint8_t map[65536];
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = threadIdx.x >> 6;
+  const uint64_t r = (uint64_t)blockIdx.x * WAVES + wave;
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  for (int i = threadIdx.x; i < 65536 / 16; i += 64 * WAVES)
+    ((uint4 *)map)[i] = uint4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  int sd = 0;
+  if (r < a.n_reps && (uint32_t)lane < a.walkers) {
+    int x0, y0;
+    start_site((uint32_t)lane, GRID, x0, y0);
+    const int X0 = S::byte0(x0, wave), Y0 = S::byte1(y0, wave);
+    int X = X0, Y = Y0;
+    map[map_address(X, Y)] = 1;
+    const uint32_t rep = (uint32_t)(a.rep0 + r);
+    if (RNG == RNG_TAUS88) {
+      Taus t = taus_seed(TAG_RW, 0u, rep, k0, k1);
+      taus_jump(t, a.taus_walk + (uint64_t)lane * TAUS_COLS);  // to the walker's run
+      uint32_t g = 0;
+      for (; g + 16u <= a.steps; g += 16) walk_word<S::SH>(taus_next(t), 16u, X, Y, map);
+      if (g < a.steps) walk_word<S::SH>(taus_next(t), a.steps - g, X, Y, map);
+    } else {
+      walk_blocks<S::SH>(0u, a.steps, (uint32_t)lane, rep, k0, k1, X, Y, map);
     }
-    lds_or(paddr, pmask);
-    return true;
-  } else {
-    (void)a, (void)r, (void)w, (void)k0, (void)k1, (void)t0, (void)t1, (void)first, (void)bm,
-        (void)X, (void)Y;
-    return false;
+    const int ux = (X - X0) >> S::SH, uy = (Y - Y0) >> S::SH;
+    sd = ux * ux + uy * uy;
+  }
+  __syncthreads();
+  const int cnt = group_sum_i(count_sites<GRID>(map, wave, lane, 64), 64);
+  const int ssd = group_sum_i(sd, 64);
+  if (lane == 0 && r < a.n_reps) {
+    a.ssd[r] = ssd;
+    a.distinct[r] = cnt;
   }
 }
 
-template <int GRID, int RNG, bool PW>
-__global__ void rw_wave_kernel(RwArgs a) {
+// The walk with per-walker site counts: the union's bitmap (grid^2 bits) in
+// LDS, set with atomic ors, and a bitmap of its own per walker in global
+// memory.
+template <int GRID, int RNG>
+__global__ void rw_sites_kernel(RwArgs a) {
   constexpr int WORDS = GRID * GRID / 32;
-  constexpr int WB = PW ? WB_OWN : WB_NONE;
-  // aligned to the largest bitmap (128 x 128 bits), so that each
-  // wavefront's bitmap address is a multiple of its size
-  extern __shared__ __attribute__((aligned(2048))) uint32_t lds[];
+  constexpr int WB = WB_OWN;
+  extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t r = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
@@ -270,7 +286,7 @@ __global__ void rw_wave_kernel(RwArgs a) {
   if (active) mark(bm, y0 * GRID + x0);
   // this walker's own bitmap (global memory, owned by this lane)
   uint32_t *wb = nullptr;
-  if (PW && active) {
+  if (active) {
     wb = a.walker_bitmaps + (r * a.walkers + w) * WORDS;
     for (int i = 0; i < WORDS; ++i) wb[i] = 0u;
     mark_walker<WB>(wb, y0 * GRID + x0, true);
@@ -281,8 +297,6 @@ __global__ void rw_wave_kernel(RwArgs a) {
     taus_jump(t, a.taus_walk + (uint64_t)w * TAUS_COLS);  // to walker w's run
     for (uint32_t g = 0; g < a.steps; g += 16)
       walk16<GRID, true, WB>(taus_next(t), g, a.steps, active, X, Y, bm, spare, wb);
-  } else if (lean_walk<GRID, PW>(a, r, w, k0, k1, bm, X, Y)) {
-    // every lane a walker (or the whole wavefront idle): done in the lean form
   } else {
     for (uint32_t g = 0; g < a.steps; g += 64) {
       const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
@@ -300,15 +314,13 @@ __global__ void rw_wave_kernel(RwArgs a) {
   const int sd = active ? ux * ux + uy * uy : 0;
   const int ssd = group_sum_i(sd, 64);
   int mine = 0;
-  if (PW) {
-    if (active)
-      for (int i = 0; i < WORDS; ++i) mine += __popc(wb[i]);
-    mine = group_sum_i(mine, 64);
-  }
+  if (active)
+    for (int i = 0; i < WORDS; ++i) mine += __popc(wb[i]);
+  mine = group_sum_i(mine, 64);
   if (lane == 0 && r < a.n_reps) {
     a.ssd[r] = ssd;
     a.distinct[r] = cnt;
-    if (PW) a.walker_sites[r] = mine;
+    a.walker_sites[r] = mine;
   }
 }
 
@@ -387,171 +399,237 @@ __device__ __forceinline__ int block_sum_i(int v, int *sh) {
   return t;
 }
 
-// One workgroup per replication, 16 lanes per walker.
-template <int GRID, int RNG, bool PW>
+// Pass 1 of the segmented walk: the net displacement of walker w's moves
+// t0 .. t1 - 1 (t0 a multiple of 64). The words of the first 64 moves are
+// kept for pass 2 (for up to 1024 steps that is the whole segment, and pass
+// 2 draws nothing).
+struct Segment {
+  int dx = 0, dy = 0;
+  uint32_t first[4] = {0u, 0u, 0u, 0u};
+  Taus after;  // taus88: the state after those words
+};
+template <int RNG>
+__device__ __forceinline__ void words64(Taus &ts, uint32_t g, uint32_t t1, uint32_t w, uint32_t rep,
+                                        uint32_t k0, uint32_t k1, uint32_t (&wd)[4]) {
+  if (RNG == RNG_TAUS88) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) wd[j] = g + 16u * j < t1 ? taus_next(ts) : 0u;
+  } else {
+    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
+    wd[0] = b.x;
+    wd[1] = b.y;
+    wd[2] = b.z;
+    wd[3] = b.w;
+  }
+}
+template <int RNG>
+__device__ __forceinline__ Segment segment_pass1(const RwArgs &a, uint32_t rep, uint32_t w,
+                                                 uint32_t sgi, uint32_t t0, uint32_t t1,
+                                                 uint32_t k0, uint32_t k1) {
+  Segment s;
+  Taus ts;
+  if (RNG == RNG_TAUS88) {
+    ts = taus_seed(TAG_RW, 0u, rep, k0, k1);
+    // to walker w's run, then to this segment's start within it (w <= 63)
+    taus_jump(ts, a.taus_walk + (uint64_t)w * TAUS_COLS);
+    taus_jump(ts, a.taus_walk + (uint64_t)(TAUS_WALK_WALKERS + sgi) * TAUS_COLS);
+  }
+  s.after = ts;
+  for (uint32_t g = t0; g < t1; g += 64) {
+    uint32_t wd[4];
+    words64<RNG>(ts, g, t1, w, rep, k0, k1, wd);
+    if (g == t0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s.first[j] = wd[j];
+      s.after = ts;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) word_displacement(wd[j], g + 16u * j, t1, s.dx, s.dy);
+  }
+  return s;
+}
+// Inclusive sum over the walker's 16 segments.
+__device__ __forceinline__ int segment_scan(int v, uint32_t sgi) {
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const int p = __shfl_up(v, o, 16);
+    if ((int)sgi >= o) v += p;
+  }
+  return v;
+}
+
+// One workgroup per replication, 16 lanes per walker; pass 2 marks the sites
+// in the byte map (slot 0).
+template <int GRID, int RNG>
 __global__ __launch_bounds__(1024) void rw_seg_kernel(RwArgs a, uint32_t seg) {
+  using S = SiteMap<GRID>;
+  __shared__ __attribute__((aligned(16))) uint8_t map[65536];
+  __shared__ int sh_red[16];
+  const int tid = threadIdx.x;
+  const uint32_t w = (uint32_t)tid >> 4, sgi = (uint32_t)tid & 15u;
+  const uint32_t rep = (uint32_t)(a.rep0 + blockIdx.x);
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  for (int v = tid; v < 16 * S::TORUS; v += blockDim.x)  // slot 0's rows
+    *(uint4 *)(map + ((v >> 4) << (S::SH + 8)) + 16 * (v & 15)) = uint4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  const bool active = w < a.walkers;
+  const uint32_t t0 = min(a.steps, sgi * seg), t1 = min(a.steps, t0 + seg);
+  const Segment s1 = segment_pass1<RNG>(a, rep, w, sgi, t0, t1, k0, k1);
+  const int sx = segment_scan(s1.dx, sgi), sy = segment_scan(s1.dy, sgi);
+  if (active) {
+    int x0, y0;
+    start_site(w, GRID, x0, y0);
+    if (sgi == 0) map[map_address(S::byte0(x0, 0), S::byte1(y0, 0))] = 1;
+    // pass 2: the segment's moves from its (unwrapped) start
+    int X = S::byte0(x0 + sx - s1.dx, 0);
+    int Y = S::byte1(y0 + sy - s1.dy, 0);
+    if (t0 < t1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        walk_word<S::SH>(s1.first[j], moves_left(t0 + 16u * j, t1), X, Y, map);
+      if (RNG == RNG_TAUS88) {
+        Taus ts = s1.after;
+        for (uint32_t g = t0 + 64; g < t1; g += 16)
+          walk_word<S::SH>(taus_next(ts), moves_left(g, t1), X, Y, map);
+      } else {
+        walk_blocks<S::SH>(t0 + 64, t1, w, rep, k0, k1, X, Y, map);
+      }
+    }
+  }
+  __syncthreads();
+  // the walkers' squared end displacements (the last segment's lane holds the
+  // walker's total) and the marked sites
+  const int sd = block_sum_i((active && sgi == 15) ? sx * sx + sy * sy : 0, sh_red);
+  const int cnt = block_sum_i(count_sites<GRID>(map, 0, tid, blockDim.x), sh_red);
+  if (tid == 0) {
+    a.ssd[blockIdx.x] = sd;
+    a.distinct[blockIdx.x] = cnt;
+  }
+}
+
+// The segmented form with per-walker site counts: a bitmap in LDS for the
+// union and one per walker, shared by its 16 lanes, in global memory.
+template <int GRID, int RNG>
+__global__ __launch_bounds__(1024) void rw_seg_sites_kernel(RwArgs a, uint32_t seg) {
   constexpr int WORDS = GRID * GRID / 32;
-  constexpr int WB = PW ? WB_SHARED : WB_NONE;
-  // + the inactive lanes' spare word; aligned to the largest bitmap (128 x
-  // 128 bits), so that the lean form can or a site's offset into its address
-  __shared__ __attribute__((aligned(2048))) uint32_t bm[WORDS + 1];
+  __shared__ uint32_t bm[WORDS + 1];  // + the inactive lanes' spare word
   __shared__ int sh_red[16];
   const int tid = threadIdx.x;
   const uint32_t w = (uint32_t)tid >> 4, sgi = (uint32_t)tid & 15u;
   const uint64_t r = blockIdx.x;
+  const uint32_t rep = (uint32_t)(a.rep0 + r);
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   for (int i = tid; i < WORDS; i += blockDim.x) bm[i] = 0u;
-  // the walker's own bitmap, shared by its 16 segment lanes (global memory)
   const bool active = w < a.walkers;
   uint32_t *wb = nullptr;
-  if (PW && active) {
+  if (active) {
     wb = a.walker_bitmaps + (r * a.walkers + w) * WORDS;
     for (int i = (int)sgi; i < WORDS; i += 16) wb[i] = 0u;
   }
   __syncthreads();
   const uint32_t t0 = min(a.steps, sgi * seg), t1 = min(a.steps, t0 + seg);
-
-  // pass 1: the segment's net displacement (seg is a multiple of 64 steps)
-  Taus ts;
-  if (RNG == RNG_TAUS88) {
-    ts = taus_seed(TAG_RW, 0u, (uint32_t)(a.rep0 + r), k0, k1);
-    // to walker w's run, then to this segment's start within it (w <= 63)
-    taus_jump(ts, a.taus_walk + (uint64_t)w * TAUS_COLS);
-    taus_jump(ts, a.taus_walk + (uint64_t)(TAUS_WALK_WALKERS + sgi) * TAUS_COLS);
-  }
-  // the first 64 moves' words are kept for pass 2 (for up to 1024 steps
-  // that is the whole segment, and pass 2 draws nothing)
-  uint32_t first[4] = {0u, 0u, 0u, 0u};
-  Taus ts1 = ts;  // taus88: the state after those words
-  int dx = 0, dy = 0;
-  for (uint32_t g = t0; g < t1; g += 64) {
-    uint32_t wd[4];
-    if (RNG == RNG_TAUS88) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wd[j] = g + 16u * j < t1 ? taus_next(ts) : 0u;
-    } else {
-      const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
-      wd[0] = b.x;
-      wd[1] = b.y;
-      wd[2] = b.z;
-      wd[3] = b.w;
-    }
-    if (g == t0) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) first[j] = wd[j];
-      ts1 = ts;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) word_displacement(wd[j], g + 16u * j, t1, dx, dy);
-  }
-  // inclusive scan over the walker's 16 segments, then this segment's start
-  int sx = dx, sy = dy;
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) {
-    const int px = __shfl_up(sx, o, 16), py = __shfl_up(sy, o, 16);
-    if ((int)sgi >= o) {
-      sx += px;
-      sy += py;
-    }
-  }
-  const int x0 = (int)(((w % 8u) * (GRID / 8) + GRID / 16) % GRID);
-  const int y0 = (int)(((w / 8u) * (GRID / 8) + GRID / 16) % GRID);
+  const Segment s1 = segment_pass1<RNG>(a, rep, w, sgi, t0, t1, k0, k1);
+  const int sx = segment_scan(s1.dx, sgi), sy = segment_scan(s1.dy, sgi);
+  int x0, y0;
+  start_site(w, GRID, x0, y0);
   if (active && sgi == 0) {
     mark(bm, y0 * GRID + x0);
-    mark_walker<WB>(wb, y0 * GRID + x0, true);
+    mark_walker<WB_SHARED>(wb, y0 * GRID + x0, true);
   }
-  // unwrapped position at the segment's start
-  int X = x0 + (sx - dx), Y = y0 + (sy - dy);
-
-  // pass 2: replay the segment's moves from its start
-  if (lean_segment<GRID, RNG, PW>(a, r, w, k0, k1, t0, t1, first, bm, X, Y)) {
-    // every lane a walker's segment: done in the lean form
-  } else {
+  // pass 2: the segment's moves from its (unwrapped) start
+  int X = x0 + (sx - s1.dx), Y = y0 + (sy - s1.dy);
   if (t0 < t1) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      walk16<GRID, true, WB>(first[j], t0 + 16u * j, t1, active, X, Y, bm, &bm[WORDS], wb);
+      walk16<GRID, true, WB_SHARED>(s1.first[j], t0 + 16u * j, t1, active, X, Y, bm, &bm[WORDS],
+                                    wb);
   }
-  ts = ts1;
+  Taus ts = s1.after;
   for (uint32_t g = t0 + 64; g < t1; g += 64) {
     uint32_t wd[4];
-    if (RNG == RNG_TAUS88) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wd[j] = g + 16u * j < t1 ? taus_next(ts) : 0u;
-    } else {
-      const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
-      wd[0] = b.x;
-      wd[1] = b.y;
-      wd[2] = b.z;
-      wd[3] = b.w;
-    }
+    words64<RNG>(ts, g, t1, w, rep, k0, k1, wd);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      walk16<GRID, true, WB>(wd[j], g + 16u * j, t1, active, X, Y, bm, &bm[WORDS], wb);
-  }
+      walk16<GRID, true, WB_SHARED>(wd[j], g + 16u * j, t1, active, X, Y, bm, &bm[WORDS], wb);
   }
   __syncthreads();
-
-  // outputs: the walkers' squared end displacements (last segment's lane
-  // holds the walker's total) and the popcount of the union bitmap
   int mine = 0;
-  if (PW && active) {
+  if (active) {
     // read the walker's words back through the atomic unit (where the other
     // segment lanes' ors were performed)
     for (int i = (int)sgi; i < WORDS; i += 16) mine += __popc(atomicOr(&wb[i], 0u));
   }
   const int sd = block_sum_i((active && sgi == 15) ? sx * sx + sy * sy : 0, sh_red);
-  if (PW) mine = block_sum_i(mine, sh_red);
+  mine = block_sum_i(mine, sh_red);
   int cnt = 0;
   for (int i = tid; i < WORDS; i += blockDim.x) cnt += __popc(bm[i]);
   cnt = block_sum_i(cnt, sh_red);
   if (tid == 0) {
     a.ssd[r] = sd;
     a.distinct[r] = cnt;
-    if (PW) a.walker_sites[r] = mine;
+    a.walker_sites[r] = mine;
   }
 }
 
-// Replications up to which the segmented form is used (measured for 64
-// walkers x 1000 steps: 44 against 83 us at 1024 replications, 79 against
-// 87 at 2048, 149 against 146 at 4096): below, the sequential form leaves
-// the chip idle; above, its single pass over the moves is cheaper. On
-// taus88 streams every segment lane first jumps to its place (two tables
-// of 88 columns), so the sequential form wins earlier (64 x 1000: 39 against
-// 55 us at 128 replications, 57 against 56 at 512, 90 against 56 at 1024,
-// 148 against 78 at 2048).
-constexpr uint64_t RW_SEG_MAX_REPS = 2048;
-constexpr uint64_t RW_SEG_MAX_REPS_TAUS88 = 512;
+// Replications up to which the segmented form is used: below, one wavefront
+// per replication leaves the chip idle; above, its single pass over the moves
+// is cheaper (64 walkers x 1000 steps, segmented / one wavefront: 32
+// replications 10.2 / 22 us, 512 16 / 22, 700 20.4 / 22.6, 1024 25 / 22.5; on
+// taus88 streams every segment lane first jumps to its place, two tables of
+// 88 columns: 256 replications 26.0 / 26.7 us, 400 39 / 27).
+constexpr uint64_t RW_SEG_MAX_REPS = 768, RW_SEG_MAX_REPS_TAUS88 = 256;
+// ... and with per-walker site counts (1000 steps: 44 / 83 us at 1024
+// replications, 79 / 87 at 2048, 149 / 146 at 4096; taus88 57 / 56 at 512).
+constexpr uint64_t RW_SITES_SEG_MAX_REPS = 2048, RW_SITES_SEG_MAX_REPS_TAUS88 = 512;
+// Replications from which a workgroup of the byte-map form takes eight
+// wavefronts instead of four: four spread a run over the compute units (2500
+// replications 47 us against 58 with eight), but two workgroups fill a
+// compute unit's LDS, so eight keep more wavefronts on it (8192: 111 / 107).
+constexpr uint64_t RW_MAP8_MIN_REPS = 4096;
+
+template <int GRID, int WAVES>
+hipError_t map_launch(const RwArgs &a, hipStream_t s) {
+  const dim3 g((uint32_t)((a.n_reps + WAVES - 1) / WAVES)), b(64 * WAVES);
+  if (a.rng == RNG_TAUS88)
+    hipLaunchKernelGGL((rw_map_kernel<GRID, RNG_TAUS88, WAVES>), g, b, 0, s, a);
+  else
+    hipLaunchKernelGGL((rw_map_kernel<GRID, RNG_PHILOX, WAVES>), g, b, 0, s, a);
+  return hipGetLastError();
+}
 
 template <int GRID>
 hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
-  if (a.n_reps <= (a.rng == RNG_TAUS88 ? RW_SEG_MAX_REPS_TAUS88 : RW_SEG_MAX_REPS)) {
+  const bool sites = a.walker_sites != nullptr, taus = a.rng == RNG_TAUS88;
+  const uint64_t seg_max =
+      sites ? (taus ? RW_SITES_SEG_MAX_REPS_TAUS88 : RW_SITES_SEG_MAX_REPS)
+            : (taus ? RW_SEG_MAX_REPS_TAUS88 : RW_SEG_MAX_REPS);
+  if (a.n_reps <= seg_max) {
     // 16 lanes per walker; segments of whole Philox blocks (64 moves)
     const uint32_t threads = (16u * a.walkers + 63u) / 64u * 64u;
     const uint32_t seg = (a.steps + 16u * 64u - 1u) / (16u * 64u) * 64u;
     const dim3 g((uint32_t)a.n_reps), b(threads);
-    const bool pw = a.walker_sites != nullptr;
     if (a.rng == RNG_TAUS88) {
-      if (pw) hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_TAUS88, true>), g, b, 0, s, a, seg);
-      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_TAUS88, false>), g, b, 0, s, a, seg);
+      if (sites) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
+      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
     } else {
-      if (pw) hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_PHILOX, true>), g, b, 0, s, a, seg);
-      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_PHILOX, false>), g, b, 0, s, a, seg);
+      if (sites) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
+      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
     }
     return hipGetLastError();
+  }
+  if (!sites) {
+    if constexpr (GRID < 128)
+      if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
+    return map_launch<GRID, 4>(a, s);
   }
   const uint32_t wpb = wg / 64;
   const uint64_t blocks = (a.n_reps + wpb - 1) / wpb;
   const size_t lds = ((size_t)wpb * (GRID * GRID / 32) + 1) * sizeof(uint32_t);  // + spare
   const dim3 g((uint32_t)blocks), b(wg);
-  const bool pw = a.walker_sites != nullptr;
-  if (a.rng == RNG_TAUS88) {
-    if (pw) hipLaunchKernelGGL((rw_wave_kernel<GRID, RNG_TAUS88, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((rw_wave_kernel<GRID, RNG_TAUS88, false>), g, b, lds, s, a);
-  } else {
-    if (pw) hipLaunchKernelGGL((rw_wave_kernel<GRID, RNG_PHILOX, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((rw_wave_kernel<GRID, RNG_PHILOX, false>), g, b, lds, s, a);
-  }
+  if (a.rng == RNG_TAUS88)
+    hipLaunchKernelGGL((rw_sites_kernel<GRID, RNG_TAUS88>), g, b, lds, s, a);
+  else
+    hipLaunchKernelGGL((rw_sites_kernel<GRID, RNG_PHILOX>), g, b, lds, s, a);
   return hipGetLastError();
 }
 

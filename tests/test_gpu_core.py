@@ -185,3 +185,25 @@ def test_rw_consecutive_runs_of_different_sizes(gpu, rng):
         ref = core.rw_many(seed, ids, W, G, T, threads=4, rng=rng, walker_sites=True)
         for o in range(3):
             assert np.array_equal(ctx.output(o).cpu().numpy()[ids], ref[o]), (R, o)
+
+
+@pytest.mark.parametrize("grid,walkers,steps,R", [
+    (64, 64, 1000, 769), (64, 64, 65, 4095), (64, 64, 15, 4097), (64, 1, 2000, 771),
+    (64, 35, 64, 770), (32, 64, 333, 900), (32, 7, 1, 4100), (16, 64, 500, 800),
+    (16, 64, 129, 5000), (128, 64, 1000, 1001), (128, 50, 17, 4099), (64, 64, 1100, 768),
+    (16, 33, 1500, 3), (32, 64, 1025, 40), (128, 64, 2049, 40)])
+@pytest.mark.parametrize("rng", ["philox", "taus88"])
+def test_walk_site_map_bit_exact(gpu, grid, walkers, steps, R, rng):
+    # the byte map in its workgroup sizes and in the segmented form: torus
+    # wraps in both coordinates (few sites, long walks), grids folded from the
+    # 64-torus, idle lanes, walks that end inside a word or a block, and the
+    # last workgroup's idle wavefronts
+    announce("rw map", grid, walkers, steps, R, rng)
+    ctx = mrip.Context(mrip.MRIP_RW, mrip.rw_params(walkers, grid, steps), WAVE)
+    if rng == "taus88":
+        ctx.set_rng(mrip.MRIP_RNG_TAUS88)
+    ctx.run(R, seed=11)
+    ids = sorted({0, 1, R // 2, R - 2, R - 1})
+    ssd, dist = core.rw_many(11, ids, walkers, grid, steps, rng=rng)
+    assert np.array_equal(ctx.output(0).cpu().numpy()[ids], ssd)
+    assert np.array_equal(ctx.output(1).cpu().numpy()[ids], dist)
