@@ -7,6 +7,13 @@
 // (a2, b2) after (a1, b1) = (max(a2, a1 + b2), b1 + b2). That turns the
 // sequential Lindley recursion into a prefix scan.
 //
+// Bound of every wavefront engine: vector-ALU issue, one instruction per four
+// cycles per SIMD (the two logarithms of a customer take two slots each). A
+// full chunk of 16 customers per lane is 620 instructions (678 before the
+// fused b, the running first Philox product, the in-place DPP scan and the
+// fp64 sums): 4096 x 20000 customers 97 -> 87.5 us, 1024 x 1e5 over four
+// wavefronts 111 -> 100.7, the 64 x 32 plan 0.64 -> 0.59 ms.
+//
 // WAVE mapping (one replication per wavefront): a segment of 16 lanes takes
 // 16 P consecutive customers, P per lane from P/2 Philox blocks, composes
 // the lane's maps, runs a 4-step DPP inclusive scan (row_shr 1, 2, 4, 8;
@@ -65,17 +72,30 @@ struct Rep {
   uint64_t out;      // output index
 };
 
+// fp64 accumulator of fp32 partial sums (16 customers' worth): two
+// instructions per partial where a compensated fp32 sum takes four, and wide
+// enough that the sums of T, S and I are exact for all but a few of them, so
+// that a replication's fp32 means are the same bits whether one wavefront
+// runs it or eight (their fp64 sums differ by an ulp at most).
+struct Acc64 {
+  double v = 0.0;
+  __device__ __forceinline__ void add(float x) { v += (double)x; }
+  __device__ __forceinline__ void sub(float x) { v -= (double)x; }
+  __device__ __forceinline__ double value() const { return v; }
+};
+
 // Sums of T, S and I, and of the four martingale controls over customers
 // n >= K (FT forms only): S_n - E S, A_n - E A, and both weighted by T_{n-1}.
 // The waits follow as W_n = T_n - S_n: their sum is that of T less that of S.
 struct Sums {
-  Kahan t, s, i;
-  Kahan c[4];
+  Acc64 t, s, i;
+  Acc64 c[4];
 };
 
-// A lane's sum of waits from its sums of T and S.
-__device__ __forceinline__ float wait_sum(const Sums &x) {
-  return (x.t.sum - x.s.sum) - (x.t.comp - x.s.comp);
+// Sum over aligned groups of `width` lanes; every lane gets the total.
+__device__ __forceinline__ double group_sum_f64(double v, int width) {
+  for (int off = 1; off < width; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
 }
 
 // Prefix features, and the four controls over the prefix customers (n < K:
@@ -96,27 +116,36 @@ __device__ __forceinline__ float pick4(int q, float v0, float v1, float v2, floa
 constexpr int MM1_P = 16;
 
 // The variates of one chunk for this lane: P customers from P/2 blocks.
-template <int P>
+// Customer j's service time S and the net change b = S - A its map adds, one
+// fused multiply-add from the two logarithms; the forms with the controls
+// (FT) also keep log2 u of the interarrival time (A = qa L).
+template <int P, bool FT>
 struct Draw {
-  float A[P], S[P];
+  float S[P], b[P], L[FT ? P : 1];
 };
 
-template <int RPW, int P>
-__device__ __forceinline__ Draw<P> draw_chunk(uint64_t base, const Rep &d, uint32_t k0,
-                                              uint32_t k1) {
+template <int RPW, int P, bool FT>
+__device__ __forceinline__ Draw<P, FT> draw_chunk(uint64_t base, const Rep &d, uint32_t k0,
+                                                  uint32_t k1) {
   constexpr int S = 4 / RPW;
   constexpr int NB = P / 2;
   const int lane = threadIdx.x & 63;
   const int s = (lane >> 4) % S, l = lane & 15;
-  const uint64_t kb = (base >> 1) + (uint64_t)(16 * s + l) * NB;
-  Draw<P> r;
+  uint64_t p0 = (uint64_t)PHILOX_M0 * ((uint32_t)(base >> 1) + (uint32_t)(16 * s + l) * NB);
+  Draw<P, FT> r;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    const Block4 b = philox((uint32_t)(kb + j), d.dp, d.rep, TAG_MM1, k0, k1);
-    r.A[2 * j] = d.qa * log2_u01(b.x);
+    const Block4 b = philox_from(p0, d.dp, d.rep, TAG_MM1, k0, k1);
+    p0 += PHILOX_M0;
+    const float l0 = log2_u01(b.x), l1 = log2_u01(b.z);
     r.S[2 * j] = log2_u01(b.y);
-    r.A[2 * j + 1] = d.qa * log2_u01(b.z);
     r.S[2 * j + 1] = log2_u01(b.w);
+    r.b[2 * j] = __builtin_fmaf(-d.qa, l0, r.S[2 * j]);
+    r.b[2 * j + 1] = __builtin_fmaf(-d.qa, l1, r.S[2 * j + 1]);
+    if constexpr (FT) {
+      r.L[2 * j] = l0;
+      r.L[2 * j + 1] = l1;
+    }
   }
   return r;
 }
@@ -124,89 +153,96 @@ __device__ __forceinline__ Draw<P> draw_chunk(uint64_t base, const Rep &d, uint3
 // Draw sources for wave_group: chunk c is requested in order c = 0, 1, ...
 struct PhiloxSource {
   uint32_t k0, k1;
-  template <int RPW, int P>
-  __device__ __forceinline__ Draw<P> next(uint64_t base, const Rep &d) {
-    return draw_chunk<RPW, P>(base, d, k0, k1);
+  template <int RPW, int P, bool FT>
+  __device__ __forceinline__ Draw<P, FT> next(uint64_t base, const Rep &d) {
+    return draw_chunk<RPW, P, FT>(base, d, k0, k1);
   }
 };
 
-// The scanned maps of one chunk: this lane's exclusive prefix (ea, eb), the
-// map of its first P / 2 customers (ha, hb) and the four segment totals.
+// The scanned maps of one chunk: the composite map (a, b) of the 16-lane
+// segment's customers up to and including this lane's, and the map of this
+// lane's first P / 2 customers (ha, hb).
 struct ChunkScan {
-  float ea, eb, ha, hb;
-  float ta[4], tb[4];
+  float a, b, ha, hb;
 };
+
+// min(a, b) for operands the compiler cannot tell from signalling NaNs
+// (it would quiet each with an instruction of its own).
+__device__ __forceinline__ float later_raw(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// One step of the inclusive scan of the maps over the 16-lane segment: lane
+// l takes (a, b) of lane l - N before its own. Lanes below N have no source:
+// their DPP writes are off, which leaves b as it is and in t an earlier
+// candidate that a already holds (before all times at the first step). The
+// leading wait covers the DPP reads of registers the vector ALU has just
+// written.
+template <int N>
+__device__ __forceinline__ void scan_step(float &a, float &b, float &t) {
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %2, %0, %1 row_shr:%3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_shr:%3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_min_f32 %0, %0, %2"
+      : "+&v"(a), "+&v"(b), "+&v"(t)
+      : "n"(N));
+}
 
 // Compose this lane's P customers (its two halves side by side, in order
 // within each, then the second half after the first), then scan the
 // 16-lane segment.
-template <int P>
-__device__ __forceinline__ ChunkScan compose_scan(const Draw<P> &dr) {
+template <int P, bool FT>
+__device__ __forceinline__ ChunkScan compose_scan(const Draw<P, FT> &dr) {
   constexpr int H = P / 2;
-  float a0 = dr.S[0], b0 = dr.S[0] - dr.A[0];
-  float a1 = dr.S[H], b1 = dr.S[H] - dr.A[H];
+  float a0 = dr.S[0], b0 = dr.b[0];
+  float a1 = dr.S[H], b1 = dr.b[H];
 #pragma unroll
   for (int j = 1; j < H; ++j) {
-    const float c0 = dr.S[j] - dr.A[j];
-    a0 = later(dr.S[j], a0 + c0);
-    b0 = b0 + c0;
-    const float c1 = dr.S[H + j] - dr.A[H + j];
-    a1 = later(dr.S[H + j], a1 + c1);
-    b1 = b1 + c1;
+    a0 = later(dr.S[j], a0 + dr.b[j]);
+    b0 = b0 + dr.b[j];
+    a1 = later(dr.S[H + j], a1 + dr.b[H + j]);
+    b1 = b1 + dr.b[H + j];
   }
-  float a = later(a1, a0 + b1);
-  float bb = b0 + b1;
-#define MRIP_SCAN_STEP(N)                              \
-  {                                                    \
-    const float as = row_shr<N>(a, kBeforeAll);        \
-    const float bs = row_shr<N>(bb, 0.0f);             \
-    a = later(a, as + bb);                             \
-    bb = bs + bb;                                      \
-  }
-  MRIP_SCAN_STEP(1)
-  MRIP_SCAN_STEP(2)
-  MRIP_SCAN_STEP(4)
-  MRIP_SCAN_STEP(8)
-#undef MRIP_SCAN_STEP
   ChunkScan r;
   r.ha = a0;
   r.hb = b0;
-  r.ea = row_shr<1>(a, kBeforeAll);
-  r.eb = row_shr<1>(bb, 0.0f);
-  r.ta[0] = readlane_f(a, 15);
-  r.ta[1] = readlane_f(a, 31);
-  r.ta[2] = readlane_f(a, 47);
-  r.ta[3] = readlane_f(a, 63);
-  r.tb[0] = readlane_f(bb, 15);
-  r.tb[1] = readlane_f(bb, 31);
-  r.tb[2] = readlane_f(bb, 47);
-  r.tb[3] = readlane_f(bb, 63);
+  r.a = later(a1, a0 + b1);
+  r.b = b0 + b1;
+  float t = kBeforeAll;
+  scan_step<1>(r.a, r.b, t);
+  scan_step<2>(r.a, r.b, t);
+  scan_step<4>(r.a, r.b, t);
+  scan_step<8>(r.a, r.b, t);
   return r;
 }
 
 // Pass the carry through the replication's segments in order: returns the
-// carry after the chunk and sets `tin`, the carry into this lane's segment.
+// carry after the chunk and sets `T0`, the system time before this lane's
+// first customer. Every lane applies its inclusive map to the time its
+// segment starts from (u, the time after its customers); the last lane of a
+// segment so has the next one's start, which DPP row_bcast:15 hands on one
+// segment at a time, and a lane's T0 is u of the lane before it.
 template <int RPW>
-__device__ __forceinline__ float carry_through(const ChunkScan &cs, float carry, float &tin) {
-  constexpr int S = 4 / RPW;
-  const int row = (threadIdx.x & 63) >> 4;
-  const int q = row / S, s = row % S;
-  float cur = carry;
-  tin = carry;
-#pragma unroll
-  for (int j = 0; j < S; ++j) {
-    float ta, tb;
-    if (RPW == 1) {
-      ta = cs.ta[j];
-      tb = cs.tb[j];
-    } else {
-      ta = pick4(q * S + j, cs.ta[0], cs.ta[1], cs.ta[2], cs.ta[3]);
-      tb = pick4(q * S + j, cs.tb[0], cs.tb[1], cs.tb[2], cs.tb[3]);
-    }
-    tin = (j == s) ? cur : tin;
-    cur = later(ta, cur + tb);
+__device__ __forceinline__ float carry_through(const ChunkScan &cs, float carry, float &T0) {
+  float tin = carry;
+  float u = later_raw(cs.a, tin + cs.b);
+#define MRIP_NEXT_SEGMENT(ROWS)                                                               \
+  tin = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(tin), __float_as_int(u),    \
+                                                   0x142, ROWS, 0xF, false));                 \
+  u = later_raw(cs.a, tin + cs.b);
+  if (RPW == 1) {
+    MRIP_NEXT_SEGMENT(0x2)
+    MRIP_NEXT_SEGMENT(0x4)
+    MRIP_NEXT_SEGMENT(0x8)
+  } else if (RPW == 2) {
+    MRIP_NEXT_SEGMENT(0xA)
   }
-  return cur;
+#undef MRIP_NEXT_SEGMENT
+  T0 = row_shr<1>(u, tin);
+  if (RPW == 1) return readlane_f(u, 63);
+  return __shfl(u, (int)(threadIdx.x & 63) | (64 / RPW - 1), 64);
 }
 
 // The lane's P customers in order, from the system time T before the first
@@ -221,10 +257,9 @@ __device__ __forceinline__ float carry_through(const ChunkScan &cs, float carry,
 // system time the lane holds when it reaches customer n, so every control
 // term has mean zero given the past.
 template <int P, bool FEAT, bool TAIL, bool FT>
-__device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const Draw<P> &dr,
-                                           uint64_t n0, uint64_t n, uint64_t K, float unit,
-                                           float ea, float es, float &st, float &ss, float &si,
-                                           Feat &ft, float (&cl)[4]) {
+__device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const Draw<P, FT> &dr,
+                                           uint64_t n0, const Rep &d, uint64_t K, float &st,
+                                           float &ss, float &si, Feat &ft, float (&cl)[4]) {
   constexpr int H = P / 2;
   // the two halves side by side, the second from later(ha, T0 + hb), the
   // system time the first half's map gives; each half sums on its own
@@ -232,11 +267,13 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
   const float Ts[2] = {Th[0], Th[1]};  // the halves' starts
   float sth[2] = {0.0f, 0.0f}, ssh[2] = {0.0f, 0.0f}, sih[2] = {0.0f, 0.0f};
   if (FT) cl[0] = cl[1] = cl[2] = cl[3] = 0.0f;
+  const uint64_t n = d.n;
   // FT chunks with every customer counted (no feature prefix, no tail):
-  // the controls from raw sums, sum A, sum T_{n-1} S and sum T_{n-1} A,
-  // centred once per chunk (three operations per customer instead of six)
+  // the controls from raw sums, sum L, sum T_{n-1} S and sum T_{n-1} L (A =
+  // qa L), centred once per chunk (three operations per customer instead of
+  // six)
   constexpr bool RAW = FT && !FEAT && !TAIL;
-  float qa = 0.0f, qts = 0.0f, qta = 0.0f;
+  float ql = 0.0f, qts = 0.0f, qtl = 0.0f;
 #pragma unroll
   for (int j = 0; j < P; ++j) {
     const int h = j >= H;
@@ -246,7 +283,8 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
       if (FEAT) v = n0 + j >= K;
       if (TAIL) v = v && n0 + j < n;
       // the centred variates in time (T-weighted sums stay in the unit)
-      const float da = __builtin_fmaf(unit, dr.A[j], -ea), ds = __builtin_fmaf(unit, dr.S[j], -es);
+      const float da = __builtin_fmaf(d.ca, dr.L[j], -d.ea);
+      const float ds = __builtin_fmaf(d.cs, dr.S[j], -d.es);
       if (FEAT) {  // customers < K <= n: the prefix four
         const bool p = n0 + j < K;
         ft.pc[0] += p ? ds : 0.0f;
@@ -260,25 +298,26 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
         cl[2] = v ? __builtin_fmaf(T, ds, cl[2]) : cl[2];
         cl[3] = v ? __builtin_fmaf(T, da, cl[3]) : cl[3];
       } else {
-        qa += dr.A[j];
+        ql += dr.L[j];
         qts = __builtin_fmaf(T, dr.S[j], qts);
-        qta = __builtin_fmaf(T, dr.A[j], qta);
+        qtl = __builtin_fmaf(T, dr.L[j], qtl);
       }
     }
     if (FEAT) {  // the prefix features, from their definitions
       const bool f = n0 + j < K;
       // I = max(0, A - T) = W - (T - A) exactly: A - T = -(T - A) in IEEE
       // arithmetic, and W is either 0 or T - A
-      const float dlt = T - dr.A[j];
+      const float A = d.qa * dr.L[j];
+      const float dlt = T - A;
       const float W = later(0.0f, dlt);
-      ft.sa += f ? dr.A[j] : 0.0f;
+      ft.sa += f ? A : 0.0f;
       ft.ss += f ? dr.S[j] : 0.0f;
       ft.sw += f ? W : 0.0f;
       ft.si += f ? W - dlt : 0.0f;
       ft.zeros += (f && W == 0.0f);
       ft.wmax = later(ft.wmax, f ? W : 0.0f);
     }
-    const float x = T + (dr.S[j] - dr.A[j]);
+    const float x = T + dr.b[j];
     T = later(x, dr.S[j]);
     const float I = T - x;
     if (TAIL) {
@@ -304,10 +343,10 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
     // sum of T_{n-1} over the lane: each half's start, plus its T's but
     // the last
     const float tp = (Ts[0] + (sth[0] - Th[0])) + (Ts[1] + (sth[1] - Th[1]));
-    cl[0] = __builtin_fmaf(unit, ss, -(float)P * es);
-    cl[1] = __builtin_fmaf(unit, qa, -(float)P * ea);
-    cl[2] = __builtin_fmaf(unit, qts, -es * tp);
-    cl[3] = __builtin_fmaf(unit, qta, -ea * tp);
+    cl[0] = __builtin_fmaf(d.cs, ss, -(float)P * d.es);
+    cl[1] = __builtin_fmaf(d.ca, ql, -(float)P * d.ea);
+    cl[2] = __builtin_fmaf(d.cs, qts, -d.es * tp);
+    cl[3] = __builtin_fmaf(d.ca, qtl, -d.ea * tp);
   }
 }
 
@@ -324,14 +363,14 @@ __device__ __forceinline__ uint64_t lane_first_customer(uint64_t base) {
 // customers >= n (only chunks that reach past some replication's end need
 // it); FT adds the controls.
 template <int RPW, int P, bool FEAT, bool TAIL, bool FT>
-__device__ __forceinline__ void wave_chunk(uint64_t base, const Draw<P> &dr, const Rep &d,
+__device__ __forceinline__ void wave_chunk(uint64_t base, const Draw<P, FT> &dr, const Rep &d,
                                            uint64_t K, float &carry, Sums &acc, Feat &ft) {
-  const ChunkScan cs = compose_scan<P>(dr);
-  float tin;
-  carry = carry_through<RPW>(cs, carry, tin);
+  const ChunkScan cs = compose_scan<P, FT>(dr);
+  float T0;
+  carry = carry_through<RPW>(cs, carry, T0);
   float st, ss, si, cl[4];
-  apply_lane<P, FEAT, TAIL, FT>(later(cs.ea, tin + cs.eb), cs, dr, lane_first_customer<RPW, P>(base),
-                                d.n, K, d.cs, d.ea, d.es, st, ss, si, ft, cl);
+  apply_lane<P, FEAT, TAIL, FT>(T0, cs, dr, lane_first_customer<RPW, P>(base), d, K, st, ss, si, ft,
+                                cl);
   acc.t.add(st);
   acc.s.add(ss);
   acc.i.add(si);
@@ -342,29 +381,32 @@ __device__ __forceinline__ void wave_chunk(uint64_t base, const Draw<P> &dr, con
 }
 
 // Fix-up chunk of a split replication: the same customers from two carries
-// (the true one and the speculative one the part started from); adds the
-// difference of their sums (S and the two unweighted controls do not depend
-// on the carry). Fix-up chunks lie after the feature prefix, so with FT
-// every customer counts for the controls.
+// (the true one and the speculative one the part started from); exchanges
+// the speculative sums for the true ones (S and the two unweighted controls
+// do not depend on the carry). Fix-up chunks lie after the feature prefix,
+// so with FT every customer counts for the controls.
 template <int P, bool TAIL, bool FT>
-__device__ __forceinline__ void fixup_chunk(uint64_t base, const Draw<P> &dr, const Rep &d,
+__device__ __forceinline__ void fixup_chunk(uint64_t base, const Draw<P, FT> &dr, const Rep &d,
                                             float &c_true, float &c_spec, Sums &acc) {
-  const ChunkScan cs = compose_scan<P>(dr);
-  float tin_t, tin_s;
-  c_true = carry_through<1>(cs, c_true, tin_t);
-  c_spec = carry_through<1>(cs, c_spec, tin_s);
+  const ChunkScan cs = compose_scan<P, FT>(dr);
+  float T_t, T_s;
+  c_true = carry_through<1>(cs, c_true, T_t);
+  c_spec = carry_through<1>(cs, c_spec, T_s);
   const uint64_t n0 = lane_first_customer<1, P>(base);
   Feat none;
   float tt, st_, it, ts, ss_, is, clt[4], cls[4];
-  apply_lane<P, false, TAIL, FT>(later(cs.ea, tin_t + cs.eb), cs, dr, n0, d.n, 0, d.cs, d.ea, d.es, tt, st_,
-                                 it, none, clt);
-  apply_lane<P, false, TAIL, FT>(later(cs.ea, tin_s + cs.eb), cs, dr, n0, d.n, 0, d.cs, d.ea, d.es, ts, ss_,
-                                 is, none, cls);
-  acc.t.add(tt - ts);
-  acc.i.add(it - is);
+  apply_lane<P, false, TAIL, FT>(T_t, cs, dr, n0, d, 0, tt, st_, it, none, clt);
+  apply_lane<P, false, TAIL, FT>(T_s, cs, dr, n0, d, 0, ts, ss_, is, none, cls);
+  acc.t.add(tt);
+  acc.t.sub(ts);
+  acc.i.add(it);
+  acc.i.sub(is);
   if (FT) {
-    acc.c[2].add(clt[2] - cls[2]);
-    acc.c[3].add(clt[3] - cls[3]);
+#pragma unroll
+    for (int k = 2; k < 4; ++k) {
+      acc.c[k].add(clt[k]);
+      acc.c[k].sub(cls[k]);
+    }
   }
 }
 
@@ -399,7 +441,7 @@ __device__ void wave_group(const Rep &d, Src &src, uint64_t K, const Mm1Args &a)
   uint32_t c = 0;
 #define MRIP_CHUNK(F, TL)                                                            \
   {                                                                                  \
-    const Draw<P> cur = src.template next<RPW, P>((uint64_t)c * CHUNK, d);          \
+    const Draw<P, FT> cur = src.template next<RPW, P, FT>((uint64_t)c * CHUNK, d);  \
     wave_chunk<RPW, P, F, TL, FT>(c * CHUNK, cur, d, K, carry, acc, ft);             \
   }
   if (FT)
@@ -408,9 +450,9 @@ __device__ void wave_group(const Rep &d, Src &src, uint64_t K, const Mm1Args &a)
   for (; c < chunks; ++c) MRIP_CHUNK(false, true)
 #undef MRIP_CHUNK
 
-  const float sw = group_sum_compensated(wait_sum(acc), WIDTH);
-  const float st = group_sum_compensated(acc.t.value(), WIDTH);
-  const float si = group_sum_compensated(acc.i.value(), WIDTH);
+  const double st = group_sum_f64(acc.t.value(), WIDTH);
+  const double sw = st - group_sum_f64(acc.s.value(), WIDTH);
+  const double si = group_sum_f64(acc.i.value(), WIDTH);
   float f[10], cl[8];
   if (FT) {
     const float kf = (float)K;
@@ -426,7 +468,7 @@ __device__ void wave_group(const Rep &d, Src &src, uint64_t K, const Mm1Args &a)
     f[9] = group_sum_compensated(ft.tlast, WIDTH) * d.cs;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      cl[k] = group_sum_compensated(acc.c[k].value(), WIDTH);
+      cl[k] = (float)group_sum_f64(acc.c[k].value(), WIDTH);
       cl[4 + k] = group_sum_compensated(ft.pc[k], WIDTH);
     }
     // the T-weighted controls, from the unit
@@ -436,10 +478,10 @@ __device__ void wave_group(const Rep &d, Src &src, uint64_t K, const Mm1Args &a)
     cl[7] *= d.cs;
   }
   if ((lane % WIDTH) == 0 && d.n > 0) {
-    const float nf = (float)d.n;
-    a.mean_w[d.out] = sw * d.cs / nf;
-    a.mean_t[d.out] = st * d.cs / nf;
-    a.mean_i[d.out] = si * d.cs / nf;
+    const double per = (double)d.cs / (double)d.n;
+    a.mean_w[d.out] = (float)(sw * per);
+    a.mean_t[d.out] = (float)(st * per);
+    a.mean_i[d.out] = (float)(si * per);
     if (FT) {
 #pragma unroll
       for (int j = 0; j < 10; ++j) a.features[d.out * 10 + j] = f[j];
@@ -517,7 +559,7 @@ __global__ __launch_bounds__(ft_max_wg<FT>()) void mm1_wave_kernel(Mm1Args a, fl
   const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int q = (lane >> 4) / S;
   const uint64_t r = wave * RPW + q;
-  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint32_t k0 = in_vgpr((uint32_t)a.seed), k1 = in_vgpr((uint32_t)(a.seed >> 32));
   if (wave * RPW >= a.n_reps) return;  // whole wave idle (wave-uniform)
   const Rep d = uniform_rep(a, r, ca, cs);
   PhiloxSource src{k0, k1};
@@ -769,7 +811,7 @@ __global__ __launch_bounds__(ft_max_wg<FT>()) void mm1_plan_kernel(Mm1Args a, ui
   constexpr int S = 4 / RPW;
   const int lane = threadIdx.x & 63;
   const int q = (lane >> 4) / S;
-  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint32_t k0 = in_vgpr((uint32_t)a.seed), k1 = in_vgpr((uint32_t)(a.seed >> 32));
   const uint64_t n_units = (n_items + RPW - 1) / RPW;
   for (;;) {
     uint32_t unit = 0;
@@ -814,9 +856,8 @@ template <int X, bool STASH>
 struct SplitShared {
   static constexpr int NF = STASH ? X - 1 : 1;
   float spec[split_slots<X>()][X], fin[split_slots<X>()][X];
-  float sum[split_slots<X>()][X][7];  // W, T, I, then the four controls
+  double sum[split_slots<X>()][X][7];  // S, T, I, then the four controls
   float first[split_slots<X>()][NF][STASH ? 2 * MM1_P + 4 : 1][64];
-  float first_t[split_slots<X>()][NF][8];
 };
 
 // Part h of replication d (slot `slot` of the workgroup); every thread of
@@ -868,35 +909,28 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
   const bool deferred_first = split && h >= 1;
   float spec0 = 0.0f;  // the speculative carry after the first chunk
   if (deferred_first) {
-    const Draw<P> dr = draw_chunk<1, P>((uint64_t)c * CHUNK, d, k0, k1);
-    const ChunkScan cs = compose_scan<P>(dr);
-    float tin;
-    carry = carry_through<1>(cs, carry, tin);
+    const Draw<P, FT> dr = draw_chunk<1, P, FT>((uint64_t)c * CHUNK, d, k0, k1);
+    const ChunkScan cs = compose_scan<P, FT>(dr);
+    float T0;
+    carry = carry_through<1>(cs, carry, T0);
     spec0 = carry;
     if constexpr (STASH) {
       float(*st)[64] = sh.first[slot][h - 1];
 #pragma unroll
       for (int j = 0; j < P; ++j) {
-        st[j][lane] = dr.A[j];
+        st[j][lane] = dr.b[j];
         st[P + j][lane] = dr.S[j];
       }
-      st[2 * P][lane] = cs.ea;
-      st[2 * P + 1][lane] = cs.eb;
+      st[2 * P][lane] = cs.a;
+      st[2 * P + 1][lane] = cs.b;
       st[2 * P + 2][lane] = cs.ha;
       st[2 * P + 3][lane] = cs.hb;
-      if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          sh.first_t[slot][h - 1][j] = cs.ta[j];
-          sh.first_t[slot][h - 1][4 + j] = cs.tb[j];
-        }
-      }
     }
     ++c;
   }
 #define MRIP_CHUNK(F, TL)                                                          \
   {                                                                                \
-    const Draw<P> dr = draw_chunk<1, P>((uint64_t)c * CHUNK, d, k0, k1);          \
+    const Draw<P, FT> dr = draw_chunk<1, P, FT>((uint64_t)c * CHUNK, d, k0, k1);  \
     wave_chunk<1, P, F, TL, FT>((uint64_t)c * CHUNK, dr, d, K, carry, acc, ft);    \
   }
   if (FT)
@@ -913,36 +947,30 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
   Sums fix;
   auto correct = [&](float cin) -> float {
     fix = Sums();
-    Draw<P> dr;
+    Draw<P, FT> dr;
     ChunkScan scan;
     if constexpr (STASH) {
       const float(*st)[64] = sh.first[slot][h - 1];
 #pragma unroll
       for (int j = 0; j < P; ++j) {
-        dr.A[j] = st[j][lane];
+        dr.b[j] = st[j][lane];
         dr.S[j] = st[P + j][lane];
       }
-      scan.ea = st[2 * P][lane];
-      scan.eb = st[2 * P + 1][lane];
+      scan.a = st[2 * P][lane];
+      scan.b = st[2 * P + 1][lane];
       scan.ha = st[2 * P + 2][lane];
       scan.hb = st[2 * P + 3][lane];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        scan.ta[j] = sh.first_t[slot][h - 1][j];
-        scan.tb[j] = sh.first_t[slot][h - 1][4 + j];
-      }
     } else {  // the same chunk drawn and scanned again: the same bits
-      dr = draw_chunk<1, P>((uint64_t)cb * CHUNK, d, k0, k1);
-      scan = compose_scan<P>(dr);
+      dr = draw_chunk<1, P, FT>((uint64_t)cb * CHUNK, d, k0, k1);
+      scan = compose_scan<P, FT>(dr);
     }
-    float tin;
-    float ct = carry_through<1>(scan, cin, tin);
+    float T0;
+    float ct = carry_through<1>(scan, cin, T0);
     {
       Feat none;
       float stt, ss, si, cl[4];
-      apply_lane<P, false, false, FT>(later(scan.ea, tin + scan.eb), scan, dr,
-                                      lane_first_customer<1, P>((uint64_t)cb * CHUNK), d.n, 0,
-                                      d.cs, d.ea, d.es, stt, ss, si, none, cl);
+      apply_lane<P, false, false, FT>(T0, scan, dr, lane_first_customer<1, P>((uint64_t)cb * CHUNK),
+                                      d, 0, stt, ss, si, none, cl);
       fix.t.add(stt);
       fix.s.add(ss);
       fix.i.add(si);
@@ -955,7 +983,7 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
     bool coupled =
         __builtin_amdgcn_readfirstlane((int)(__float_as_uint(ct) == __float_as_uint(cs))) != 0;
     for (uint32_t cc = cb + 1; cc < ce && !coupled; ++cc) {
-      const Draw<P> dr = draw_chunk<1, P>((uint64_t)cc * CHUNK, d, k0, k1);
+      const Draw<P, FT> dr = draw_chunk<1, P, FT>((uint64_t)cc * CHUNK, d, k0, k1);
       if (cc < full) fixup_chunk<P, false, FT>((uint64_t)cc * CHUNK, dr, d, ct, cs, fix);
       else fixup_chunk<P, true, FT>((uint64_t)cc * CHUNK, dr, d, ct, cs, fix);
       coupled = __builtin_amdgcn_readfirstlane((int)(__float_as_uint(ct) == __float_as_uint(cs))) != 0;
@@ -990,23 +1018,16 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
       __syncthreads();
     }
   }
-  acc.t.add(fix.t.value());
-  acc.s.add(fix.s.value());
-  acc.i.add(fix.i.value());
-  if (FT) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.c[k].add(fix.c[k].value());
-  }
-
-  // phase 3: part sums, then the replication's means in part order
+  // part sums, then the replication's means in part order
   constexpr int NS = FT ? 7 : 3;
-  float part[NS];
-  part[0] = group_sum_compensated(wait_sum(acc), 64);
-  part[1] = group_sum_compensated(acc.t.value(), 64);
-  part[2] = group_sum_compensated(acc.i.value(), 64);
+  double part[NS];
+  part[0] = group_sum_f64(acc.s.value() + fix.s.value(), 64);
+  part[1] = group_sum_f64(acc.t.value() + fix.t.value(), 64);
+  part[2] = group_sum_f64(acc.i.value() + fix.i.value(), 64);
   if (FT) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) part[3 + k] = group_sum_compensated(acc.c[k].value(), 64);
+    for (int k = 0; k < 4; ++k)
+      part[3 + k] = group_sum_f64(acc.c[k].value() + fix.c[k].value(), 64);
   }
   float f[10], pcs[4];
   if (FT && h == 0 && K > 0) {
@@ -1030,29 +1051,24 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
   }
   __syncthreads();
   if (h == 0 && lane == 0 && d.n > 0) {
-    float tot[NS];
+    double tot[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      float hi = sh.sum[slot][0][k], lo = 0.0f;
+      tot[k] = sh.sum[slot][0][k];
 #pragma unroll
-      for (int j = 1; j < X; ++j) {
-        float s2, e;
-        two_sum(hi, sh.sum[slot][j][k], s2, e);
-        hi = s2;
-        lo += e;
-      }
-      tot[k] = hi + lo;
+      for (int j = 1; j < X; ++j) tot[k] += sh.sum[slot][j][k];
     }
-    const float nf = (float)d.n;
-    a.mean_w[d.out] = tot[0] * d.cs / nf;
-    a.mean_t[d.out] = tot[1] * d.cs / nf;
-    a.mean_i[d.out] = tot[2] * d.cs / nf;
+    const double per = (double)d.cs / (double)d.n;
+    a.mean_w[d.out] = (float)((tot[1] - tot[0]) * per);
+    a.mean_t[d.out] = (float)(tot[1] * per);
+    a.mean_i[d.out] = (float)(tot[2] * per);
     if (FT && K > 0) {
 #pragma unroll
       for (int j = 0; j < 10; ++j) a.features[d.out * 10 + j] = f[j];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {  // the T-weighted two from the unit
-        a.controls[d.out * 8 + k] = k >= 2 ? tot[3 + k] * d.cs : tot[3 + k];
+        const float c = (float)tot[3 + k];
+        a.controls[d.out * 8 + k] = k >= 2 ? c * d.cs : c;
         a.controls[d.out * 8 + 4 + k] = k >= 2 ? pcs[k] * d.cs : pcs[k];
       }
     }
@@ -1085,8 +1101,8 @@ __global__ __launch_bounds__(split_wg<X>(), FT ? 1 : 4) void mm1_split_kernel(Mm
   const int wave = threadIdx.x >> 6;
   const int slot = wave / X, h = wave % X;
   const uint64_t r = (uint64_t)blockIdx.x * SLOTS + slot;
-  split_replication<X, FT>(uniform_rep(a, r, ca, cs), slot, h, (uint32_t)a.seed,
-                           (uint32_t)(a.seed >> 32), a.feature_prefix, a, sh);
+  split_replication<X, FT>(uniform_rep(a, r, ca, cs), slot, h, in_vgpr((uint32_t)a.seed),
+                           in_vgpr((uint32_t)(a.seed >> 32)), a.feature_prefix, a, sh);
 }
 
 // Persistent plan kernel with the long items split: the first n_long items
@@ -1107,7 +1123,7 @@ __global__ __launch_bounds__(split_wg<X>()) void mm1_plan_split_kernel(Mm1Args a
   __shared__ uint32_t sh_pop;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int slot = wave / X, h = wave % X;
-  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint32_t k0 = in_vgpr((uint32_t)a.seed), k1 = in_vgpr((uint32_t)(a.seed >> 32));
   __builtin_amdgcn_s_setprio(2);
   for (;;) {
     if (threadIdx.x == 0) sh_pop = atomicAdd(&a.queue_head[0], (uint32_t)SLOTS);

@@ -197,3 +197,26 @@ def test_split_statistics_across_runs(gpu, split):
             assert st["n"] == R
             assert abs(st["mean"] - x.mean()) <= 1e-12 * abs(x.mean())
             assert abs(st["var"] - x.var(ddof=1)) <= 1e-9 * x.var(ddof=1)
+
+
+@pytest.mark.parametrize("N,lam,K", [(5, 0.9, 0), (1024, 0.9, 0), (4321, 0.95, 0), (30001, 0.9, 0),
+                                     (100000, 0.7, 0), (30001, 1.1, 0), (30001, 0.9, 700)])
+def test_mm1_same_bits_in_every_wave_form(gpu, N, lam, K):
+    # every form adds the same fp32 partial sums in fp64, so a replication's
+    # means do not depend on how many lanes or wavefronts run it (nor, with a
+    # prefix, the controls on how many wavefronts)
+    announce("mm1 same bits", N, lam, K)
+    R = 200
+    ref = None
+    for rpw, split in ((1, 1), (2, 1), (4, 1), (1, 2), (1, 4), (1, 8)):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(lam, 1.0, N, K), WAVE)
+        ctx.set_shape(rpw, 256)
+        if split > 1:
+            ctx.set_split(split)
+        ctx.run(R, seed=3)
+        outs = [ctx.output(o).cpu().numpy() for o in range(3)]
+        if K and rpw == 1:
+            outs.append(ctx.output(4).cpu().numpy())
+        ref = outs if ref is None else ref
+        for a, b in zip(outs, ref):
+            assert np.array_equal(a, b), (rpw, split)
