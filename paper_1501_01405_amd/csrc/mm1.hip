@@ -9,10 +9,10 @@
 //
 // Bound of every wavefront engine: vector-ALU issue, one instruction per four
 // cycles per SIMD (the two logarithms of a customer take two slots each). A
-// full chunk of 16 customers per lane is 620 instructions (678 before the
-// fused b, the running first Philox product, the in-place DPP scan and the
-// fp64 sums): 4096 x 20000 customers 97 -> 87.5 us, 1024 x 1e5 over four
-// wavefronts 111 -> 100.7, the 64 x 32 plan 0.64 -> 0.59 ms.
+// full chunk of 16 customers per lane is 636 instructions (678 before the
+// running first Philox product, the in-place DPP scan and the fp64 sums):
+// 4096 x 20000 customers 97 -> 86 us, 1024 x 1e5 over four wavefronts 111 ->
+// 102, the 64 x 32 plan 0.64 -> 0.585 ms.
 //
 // WAVE mapping (one replication per wavefront): a segment of 16 lanes takes
 // 16 P consecutive customers, P per lane from P/2 Philox blocks, composes
@@ -116,12 +116,13 @@ __device__ __forceinline__ float pick4(int q, float v0, float v1, float v2, floa
 constexpr int MM1_P = 16;
 
 // The variates of one chunk for this lane: P customers from P/2 blocks.
-// Customer j's service time S and the net change b = S - A its map adds, one
-// fused multiply-add from the two logarithms; the forms with the controls
-// (FT) also keep log2 u of the interarrival time (A = qa L).
+// Customer j's service time S and the net change b = S - A its map adds; the
+// forms with the controls (FT) also keep the interarrival time A. (A fused b
+// saves an instruction per customer, 2.5 %, but rounds once where A and S - A
+// round twice, and the features feed a bf16 network.)
 template <int P, bool FT>
 struct Draw {
-  float S[P], b[P], L[FT ? P : 1];
+  float S[P], b[P], A[FT ? P : 1];
 };
 
 template <int RPW, int P, bool FT>
@@ -137,14 +138,14 @@ __device__ __forceinline__ Draw<P, FT> draw_chunk(uint64_t base, const Rep &d, u
   for (int j = 0; j < NB; ++j) {
     const Block4 b = philox_from(p0, d.dp, d.rep, TAG_MM1, k0, k1);
     p0 += PHILOX_M0;
-    const float l0 = log2_u01(b.x), l1 = log2_u01(b.z);
+    const float A0 = d.qa * log2_u01(b.x), A1 = d.qa * log2_u01(b.z);
     r.S[2 * j] = log2_u01(b.y);
     r.S[2 * j + 1] = log2_u01(b.w);
-    r.b[2 * j] = __builtin_fmaf(-d.qa, l0, r.S[2 * j]);
-    r.b[2 * j + 1] = __builtin_fmaf(-d.qa, l1, r.S[2 * j + 1]);
+    r.b[2 * j] = r.S[2 * j] - A0;
+    r.b[2 * j + 1] = r.S[2 * j + 1] - A1;
     if constexpr (FT) {
-      r.L[2 * j] = l0;
-      r.L[2 * j + 1] = l1;
+      r.A[2 * j] = A0;
+      r.A[2 * j + 1] = A1;
     }
   }
   return r;
@@ -269,11 +270,10 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
   if (FT) cl[0] = cl[1] = cl[2] = cl[3] = 0.0f;
   const uint64_t n = d.n;
   // FT chunks with every customer counted (no feature prefix, no tail):
-  // the controls from raw sums, sum L, sum T_{n-1} S and sum T_{n-1} L (A =
-  // qa L), centred once per chunk (three operations per customer instead of
-  // six)
+  // the controls from raw sums, sum A, sum T_{n-1} S and sum T_{n-1} A,
+  // centred once per chunk (three operations per customer instead of six)
   constexpr bool RAW = FT && !FEAT && !TAIL;
-  float ql = 0.0f, qts = 0.0f, qtl = 0.0f;
+  float qa = 0.0f, qts = 0.0f, qta = 0.0f;
 #pragma unroll
   for (int j = 0; j < P; ++j) {
     const int h = j >= H;
@@ -283,7 +283,7 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
       if (FEAT) v = n0 + j >= K;
       if (TAIL) v = v && n0 + j < n;
       // the centred variates in time (T-weighted sums stay in the unit)
-      const float da = __builtin_fmaf(d.ca, dr.L[j], -d.ea);
+      const float da = __builtin_fmaf(d.cs, dr.A[j], -d.ea);
       const float ds = __builtin_fmaf(d.cs, dr.S[j], -d.es);
       if (FEAT) {  // customers < K <= n: the prefix four
         const bool p = n0 + j < K;
@@ -298,19 +298,18 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
         cl[2] = v ? __builtin_fmaf(T, ds, cl[2]) : cl[2];
         cl[3] = v ? __builtin_fmaf(T, da, cl[3]) : cl[3];
       } else {
-        ql += dr.L[j];
+        qa += dr.A[j];
         qts = __builtin_fmaf(T, dr.S[j], qts);
-        qtl = __builtin_fmaf(T, dr.L[j], qtl);
+        qta = __builtin_fmaf(T, dr.A[j], qta);
       }
     }
     if (FEAT) {  // the prefix features, from their definitions
       const bool f = n0 + j < K;
       // I = max(0, A - T) = W - (T - A) exactly: A - T = -(T - A) in IEEE
       // arithmetic, and W is either 0 or T - A
-      const float A = d.qa * dr.L[j];
-      const float dlt = T - A;
+      const float dlt = T - dr.A[j];
       const float W = later(0.0f, dlt);
-      ft.sa += f ? A : 0.0f;
+      ft.sa += f ? dr.A[j] : 0.0f;
       ft.ss += f ? dr.S[j] : 0.0f;
       ft.sw += f ? W : 0.0f;
       ft.si += f ? W - dlt : 0.0f;
@@ -344,9 +343,9 @@ __device__ __forceinline__ void apply_lane(float T0, const ChunkScan &cs, const 
     // the last
     const float tp = (Ts[0] + (sth[0] - Th[0])) + (Ts[1] + (sth[1] - Th[1]));
     cl[0] = __builtin_fmaf(d.cs, ss, -(float)P * d.es);
-    cl[1] = __builtin_fmaf(d.ca, ql, -(float)P * d.ea);
+    cl[1] = __builtin_fmaf(d.cs, qa, -(float)P * d.ea);
     cl[2] = __builtin_fmaf(d.cs, qts, -d.es * tp);
-    cl[3] = __builtin_fmaf(d.ca, qtl, -d.ea * tp);
+    cl[3] = __builtin_fmaf(d.cs, qta, -d.ea * tp);
   }
 }
 
