@@ -204,15 +204,17 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
 MRIP_API mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t reps_per_wave, uint32_t workgroup);
 
 /* Wavefronts per replication for mrip_run on an M/M/1 WAVE context: 1, 2,
- * 4 or 8 (default 1; needs reps_per_wave = 1). With more than one, the
+ * 4 or 8 (default 1; needs reps_per_wave = 1). At the default, runs on
+ * Philox streams that would leave the device idle are split all the same,
+ * to the same values. With more than one, the
  * wavefronts of a workgroup (256 threads, or 512 for 8) each take an equal
  * run of the replication's customers from an empty system; then every part
  * at once re-runs its leading chunks from the carry its predecessor ended
  * with until the two trajectories meet (Lindley's recursion forgets its
  * start once the queue empties), and, in order, a part whose predecessor
  * never met corrects again from that part's true end. On Philox streams the
- * per-customer values are those of the unsplit run and the means differ
- * only by fp32 summation order; on taus88 streams (at most 4) each lane
+ * per-customer values are those of the unsplit run, summed in fp64: the
+ * means are the same; on taus88 streams (at most 4) each lane
  * takes a run of N / (64 split) customers, so values agree to fp32
  * rounding. */
 MRIP_API mrip_status mrip_set_split(mrip_ctx ctx, uint32_t waves_per_rep);

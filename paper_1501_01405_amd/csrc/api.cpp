@@ -500,6 +500,49 @@ uint64_t lanes_per_rep(mrip_ctx c) {
   return 64;
 }
 
+// Wavefronts per replication of an M/M/1 run in the default shape (one
+// wavefront per replication, unless mrip_set_split says otherwise): runs
+// that leave SIMDs idle, or end in an uneven last round, are split as
+// mrip_set_split would, which gives the same bits. The lines follow kernel
+// times over customers x replications (us for 1 / 2 / 4 / 8 wavefronts, rho
+// 0.9): 4000 x 300 10.3 / 8.8 / 9.9 / -, 7000 x 1500 21.9 / 17.8 / 24.9 / -,
+// 10000 x 300 19.0 / 11.4 / 10.6 / -, 10000 x 2048 28.4 / 28.9 / 34.2 / -, 20000
+// x 700 29.5 / 24.6 / 21.0 / 25.2, 20000 x 4096 87 / 84 / 92 / 94, 20000 x 8192
+// 166 / 174 / 185 / -, 1e5 x 32 115 / 65 / 34.4 / 32.4, 1e5 x 1024 119 / 108 /
+// 101 / 102, 54321 x 4096 225 / 211 / 208 / 217. A part's correction lasts until
+// its queue has emptied, so near critical load only idle SIMDs pay for it
+// (20000 customers, rho 0.95: 300 replications 29.2 / 22.2 / 19.6, 1024 31.4 /
+// 32.3 / 32.9; rho 0.97: 54321 x 300 67 / 56 / 50, 20000 x 300 29.0 / 29.4 /
+// 29.0; rho 0.99: 1e5 x 300 117 / 137 / 166) and above that nothing is split.
+static uint32_t default_split(mrip_ctx c, uint64_t n_reps) {
+  const uint64_t chunk = 1024;  // customers a wavefront takes at a time
+  const uint64_t chunks = (c->mm1.customers + chunk - 1) / chunk;
+  const bool ft = c->mm1.feature_prefix > 0;
+  const double rho = (double)c->mm1.lambda / (double)c->mm1.mu;
+  uint64_t max2 = 0, max4 = 0, max8 = 0;  // replications up to which 2, 4, 8 are taken
+  if (rho <= 0.92) {
+    if (chunks >= 48) {
+      max2 = 4096;
+      max4 = ft ? 512 : 4096;
+      max8 = chunks >= 64 ? 256 : 0;
+    } else if (chunks >= 16) {
+      max2 = ft ? 1024 : 4096;
+      max4 = ft ? 512 : 704;
+    } else if (chunks >= 8) {
+      max2 = ft ? 1024 : 1500;
+      max4 = 320;
+    } else if (chunks >= 4) {
+      max2 = ft ? 512 : 640;
+    }
+  } else if (rho <= 0.96) {
+    if (chunks >= 8) max2 = max4 = 512;
+    else if (chunks >= 4) max2 = 512;
+  } else if (rho <= 0.975) {
+    if (chunks >= 48) max2 = max4 = 512;
+  }
+  return n_reps <= max8 ? 8 : n_reps <= max4 ? 4 : n_reps <= max2 ? 2 : 1;
+}
+
 mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_stream) {
   if (!ctx) return MRIP_E_INVAL;
   if (n_reps == 0) return inval(ctx, "n_reps must be >= 1");
@@ -517,6 +560,10 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
   bool overlap = true;
   for (uint32_t o = 0; o < mrip_ctx_s::MAX_OUT; ++o) overlap = overlap && !ctx->bound[o].p;
   const bool wave = ctx->mapping == MRIP_MAP_WAVE;
+  uint32_t split = ctx->split;  // wavefronts per M/M/1 replication
+  if (ctx->model == MRIP_MM1 && wave && split == 1 && ctx->rpw == 1 &&
+      ctx->rng == MRIP_RNG_PHILOX)
+    split = default_split(ctx, n_reps);
   // the headline form, one kernel per run, times itself
   const bool self_timed = kSelfTimedLaunch && ctx->model == MRIP_MM1 && wave && ctx->split > 1 &&
                           ctx->rng == MRIP_RNG_PHILOX;
@@ -655,8 +702,8 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     }
     if (self_timed) {
       const KernelEvents ev = kernel_events(ctx);
-      HIP_TRY(ctx, launch_mm1_split(a, ctx->split, s, &ev));
-    } else if (wave && ctx->split > 1) HIP_TRY(ctx, launch_mm1_split(a, ctx->split, s));
+      HIP_TRY(ctx, launch_mm1_split(a, split, s, &ev));
+    } else if (wave && split > 1) HIP_TRY(ctx, launch_mm1_split(a, split, s));
     else if (wave) HIP_TRY(ctx, launch_mm1_wave(a, ctx->rpw, ctx->wg, s));
     else HIP_TRY(ctx, launch_mm1_simt(a, ctx->mapping == MRIP_MAP_LANE0, s));
   } else if (ctx->model == MRIP_PI) {

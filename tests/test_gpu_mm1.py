@@ -220,3 +220,26 @@ def test_mm1_same_bits_in_every_wave_form(gpu, N, lam, K):
         ref = outs if ref is None else ref
         for a, b in zip(outs, ref):
             assert np.array_equal(a, b), (rpw, split)
+
+
+@pytest.mark.parametrize("lam,K", [(0.9, 0), (0.95, 0), (0.97, 0), (1.2, 0), (0.9, 800)])
+@pytest.mark.parametrize("N", [3500, 4097, 9000, 17000, 50000, 66000])
+def test_mm1_default_shape_same_bits_for_any_replications(gpu, N, lam, K):
+    # the default shape splits a replication by how many there are: the first
+    # ones are the same bits whatever the number run, and those of a run that
+    # is never split (16 customers per lane on 32 lanes)
+    announce("mm1 default split", N, lam, K)
+    few, last = None, None
+    for R in (3, 260, 700, 1300):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(lam, 1.0, N, K), WAVE)
+        ctx.run(R, seed=4)
+        outs = [ctx.output(o).cpu().numpy() for o in ((0, 1, 2, 3, 4) if K else (0, 1, 2))]
+        assert ctx.shape()["split"] == 1
+        few = outs if few is None else few
+        assert all(np.array_equal(a[:3], b) for a, b in zip(outs, few)), R
+        last = outs
+    ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(lam, 1.0, N, K), WAVE)
+    ctx.set_shape(2, 256)
+    ctx.run(1300, seed=4)
+    for o in range(3):
+        assert np.array_equal(ctx.output(o).cpu().numpy(), last[o])
