@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -78,60 +79,53 @@ uint32_t ff_threshold(double prob) {
   return (uint32_t)v;
 }
 
-// The run's statistics land in pinned host memory that the reduction
-// kernel writes directly (no copy launch), one ring slot per run; reading
-// them waits for that slot's event.
+// The run's statistics land in pinned host memory that the reduction kernel
+// writes directly (no copy launch), one ring slot per run, in a form that
+// tells the polling host they are there; an event after the reduction is
+// there for a host that waits long.
 mrip_status ensure_events(mrip_ctx c) {
   for (uint32_t i = 0; i < mrip_ctx_s::STATS_RING; ++i)
     if (!c->ev_stats[i])
       HIP_TRY(c, hipEventCreateWithFlags(&c->ev_stats[i], hipEventDisableTiming));
-  for (uint32_t i = 0; i < 2; ++i)
-    if (!c->ev_set_free[i])
-      HIP_TRY(c, hipEventCreateWithFlags(&c->ev_set_free[i], hipEventDisableTiming));
-  if (!c->red_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->red_stream, hipStreamNonBlocking));
   if (!c->stats_host) {
-    const size_t bytes = sizeof(double) * mrip_ctx_s::STATS_RING * mrip_ctx_s::STATS_SLOT;
-    HIP_TRY(c, hipHostMalloc((void **)&c->stats_host, bytes, hipHostMallocMapped));
+    constexpr uint32_t words = mrip_ctx_s::STATS_RING * mrip_ctx_s::STATS_SLOT;
+    HIP_TRY(c, hipHostMalloc((void **)&c->stats_host, sizeof(uint64_t) * words, hipHostMallocMapped));
+    for (uint32_t i = 0; i < words; ++i) c->stats_host[i] = 0;
     HIP_TRY(c, hipHostGetDevicePointer((void **)&c->stats_view, c->stats_host, 0));
-  }
-  if (!c->seq_host) {
-    HIP_TRY(c, hipHostMalloc((void **)&c->seq_host, sizeof(uint64_t) * mrip_ctx_s::STATS_RING,
-                             hipHostMallocMapped));
-    for (uint32_t i = 0; i < mrip_ctx_s::STATS_RING; ++i) c->seq_host[i] = 0;
-    HIP_TRY(c, hipHostGetDevicePointer((void **)&c->seq_view, c->seq_host, 0));
   }
   if (!c->switch_ev) HIP_TRY(c, hipEventCreateWithFlags(&c->switch_ev, hipEventDisableTiming));
   return MRIP_OK;
 }
 
-// Device view of the next run's statistics slot.
-double *next_stats_slot(mrip_ctx c) {
-  const uint32_t slot = (uint32_t)(c->stats_runs % mrip_ctx_s::STATS_RING);
-  return c->stats_view + (size_t)slot * mrip_ctx_s::STATS_SLOT;
+uint32_t stats_slot(uint64_t index) { return (uint32_t)(index % mrip_ctx_s::STATS_RING); }
+// Device view of a run's statistics.
+uint64_t *stats_of(mrip_ctx c, uint64_t index) {
+  return c->stats_view + (size_t)stats_slot(index) * mrip_ctx_s::STATS_SLOT;
 }
 
-// Before a run on stream s writes output set `set`: wait for the reduction
-// that may still be reading it.
-mrip_status claim_set(mrip_ctx c, uint32_t set, hipStream_t s) {
-  if (!c->set_pending[set]) return MRIP_OK;
-  // a reduction already finished needs no wait packet on the run's stream
-  const hipError_t q = hipEventQuery(c->ev_set_free[set]);
-  if (q == hipSuccess) {
-    c->set_pending[set] = false;
-    return MRIP_OK;
+// Whether a run's mean and variance of one output are in pinned memory, and
+// if so the values (reduce_dev.hpp, publish, says why this needs no order).
+bool published(mrip_ctx c, uint64_t index, uint32_t output, double *mean_var) {
+  const uint64_t *w =
+      c->stats_host + (size_t)stats_slot(index) * mrip_ctx_s::STATS_SLOT + 4 * output;
+  uint64_t v[2];
+  for (int i = 0; i < 2; ++i) {
+    v[i] = __atomic_load_n(w + i, __ATOMIC_RELAXED);
+    if (__atomic_load_n(w + 2 + i, __ATOMIC_RELAXED) != (v[i] ^ (index + 1))) return false;
   }
-  if (q != hipErrorNotReady) return hip_fail(c, q, "hipEventQuery(ev_set_free)");
-  (void)hipGetLastError();  // "not ready" is an answer, not a failure to keep
-  HIP_TRY(c, hipStreamWaitEvent(s, c->ev_set_free[set], 0));
-  return MRIP_OK;
+  std::memcpy(mean_var, v, sizeof(v));
+  return true;
 }
 
-// Mark the slot written by the reduction just enqueued on s.
-mrip_status commit_stats_slot(mrip_ctx c, hipStream_t s) {
-  const uint32_t slot = (uint32_t)(c->stats_runs % mrip_ctx_s::STATS_RING);
+// Enqueue the reduction of run `index`'s scalar outputs on s into its
+// statistics slot, with the event that is the last thing enqueued there.
+mrip_status reduce_run(mrip_ctx c, uint64_t index, const ReduceSet &rs, uint32_t outputs,
+                       uint64_t n, hipStream_t s) {
+  const uint32_t slot = stats_slot(index);
+  HIP_TRY(c, launch_reduce_f64_multi(rs, outputs, n, stats_of(c, index), index + 1, s));
   HIP_TRY(c, hipEventRecord(c->ev_stats[slot], s));
-  c->slot_by_seq[slot] = false;
-  ++c->stats_runs;
+  c->deferred_stream[slot] = {};
+  c->stats_n[slot] = n;
   return MRIP_OK;
 }
 
@@ -167,8 +161,7 @@ void mark_unmarked(mrip_ctx c, hipStream_t s) {
 }
 
 // Launch the deferred reduction of the last uniform run on its stream (no
-// later run of the same form on that stream will carry it) and signal its
-// statistics slot by event, as a run that reduces at once does.
+// later run of the same form on that stream will carry it).
 mrip_status flush_pending(mrip_ctx c) {
   if (!c->pend.active) return MRIP_OK;
   const mrip_ctx_s::Pending p = c->pend;
@@ -178,42 +171,48 @@ mrip_status flush_pending(mrip_ctx c) {
     rs.x[o] = c->out[p.set][o].p;
     rs.dtype[o] = 1;
   }
-  const uint32_t slot = (uint32_t)(p.stats_index % mrip_ctx_s::STATS_RING);
-  HIP_TRY(c, launch_reduce_f64_multi(rs, 3, p.n,
-                                     c->stats_view + (size_t)slot * mrip_ctx_s::STATS_SLOT, p.stream));
-  HIP_TRY(c, hipEventRecord(c->ev_stats[slot], p.stream));
-  c->slot_by_seq[slot] = false;
+  mrip_status st = reduce_run(c, p.stats_index, rs, 3, p.n, p.stream);
+  if (st != MRIP_OK) return st;
   // the pending run was the last call's (any call flushes before its own work)
-  mark_done(c, p.stream, c->ev_stats[slot]);
+  mark_done(c, p.stream, c->ev_stats[stats_slot(p.stats_index)]);
   return MRIP_OK;
 }
 
-// Wait for the statistics a kernel publishes by sequence number: poll the
-// slot's number in pinned memory; a stream that has drained without
-// publishing it, or reports an error, ends the wait with an error.
-mrip_status wait_seq(mrip_ctx c, uint32_t slot, uint64_t value) {
+// Wait for a run's statistics of one output: poll them in pinned memory (a
+// result is seen 5 us sooner than through its event), then, from about a
+// millisecond on, sleep until the event recorded after the reduction. A
+// reduction carried by the next run's kernel has no such event: there the
+// stream is asked now and then, and one that has drained without publishing
+// them, or reports an error, ends the wait with an error.
+mrip_status wait_stats(mrip_ctx c, uint64_t index, uint32_t output, double *mean_var) {
+  const uint32_t slot = stats_slot(index);
+  const mrip_ctx_s::DeferredStream d = c->deferred_stream[slot];
+  const auto t0 = std::chrono::steady_clock::now();
   for (uint32_t spin = 1;; ++spin) {
-    if (__atomic_load_n(c->seq_host + slot, __ATOMIC_ACQUIRE) >= value) return MRIP_OK;
-    if ((spin & 255) == 0) {
-      const hipError_t q = hipStreamQuery(c->seq_stream[slot]);
-      if (q == hipSuccess) {
-        if (__atomic_load_n(c->seq_host + slot, __ATOMIC_ACQUIRE) >= value) return MRIP_OK;
-        c->err = "a run's statistics were not published";
-        return MRIP_E_HIP;
-      }
-      if (q != hipErrorNotReady) return hip_fail(c, q, "hipStreamQuery");
-      (void)hipGetLastError();  // "not ready" is an answer, not a failure to keep
-      std::this_thread::yield();
+    if (published(c, index, output, mean_var)) return MRIP_OK;
+    if ((spin & 255) != 0) continue;
+    bool over = false;
+    if (d.used) {
+      const hipError_t q = hipStreamQuery(d.stream);
+      if (q != hipSuccess && q != hipErrorNotReady) return hip_fail(c, q, "hipStreamQuery");
+      over = q == hipSuccess;
+      if (!over) (void)hipGetLastError();  // "not ready" is an answer, not a failure to keep
+    } else if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1)) {
+      HIP_TRY(c, hipEventSynchronize(c->ev_stats[slot]));
+      over = true;
     }
+    if (over) {
+      if (published(c, index, output, mean_var)) return MRIP_OK;
+      c->err = "a run's statistics were not published";
+      return MRIP_E_HIP;
+    }
+    std::this_thread::yield();
   }
 }
 
-// The last run-history and statistics events recorded.
+// The last run-history event recorded.
 hipEvent_t last_ring_event(mrip_ctx c) {
   return c->ring1[(c->launches - 1) % mrip_ctx_s::RING];
-}
-hipEvent_t last_stats_event(mrip_ctx c) {
-  return c->ev_stats[(c->stats_runs - 1) % mrip_ctx_s::STATS_RING];
 }
 
 // Events bracketing one simulation-kernel launch: the next slot of the
@@ -425,8 +424,9 @@ mrip_status mrip_create(mrip_ctx *out, mrip_model model, const void *params,
 
 void mrip_destroy(mrip_ctx ctx) {
   if (!ctx) return;
-  if (ctx->last_stream) (void)hipStreamSynchronize(ctx->last_stream);
-  if (ctx->red_stream) (void)hipStreamSynchronize(ctx->red_stream);
+  // reductions may still write the pinned statistics (the null stream is a
+  // stream like any other)
+  if (ctx->last_stream || ctx->stats_runs > 0) (void)hipStreamSynchronize(ctx->last_stream);
   delete ctx;
 }
 
@@ -554,9 +554,9 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
   mrip_status st = ensure_events(ctx);
   if (st != MRIP_OK) return st;
   const uint32_t nout = scalar_outputs(ctx);
-  // With the outputs in the context's buffers, the reduction runs on the
-  // library's own stream, so the next run's simulation need not wait for
-  // it: runs alternate between two output sets.
+  // With the outputs in the context's buffers, runs alternate between two
+  // output sets, so that a run whose reduction is deferred leaves its set to
+  // the next run's kernel.
   bool overlap = true;
   for (uint32_t o = 0; o < mrip_ctx_s::MAX_OUT; ++o) overlap = overlap && !ctx->bound[o].p;
   const bool wave = ctx->mapping == MRIP_MAP_WAVE;
@@ -579,8 +579,6 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
   st = order_after_last(ctx, s);
   if (st != MRIP_OK) return st;
   const uint32_t set = overlap ? ctx->next_set : 0u;
-  st = claim_set(ctx, set, s);
-  if (st != MRIP_OK) return st;
   void *outp[mrip_ctx_s::MAX_OUT] = {};
   for (uint32_t o = 0; o < nout; ++o) {
     st = output_buffer(ctx, set, o, n_reps * 4, &outp[o]);
@@ -608,14 +606,12 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     a.rng = ctx->rng;
     if (ctx->pend.active) {  // the previous run's statistics, in this launch
       const mrip_ctx_s::Pending &p = ctx->pend;
-      const uint32_t slot = (uint32_t)(p.stats_index % mrip_ctx_s::STATS_RING);
       for (uint32_t o = 0; o < 3; ++o) a.prev_x[o] = ctx->out[p.set][o].as<float>();
       a.prev_n = p.n;
-      a.prev_out = ctx->stats_view + (size_t)slot * mrip_ctx_s::STATS_SLOT;
-      a.prev_seq = ctx->seq_view + slot;
-      a.prev_seq_value = p.stats_index + 1;
-      ctx->slot_by_seq[slot] = true;
-      ctx->seq_stream[slot] = s;
+      a.prev_out = stats_of(ctx, p.stats_index);
+      a.prev_tag = p.stats_index + 1;
+      ctx->deferred_stream[stats_slot(p.stats_index)] = {true, s};
+      ctx->stats_n[stats_slot(p.stats_index)] = p.n;
       ctx->pend.active = false;
     }
     HIP_TRY(ctx, launch_mm1_split(a, ctx->split, s, timed ? &ev : nullptr));
@@ -628,8 +624,6 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     ctx->pend.set = set;
     ctx->pend.n = n_reps;
     ctx->pend.stats_index = ctx->stats_runs++;
-    // the set's next writer follows on s, after the kernel that reduces it
-    ctx->set_pending[set] = false;
     ctx->next_set = set ^ 1u;
     if (timed) mark_done(ctx, s, last_ring_event(ctx));
     else mark_unmarked(ctx, s);
@@ -746,31 +740,24 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
   st = record_end(ctx, s, !self_timed);
   if (st != MRIP_OK) return st;
   // all scalar outputs in one reduction launch, written straight into
-  // pinned host memory, so mrip_stats only waits for an event
+  // pinned host memory
   ReduceSet rs{};
   for (uint32_t o = 0; o < nout; ++o) {
     rs.x[o] = outp[o];
     rs.dtype[o] = output_dtype(ctx->model, o);
   }
-  hipStream_t rstream = s;
-  if (overlap) {
-    // the reduction waits for this run's simulation (the event just
-    // recorded after it) on the library's stream
-    const uint32_t slot = (uint32_t)((ctx->launches - 1) % mrip_ctx_s::RING);
-    rstream = ctx->red_stream;
-    HIP_TRY(ctx, hipStreamWaitEvent(rstream, ctx->ring1[slot], 0));
-  }
-  HIP_TRY(ctx, launch_reduce_f64_multi(rs, nout, n_reps, next_stats_slot(ctx), rstream));
-  st = commit_stats_slot(ctx, rstream);
+  // On the run's own stream: one of the library's own, to reduce beside the
+  // next simulation, has to wait for this one's event, and that costs more
+  // than the 3 us it hides. Host time of a run 6.0 us, was 20.5; result of a
+  // 10 us kernel 18.5 us after the call, was 31.0; runs enqueued ahead: 100
+  // replications of 2e4 customers 46 us each, was 53, 1024 of 1e5 (split 8)
+  // 135, was 141, 1024 of 1e4 (taus88) 90 on either.
+  const uint64_t index = ctx->stats_runs;
+  st = reduce_run(ctx, index, rs, nout, n_reps, s);
   if (st != MRIP_OK) return st;
-  if (overlap) {
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_set_free[set], rstream));
-    ctx->set_pending[set] = true;
-    ctx->next_set = set ^ 1u;
-  }
-  // on s: the kernel's end, and after it the reduction unless that ran on
-  // the library's stream
-  mark_done(ctx, s, overlap ? last_ring_event(ctx) : last_stats_event(ctx));
+  mark_done(ctx, s, ctx->ev_stats[stats_slot(index)]);
+  ++ctx->stats_runs;
+  if (overlap) ctx->next_set = set ^ 1u;
   ctx->last = RUN_UNIFORM;
   ctx->last_n = n_reps;
   return MRIP_OK;
@@ -787,21 +774,15 @@ mrip_status mrip_stats_back(mrip_ctx ctx, uint32_t back, uint32_t output, double
   if (back >= mrip_ctx_s::STATS_RING || back >= ctx->stats_runs)
     return (ctx->err = "no statistics kept for that run"), MRIP_E_STATE;
   const uint64_t idx = ctx->stats_runs - 1 - back;
-  const uint32_t slot = (uint32_t)(idx % mrip_ctx_s::STATS_RING);
+  const uint32_t slot = stats_slot(idx);
   if (ctx->pend.active && ctx->pend.stats_index == idx) {
-    mrip_status st = flush_pending(ctx);  // no later run has reduced it yet
+    const mrip_status st = flush_pending(ctx);  // no later run has reduced it yet
     if (st != MRIP_OK) return st;
   }
-  if (ctx->slot_by_seq[slot]) {
-    mrip_status st = wait_seq(ctx, slot, idx + 1);
-    if (st != MRIP_OK) return st;
-  } else {
-    HIP_TRY(ctx, hipEventSynchronize(ctx->ev_stats[slot]));
-  }
-  double nmv[3];
-  std::memcpy(nmv, ctx->stats_host + (size_t)slot * mrip_ctx_s::STATS_SLOT + 3 * output,
-              sizeof(nmv));
-  mrip_status st = finish_stats(nmv, confidence, out);
+  double nmv[3] = {(double)ctx->stats_n[slot]};
+  mrip_status st = wait_stats(ctx, idx, output, nmv + 1);
+  if (st != MRIP_OK) return st;
+  st = finish_stats(nmv, confidence, out);
   if (st == MRIP_E_TOO_FEW) ctx->err = "fewer than two replications";
   return st;
 }
@@ -958,8 +939,6 @@ static mrip_status run_plan_impl(mrip_ctx ctx, uint64_t seed, hipStream_t s, con
   if (st != MRIP_OK) return st;
   if (done && clear_done)
     HIP_TRY(ctx, launch_zero_u32((uint32_t *)done, (uint32_t)((ctx->n_items + 3) / 4), s));
-  st = claim_set(ctx, 0, s);
-  if (st != MRIP_OK) return st;
   void *outp[mrip_ctx_s::MAX_OUT] = {};
   for (uint32_t o = 0; o < 3; ++o) {
     st = output_buffer(ctx, 0, o, ctx->n_items * 4, &outp[o]);
@@ -1010,11 +989,11 @@ static mrip_status run_plan_impl(mrip_ctx ctx, uint64_t seed, hipStream_t s, con
       set.x[o] = outp[o];
       set.dtype[o] = 1;
     }
-    HIP_TRY(ctx, launch_reduce_f64_multi(set, 3, ctx->n_items, next_stats_slot(ctx), s));
-    st = commit_stats_slot(ctx, s);
+    st = reduce_run(ctx, ctx->stats_runs, set, 3, ctx->n_items, s);
     if (st != MRIP_OK) return st;
+    ++ctx->stats_runs;
   }
-  mark_done(ctx, s, reduce ? last_stats_event(ctx) : last_ring_event(ctx));
+  mark_done(ctx, s, reduce ? ctx->ev_stats[stats_slot(ctx->stats_runs - 1)] : last_ring_event(ctx));
   return MRIP_OK;
 }
 

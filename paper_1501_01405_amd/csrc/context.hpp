@@ -131,13 +131,10 @@ struct mrip_ctx_s {
   // runs with a feature prefix, the features (idx 3, 10 per replication)
   // and the controls (idx 4, 8 per replication).
   static constexpr uint32_t MAX_OUT = 5;
-  // Two sets of output buffers: a uniform run writes one while the
-  // reduction of the run before it, on red_stream, still reads the other.
+  // Two sets of output buffers: a uniform run writes one while its kernel
+  // reduces the other, the deferred run before it.
   mrip::DevBuf out[2][MAX_OUT];
-  uint32_t next_set = 0;                 // output set of the next uniform run
-  bool set_pending[2] = {};              // a reduction may still read set i
-  hipEvent_t ev_set_free[2] = {};        // recorded after that reduction
-  hipStream_t red_stream = nullptr;      // the library's stream for reductions
+  uint32_t next_set = 0;  // output set of the next uniform run
   // caller-owned output buffers (mrip_bind_output) and the buffers the last
   // run wrote (bound or owned)
   struct Bound {
@@ -154,8 +151,11 @@ struct mrip_ctx_s {
   // reduction kernel through its device view
   // A ring of STATS_RING slots, one per run, so a caller may read run k's
   // statistics after enqueuing run k + 1.
-  static constexpr uint32_t STATS_RING = 4, STATS_SLOT = 12;  // doubles per slot
-  double *stats_host = nullptr, *stats_view = nullptr;
+  // Per output of a slot four words (reduce_dev.hpp, publish); the tag is the
+  // run's stats index + 1.
+  static constexpr uint32_t STATS_RING = 4, STATS_SLOT = 16;  // words per slot
+  uint64_t *stats_host = nullptr, *stats_view = nullptr;
+  uint64_t stats_n[STATS_RING] = {};     // replications of the slot's run
   hipEvent_t ev_stats[STATS_RING] = {};  // recorded after each slot's reduction
   uint64_t stats_runs = 0;               // reductions enqueued so far
   mrip::RunKind last = mrip::RUN_NONE;
@@ -182,12 +182,12 @@ struct mrip_ctx_s {
     uint64_t n = 0;            // its replications
     uint64_t stats_index = 0;  // its place in the statistics ring
   } pend;
-  // per ring slot: the statistics are signalled by a sequence number the
-  // reducing kernel stores (seq_host[slot] >= stats index + 1) on
-  // seq_stream[slot], instead of by ev_stats[slot]
-  bool slot_by_seq[STATS_RING] = {};
-  hipStream_t seq_stream[STATS_RING] = {};
-  uint64_t *seq_host = nullptr, *seq_view = nullptr;
+  // per ring slot: the stream of the later run whose kernel reduces it (used
+  // false: a reduction launch of its own, with ev_stats[slot] after it)
+  struct DeferredStream {
+    bool used = false;
+    hipStream_t stream = nullptr;
+  } deferred_stream[STATS_RING];
   // time one simulation launch in timing_every with HIP events (0 = none)
   uint32_t timing_every = 1;
   uint64_t timing_count = 0;
@@ -213,13 +213,9 @@ struct mrip_ctx_s {
 
   ~mrip_ctx_s() {
     if (stats_host) (void)hipHostFree(stats_host);
-    if (seq_host) (void)hipHostFree(seq_host);
     if (switch_ev) (void)hipEventDestroy(switch_ev);
     for (uint32_t i = 0; i < STATS_RING; ++i)
       if (ev_stats[i]) (void)hipEventDestroy(ev_stats[i]);
-    for (uint32_t i = 0; i < 2; ++i)
-      if (ev_set_free[i]) (void)hipEventDestroy(ev_set_free[i]);
-    if (red_stream) (void)hipStreamDestroy(red_stream);
     for (uint32_t i = 0; i < RING; ++i) {
       if (ring0[i]) (void)hipEventDestroy(ring0[i]);
       if (ring1[i]) (void)hipEventDestroy(ring1[i]);

@@ -72,14 +72,12 @@ struct Mm1Args {
   const uint32_t *taus;
   // Split kernels of 256-thread workgroups (uniform mode): with prev_n > 0
   // one extra workgroup reduces the previous run's three fp32 outputs
-  // (prev_n replications each) into prev_out, 3 x (n, mean, variance) as
-  // the reduction kernel writes them, then stores prev_seq_value to
-  // *prev_seq (host-visible) once they are visible.
+  // (prev_n replications each) into prev_out (host-visible), as the
+  // reduction kernel does, under prev_tag.
   const float *prev_x[3];
   uint64_t prev_n;
-  double *prev_out;
-  uint64_t *prev_seq;
-  uint64_t prev_seq_value;
+  uint64_t *prev_out;
+  uint64_t prev_tag;
   uint8_t *done;                // plan mode (nullable): done[i] = 1 once item i's outputs are written
   const uint32_t *taus_run;     // taus88: the runs' jump tables (taus_build_run_tables)
 };
@@ -159,9 +157,10 @@ hipError_t launch_pi_simt(const PiArgs &a, bool one_lane, hipStream_t s);
 hipError_t launch_reduce_f64(const void *x, int dtype, uint64_t n, const uint64_t *offsets,
                              uint32_t n_segments, double *out, hipStream_t s);
 // Several outputs of n values each in one launch (one workgroup each):
-// out[3*o + {0,1,2}] for output o (ReduceSet is declared above).
+// per output o four words at out[4*o] in host-visible memory, mean and
+// variance plain and with `tag` mixed in (ReduceSet is declared above).
 hipError_t launch_reduce_f64_multi(const ReduceSet &set, uint32_t n_outputs, uint64_t n,
-                                   double *out, hipStream_t s);
+                                   uint64_t *out, uint64_t tag, hipStream_t s);
 // Gathered variant: segment g reads x[index[offsets[g] .. offsets[g+1])].
 // The pair form reduces two fp32 arrays over the same segments in one launch.
 hipError_t launch_reduce_f64_gather(const void *x, int dtype, const uint32_t *index,

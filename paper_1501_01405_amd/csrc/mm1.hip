@@ -1075,15 +1075,14 @@ __device__ __forceinline__ void split_replication(const Rep &d, int slot, int h,
 }
 
 // The extra workgroup of a split launch: the previous run's statistics,
-// the same bits as the reduction kernel's, then the sequence number that
-// tells the host they are there.
+// the same bits as the reduction kernel's. The three
+// outputs are reduced together and published in one store.
 __device__ void reduce_previous_run(const Mm1Args &a) {
-  __shared__ RedShared sh;
-  for (int o = 0; o < 3; ++o) reduce_output(a.prev_x[o], 1, a.prev_n, a.prev_out + 3 * o, sh);
-  if (threadIdx.x == 0) {
-    __threadfence_system();
-    __hip_atomic_store(a.prev_seq, a.prev_seq_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
+  __shared__ RedShared<3> sh;
+  const float *const x[3] = {a.prev_x[0], a.prev_x[1], a.prev_x[2]};
+  double mean[3], var[3];
+  reduce_outputs<3>(x, a.prev_n, mean, var, sh);
+  publish<3>(a.prev_out, mean, var, a.prev_tag);
 }
 
 template <int X, bool FT>

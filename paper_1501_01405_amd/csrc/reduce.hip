@@ -1,8 +1,7 @@
 // MRIP statistics on the device (paper section 1: a confidence interval from
 // independent replications): per segment of per-replication outputs, the
 // count, the mean and the unbiased variance, in fp64, two passes. The
-// summation order is fixed (thread-strided partial sums, then a fixed tree),
-// so results are reproducible run to run. int32 outputs are summed exactly
+// summation order is fixed, so results are reproducible run to run. int32 outputs are summed exactly
 // in int64 for the mean.
 #include "device.hpp"
 #include "kernels.hpp"
@@ -13,34 +12,10 @@ namespace mrip {
 
 namespace {
 
-constexpr int RB = 256;  // threads per segment
+constexpr int RB = RED_THREADS;  // threads per segment
 
 __device__ __forceinline__ double load_x(const void *x, int dtype, uint64_t i) {
   return dtype == 0 ? (double)((const int32_t *)x)[i] : (double)((const float *)x)[i];
-}
-
-__device__ double block_sum(double v, double *sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = RB / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-__device__ long long block_sum_ll(long long v, long long *sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = RB / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  const long long r = sh[0];
-  __syncthreads();
-  return r;
 }
 
 // Segment blockIdx.x of x (blockIdx.y = 0) or of x1, a second fp32 array
@@ -48,8 +23,7 @@ __device__ long long block_sum_ll(long long v, long long *sh) {
 __global__ void reduce_kernel(const void *x, int dtype, const uint32_t *index,
                               const uint64_t *offsets, uint64_t n, double *out, const float *x1,
                               double *out1) {
-  __shared__ double shd[RB];
-  __shared__ long long shl[RB];
+  __shared__ RedShared<1> sh;
   const uint32_t g = blockIdx.x;
   if (blockIdx.y == 1) {
     x = x1;
@@ -61,34 +35,45 @@ __global__ void reduce_kernel(const void *x, int dtype, const uint32_t *index,
   const uint64_t cnt = end - begin;
   double mean;
   if (dtype == 0) {
-    long long s = 0;
+    long long s[1] = {};
     for (uint64_t j = begin + threadIdx.x; j < end; j += RB)
-      s += ((const int32_t *)x)[index ? index[j] : j];
-    mean = (double)block_sum_ll(s, shl) / (double)cnt;
+      s[0] += ((const int32_t *)x)[index ? index[j] : j];
+    red_block_sums<1>(s, sh.whole);
+    mean = (double)s[0] / (double)cnt;
   } else {
-    double s = 0.0;
+    double s[1] = {};
     for (uint64_t j = begin + threadIdx.x; j < end; j += RB)
-      s += load_x(x, dtype, index ? index[j] : j);
-    mean = block_sum(s, shd) / (double)cnt;
+      s[0] += load_x(x, dtype, index ? index[j] : j);
+    red_block_sums<1>(s, sh.first);
+    mean = s[0] / (double)cnt;
   }
-  double ss = 0.0;
+  double ss[1] = {};
   for (uint64_t j = begin + threadIdx.x; j < end; j += RB) {
     const double d = load_x(x, dtype, index ? index[j] : j) - mean;
-    ss += d * d;
+    ss[0] += d * d;
   }
-  ss = block_sum(ss, shd);
+  red_block_sums<1>(ss, sh.second);
   if (threadIdx.x == 0) {
     out[3 * g + 0] = (double)cnt;
     out[3 * g + 1] = cnt > 0 ? mean : 0.0;
-    out[3 * g + 2] = cnt > 1 ? ss / (double)(cnt - 1) : 0.0;
+    out[3 * g + 2] = cnt > 1 ? ss[0] / (double)(cnt - 1) : 0.0;
   }
 }
 
 // One workgroup per output: the same fixed-order two-pass reduction.
-__global__ void reduce_multi_kernel(ReduceSet set, uint64_t n, double *out) {
-  __shared__ RedShared sh;
+__global__ __launch_bounds__(RB) void reduce_multi_kernel(ReduceSet set, uint64_t n, uint64_t *out,
+                                                          uint64_t tag) {
+  __shared__ RedShared<1> sh;
   const uint32_t o = blockIdx.x;
-  reduce_output(set.x[o], set.dtype[o], n, out + 3 * o, sh);
+  double mean[1], var[1];
+  if (set.dtype[o] == 0) {
+    const int32_t *const x[1] = {(const int32_t *)set.x[o]};
+    reduce_outputs<1>(x, n, mean, var, sh);
+  } else {
+    const float *const x[1] = {(const float *)set.x[o]};
+    reduce_outputs<1>(x, n, mean, var, sh);
+  }
+  publish<1>(out + 4 * o, mean, var, tag);
 }
 
 __global__ void philox_dump_kernel(uint64_t seed, const uint32_t *ctr, uint64_t n,
@@ -138,8 +123,8 @@ hipError_t launch_reduce_f64_gather2(const float *x0, const float *x1, const uin
 }
 
 hipError_t launch_reduce_f64_multi(const ReduceSet &set, uint32_t n_outputs, uint64_t n,
-                                   double *out, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_multi_kernel, dim3(n_outputs), dim3(RB), 0, s, set, n, out);
+                                   uint64_t *out, uint64_t tag, hipStream_t s) {
+  hipLaunchKernelGGL(reduce_multi_kernel, dim3(n_outputs), dim3(RB), 0, s, set, n, out, tag);
   return hipGetLastError();
 }
 

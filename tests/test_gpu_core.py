@@ -107,6 +107,31 @@ def test_statistics_of_earlier_runs_are_kept(gpu):
         ctx.stats_back(4, 0)  # only the last four runs are kept
 
 
+@pytest.mark.parametrize("R", [2, 63, 256, 257, 2047, 2048, 2049, 4097])
+def test_statistics_of_runs_enqueued_ahead(gpu, R):
+    # whole and fp32 outputs, at the edges of what the reduction keeps of a
+    # thread's values between its passes (8 x 256); equal runs in a row give
+    # equal statistics in every ring slot. fp64 sums of R terms: 4097 * 2^-53
+    # is 5e-13 of the mean, and the variance adds squares of like error.
+    announce("stats enqueued ahead", R)
+    ctx = mrip.Context(mrip.MRIP_PI, mrip.pi_params(1000), WAVE)
+    seeds = [3, 3, 4, 5, 5, 5, 5, 5, 6, 3]
+    want, got = [], []
+    for k, sd in enumerate(seeds):
+        one = mrip.Context(mrip.MRIP_PI, mrip.pi_params(1000), WAVE)
+        one.run(R, seed=sd)
+        want.append([one.output(o).cpu().numpy().astype(np.float64) for o in range(2)])
+        ctx.run(R, seed=sd)
+        if k >= 3:
+            got.append([ctx.stats_back(3, o) for o in range(2)])
+    got += [[ctx.stats_back(b, o) for o in range(2)] for b in (2, 1, 0)]
+    for x, s in zip(want, got):
+        for o in range(2):
+            assert s[o]["n"] == R
+            assert s[o]["mean"] == pytest.approx(x[o].mean(), rel=1e-12)
+            assert s[o]["var"] == pytest.approx(x[o].var(ddof=1), rel=4e-12)
+
+
 @pytest.mark.parametrize("rng", [mrip.MRIP_RNG_PHILOX, mrip.MRIP_RNG_TAUS88])
 def test_rw_segmented_and_sequential_forms_agree(gpu, rng):
     # up to 2048 replications the walk runs as a segmented scan, beyond it
