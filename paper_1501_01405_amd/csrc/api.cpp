@@ -382,6 +382,99 @@ uint32_t mrip::plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total) {
   return x;
 }
 
+namespace mrip {
+
+// Upload items (SoA), their longest-first order (and how many of its first
+// items are long), their dp grouping and, with `bins`, each item's row of the
+// coefficient table (its design point's bin of rho). One copy from pinned
+// memory and no sort of a table that is in order already: for 16384 items
+// 130 us, where nine copies and two sorts took 750.
+mrip_status upload_items(mrip_ctx c, const mrip_plan_item *items, uint64_t n, uint64_t K,
+                         uint64_t long_min, bool bins, ItemBufs &b, hipStream_t s) {
+  for (uint64_t i = 0; i < n; ++i) {
+    const mrip_plan_item &it = items[i];
+    if (it.customers < 1 || it.customers >= (1ull << 33)) return inval(c, "item customers out of range");
+    if (it.customers < K) return inval(c, "item shorter than the feature prefix");
+    if (!(it.lambda > 0.0f) || !(it.mu > 0.0f) || !std::isfinite(it.lambda) || !std::isfinite(it.mu))
+      return inval(c, "item rates must be finite and > 0");
+  }
+  b.count = 0;  // no table until all of it is there
+  if (b.in_flight) {  // left so by a call that failed
+    HIP_TRY(c, hipDeviceSynchronize());
+    b.in_flight = false;
+  }
+  // customers | dp | rep | lambda | mu | order | index | bin | offsets, the
+  // last (as many as there are design points) on an 8-byte boundary
+  const size_t words = (bins ? 7 : 6) * n;
+  const size_t offsets_at = 8 * n + (4 * words + 7) / 8 * 8;
+  HIP_TRY(c, b.table.ensure(offsets_at + 8 * (n + 1)));
+  HIP_TRY(c, b.staging.ensure(offsets_at + 8 * (n + 1)));
+  char *host = (char *)b.staging.p, *dev = (char *)b.table.p;
+  const auto array = [&](int k) { return 8 * n + 4 * (size_t)k * n; };
+  uint64_t *cust = (uint64_t *)host, *offsets = (uint64_t *)(host + offsets_at);
+  uint32_t *dp = (uint32_t *)(host + array(0)), *rep = (uint32_t *)(host + array(1));
+  float *lam = (float *)(host + array(2)), *mu = (float *)(host + array(3));
+  uint32_t *order = (uint32_t *)(host + array(4)), *index = (uint32_t *)(host + array(5));
+  b.max_customers = b.total_customers = 0;
+  bool longest_first = true, grouped = true;  // the tables often come in both orders
+  for (uint64_t i = 0; i < n; ++i) {
+    const mrip_plan_item &it = items[i];
+    cust[i] = it.customers;
+    dp[i] = it.dp;
+    rep[i] = it.rep;
+    lam[i] = it.lambda;
+    mu[i] = it.mu;
+    order[i] = index[i] = (uint32_t)i;
+    b.max_customers = std::max<uint64_t>(b.max_customers, it.customers);
+    b.total_customers += it.customers;
+    if (i > 0) {
+      longest_first = longest_first && it.customers <= items[i - 1].customers;
+      grouped = grouped && it.dp >= items[i - 1].dp;
+    }
+  }
+  if (bins) {
+    uint32_t *bin = (uint32_t *)(host + array(6));
+    for (uint64_t i = 0; i < n; ++i)
+      bin[i] = i > 0 && lam[i] == lam[i - 1] && mu[i] == mu[i - 1]
+                   ? bin[i - 1]
+                   : (uint32_t)c->cv.bin_of(lam[i] / mu[i]);
+  }
+  if (!longest_first)
+    std::stable_sort(order, order + n, [&](uint32_t a, uint32_t b2) { return cust[a] > cust[b2]; });
+  if (!grouped)
+    std::stable_sort(index, index + n, [&](uint32_t a, uint32_t b2) { return dp[a] < dp[b2]; });
+  b.dp_ids.clear();
+  b.group_offsets.clear();
+  for (uint64_t j = 0; j < n; ++j) {
+    if (j == 0 || dp[index[j]] != dp[index[j - 1]]) {
+      b.group_offsets.push_back(j);
+      b.dp_ids.push_back(dp[index[j]]);
+    }
+  }
+  b.group_offsets.push_back(n);
+  std::copy(b.group_offsets.begin(), b.group_offsets.end(), offsets);
+  b.index_host.assign(index, index + n);
+  b.order_host.assign(order, order + n);
+  b.n_long = 0;  // items of at least long_min customers: a prefix of the order
+  while (b.n_long < n && cust[order[b.n_long]] >= long_min) ++b.n_long;
+  b.in_flight = true;
+  HIP_TRY(c, hipMemcpyAsync(dev, host, offsets_at + 8 * b.group_offsets.size(),
+                           hipMemcpyHostToDevice, s));
+  b.n = (const uint64_t *)dev;
+  b.dp = (const uint32_t *)(dev + array(0));
+  b.rep = (const uint32_t *)(dev + array(1));
+  b.lambda = (const float *)(dev + array(2));
+  b.mu = (const float *)(dev + array(3));
+  b.order = (const uint32_t *)(dev + array(4));
+  b.index = (const uint32_t *)(dev + array(5));
+  b.bin = bins ? (const uint32_t *)(dev + array(6)) : nullptr;
+  b.offsets = (const uint64_t *)(dev + offsets_at);
+  b.count = n;
+  return MRIP_OK;
+}
+
+}  // namespace mrip
+
 extern "C" {
 
 const char *mrip_version(void) { return "mrip 0.1 (gfx950)"; }
@@ -808,7 +901,9 @@ mrip_status mrip_outputs(mrip_ctx ctx, uint32_t output, void *dst, uint64_t byte
   if (output >= scalar_outputs(ctx) && !vec) return inval(ctx, "no such output");
   const uint64_t need = ctx->last_n * 4 * (vec ? vector_width(ctx, output) : 1);
   if (bytes < need) return inval(ctx, "destination too small");
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
+  // after the run: a copy on the null stream follows that stream's work by
+  // itself, and a host wait here would be for the last output's copy (11 us)
+  if (ctx->last_stream) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
   HIP_TRY(ctx, hipMemcpy(dst, ctx->cur[output], need,
                          dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost));
   return MRIP_OK;
@@ -849,62 +944,22 @@ mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n)
   if (ctx->model != MRIP_MM1) return (ctx->err = "plans need an M/M/1 context"), MRIP_E_UNSUPPORTED;
   if (!items || n == 0) return inval(ctx, "empty plan");
   if (n > 0xFFFFFFFFull) return inval(ctx, "plan too large");
-  std::vector<uint32_t> dp(n), rep(n), order(n), index(n);
-  std::vector<uint64_t> cust(n);
-  std::vector<float> lam(n), mu(n);
-  for (uint64_t i = 0; i < n; ++i) {
-    const mrip_plan_item &it = items[i];
-    if (it.customers < 1 || it.customers >= (1ull << 33)) return inval(ctx, "item customers out of range");
-    if (!(it.lambda > 0.0f) || !(it.mu > 0.0f) || !std::isfinite(it.lambda) || !std::isfinite(it.mu))
-      return inval(ctx, "item rates must be finite and > 0");
-    if (ctx->mm1.feature_prefix > it.customers) return inval(ctx, "item shorter than the feature prefix");
-    dp[i] = it.dp;
-    rep[i] = it.rep;
-    cust[i] = it.customers;
-    lam[i] = it.lambda;
-    mu[i] = it.mu;
-    order[i] = (uint32_t)i;
-    index[i] = (uint32_t)i;
-  }
-  // longest-processing-time-first queue order
-  std::stable_sort(order.begin(), order.end(),
-                   [&](uint32_t a, uint32_t b) { return cust[a] > cust[b]; });
-  // items grouped by design point for the per-dp reductions
-  std::stable_sort(index.begin(), index.end(), [&](uint32_t a, uint32_t b) { return dp[a] < dp[b]; });
-  std::vector<uint64_t> offsets;
-  std::vector<uint32_t> ids;
-  for (uint64_t j = 0; j < n; ++j) {
-    if (j == 0 || dp[index[j]] != dp[index[j - 1]]) {
-      offsets.push_back(j);
-      ids.push_back(dp[index[j]]);
-    }
-  }
-  offsets.push_back(n);
   // an earlier plan run may still read the item buffers
   if (ctx->last_stream) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
-  HIP_TRY(ctx, ctx->it_dp.ensure(4 * n));
-  HIP_TRY(ctx, ctx->it_rep.ensure(4 * n));
-  HIP_TRY(ctx, ctx->it_n.ensure(8 * n));
-  HIP_TRY(ctx, ctx->it_lambda.ensure(4 * n));
-  HIP_TRY(ctx, ctx->it_mu.ensure(4 * n));
-  HIP_TRY(ctx, ctx->it_order.ensure(4 * n));
-  HIP_TRY(ctx, ctx->dp_index.ensure(4 * n));
-  HIP_TRY(ctx, ctx->dp_offsets.ensure(8 * offsets.size()));
-  HIP_TRY(ctx, ctx->dp_stats.ensure(sizeof(double) * 3 * ids.size()));
+  ItemBufs &b = ctx->items;
+  mrip_status st = upload_items(ctx, items, n, ctx->mm1.feature_prefix, ctx->long_min, false, b,
+                                nullptr);
+  if (b.count == 0) ctx->n_items = 0;  // the old plan's table is gone (a refused plan leaves it)
+  if (st != MRIP_OK) return st;
+  HIP_TRY(ctx, ctx->dp_stats.ensure(sizeof(double) * 3 * b.dp_ids.size()));
   HIP_TRY(ctx, ctx->queue.ensure(256));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_dp.p, dp.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_rep.p, rep.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_n.p, cust.data(), 8 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_lambda.p, lam.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_mu.p, mu.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->it_order.p, order.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->dp_index.p, index.data(), 4 * n, hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->dp_offsets.p, offsets.data(), 8 * offsets.size(), hipMemcpyHostToDevice));
+  HIP_TRY(ctx, hipStreamSynchronize(nullptr));
+  b.in_flight = false;
   ctx->n_items = n;
-  ctx->dp_ids = ids;
+  ctx->dp_ids = b.dp_ids;
+  ctx->lpt_order = b.order_host;
   ctx->lpt_customers.resize(n);
-  for (uint64_t j = 0; j < n; ++j) ctx->lpt_customers[j] = cust[order[j]];
-  ctx->lpt_order = order;
+  for (uint64_t j = 0; j < n; ++j) ctx->lpt_customers[j] = items[b.order_host[j]].customers;
   return MRIP_OK;
 }
 
@@ -955,11 +1010,11 @@ static mrip_status run_plan_impl(mrip_ctx ctx, uint64_t seed, hipStream_t s, con
     a.features = (float *)outp[3];
     a.controls = (float *)outp[4];
   }
-  a.items.dp = ctx->it_dp.as<uint32_t>();
-  a.items.rep = ctx->it_rep.as<uint32_t>();
-  a.items.customers = ctx->it_n.as<uint64_t>();
-  a.items.lambda = ctx->it_lambda.as<float>();
-  a.items.mu = ctx->it_mu.as<float>();
+  a.items.dp = ctx->items.dp;
+  a.items.rep = ctx->items.rep;
+  a.items.customers = ctx->items.n;
+  a.items.lambda = ctx->items.lambda;
+  a.items.mu = ctx->items.mu;
   a.items.order = order;
   a.queue_head = ctx->queue.as<uint32_t>();
   a.done = done;
@@ -981,9 +1036,9 @@ static mrip_status run_plan_impl(mrip_ctx ctx, uint64_t seed, hipStream_t s, con
   st = record_end(ctx, s);
   if (st != MRIP_OK) return st;
   if (reduce) {
-    HIP_TRY(ctx, launch_reduce_f64_gather(outp[0], 1, ctx->dp_index.as<uint32_t>(),
-                                          ctx->dp_offsets.as<uint64_t>(), (uint32_t)ctx->dp_ids.size(),
-                                          ctx->dp_stats.as<double>(), s));
+    HIP_TRY(ctx, launch_reduce_f64_gather(outp[0], 1, ctx->items.index,
+                                          ctx->items.offsets, (uint32_t)ctx->dp_ids.size(),
+                                          (double *)ctx->dp_stats.view, s));
     ReduceSet set{};
     for (uint32_t o = 0; o < 3; ++o) {
       set.x[o] = outp[o];
@@ -1019,7 +1074,7 @@ mrip_status mrip_run_plan(mrip_ctx ctx, uint64_t seed, void *hip_stream) {
   uint8_t *done = nullptr;
   mrip_status st = done_flags(ctx, &done);
   if (st != MRIP_OK) return st;
-  st = run_plan_impl(ctx, seed, (hipStream_t)hip_stream, ctx->it_order.as<uint32_t>(), n_run,
+  st = run_plan_impl(ctx, seed, (hipStream_t)hip_stream, ctx->items.order, n_run,
                      n_long, ctx->plan_rpw, ctx->plan_wg, split, whole, done, true);
   if (st != MRIP_OK) return st;
   ctx->last = whole ? RUN_PLAN : RUN_PLAN_PARTIAL;
@@ -1114,9 +1169,7 @@ mrip_status mrip_plan_stats(mrip_ctx ctx, uint32_t dp, double confidence, mrip_s
   if (it == ctx->dp_ids.end() || *it != dp) return inval(ctx, "no such design point");
   const size_t g = (size_t)(it - ctx->dp_ids.begin());
   HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
-  double nmv[3];
-  HIP_TRY(ctx, hipMemcpy(nmv, ctx->dp_stats.as<double>() + 3 * g, sizeof(nmv), hipMemcpyDeviceToHost));
-  mrip_status st = finish_stats(nmv, confidence, out);
+  mrip_status st = finish_stats((const double *)ctx->dp_stats.p + 3 * g, confidence, out);
   if (st == MRIP_E_TOO_FEW) ctx->err = "fewer than two replications";
   return st;
 }
@@ -1129,7 +1182,7 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
   if (ctx->mapping != MRIP_MAP_WAVE)
     return (ctx->err = "the autotuner times the WAVE plan shapes"), MRIP_E_UNSUPPORTED;
   hipStream_t s = (hipStream_t)hip_stream;
-  const uint32_t *order = ctx->it_order.as<uint32_t>();
+  const uint32_t *order = ctx->items.order;
   uint64_t n = ctx->n_items;
   DevBuf sub;
   if (calib_items > 0 && calib_items < ctx->n_items) {

@@ -41,18 +41,74 @@ struct DevBuf {
   }
 };
 
+// Pinned host memory that kernels write and copies read: `p` on the host,
+// `view` on the device.
+struct PinnedBuf {
+  void *p = nullptr, *view = nullptr;
+  size_t bytes = 0;
+  PinnedBuf() = default;
+  PinnedBuf(const PinnedBuf &) = delete;
+  PinnedBuf &operator=(const PinnedBuf &) = delete;
+  ~PinnedBuf() {
+    if (p) (void)hipHostFree(p);
+  }
+  hipError_t ensure(size_t n) {
+    if (n <= bytes && p) return hipSuccess;
+    if (p) {
+      // work queued earlier may still use the old buffer
+      const hipError_t e = hipDeviceSynchronize();
+      if (e != hipSuccess) return e;
+      (void)hipHostFree(p);
+      p = view = nullptr;
+      bytes = 0;
+    }
+    hipError_t e = hipHostMalloc(&p, n ? n : 1, hipHostMallocMapped);
+    if (e != hipSuccess) {
+      p = nullptr;
+      return e;
+    }
+    bytes = n;
+    return hipHostGetDevicePointer(&view, p, 0);
+  }
+};
+
+struct TimingEvent {
+  hipEvent_t ev = nullptr;
+  TimingEvent() = default;
+  TimingEvent(const TimingEvent &) = delete;
+  TimingEvent &operator=(const TimingEvent &) = delete;
+  ~TimingEvent() {
+    if (ev) (void)hipEventDestroy(ev);
+  }
+  hipError_t record(hipStream_t s) {
+    if (!ev) {
+      const hipError_t e = hipEventCreate(&ev);
+      if (e != hipSuccess) return e;
+    }
+    return hipEventRecord(ev, s);
+  }
+};
+
 // RUN_PLAN_PARTIAL: a plan run stopped by the item limit; its outputs and
 // done flags are readable, its statistics were not computed.
 enum RunKind { RUN_NONE = 0, RUN_UNIFORM = 1, RUN_PLAN = 2, RUN_PLAN_PARTIAL = 3 };
 
 // An item table on the device (structure of arrays) with its queue order
-// (longest first) and its grouping by design point (index + offsets).
+// (longest first) and its grouping by design point (index + offsets), and
+// the item's bin of rho where one is asked for. The arrays lie in one block,
+// built in pinned memory and sent in one copy on the call's stream.
 struct ItemBufs {
-  DevBuf dp, rep, n, lambda, mu, order, index, offsets;
+  DevBuf table;
+  PinnedBuf staging;
+  bool in_flight = false;  // the copy may still read `staging`
+  const uint64_t *n = nullptr, *offsets = nullptr;
+  const uint32_t *dp = nullptr, *rep = nullptr, *order = nullptr, *index = nullptr, *bin = nullptr;
+  const float *lambda = nullptr, *mu = nullptr;
   uint64_t count = 0, max_customers = 0, n_long = 0, total_customers = 0;
   std::vector<uint32_t> dp_ids;          // distinct design points, ascending
   std::vector<uint64_t> group_offsets;   // host copy of offsets
   std::vector<uint32_t> index_host;      // host copy of index
+  std::vector<uint32_t> order_host;      // host copy of order
 };
 
 // State of the learned control variate.
@@ -79,14 +135,16 @@ struct CvState {
   // of row j; network outputs g_train in item order after training
   ItemBufs train_items;
   DevBuf y_train, x_train, c_train, z_train, t_train, zt_train, g_rows, g_train, group;
-  DevBuf xn, yn, zn, scratch_t, scratch_i;
+  DevBuf xn, yn, zn, scratch_t, scratch_i, red_y;
   std::vector<uint32_t> perm;
   uint64_t n_fit = 0;
   // application: per item Y, features, controls, network outputs, the
   // network's control h, residual d = Y - coef . (h, z_pre) and the item's
   // bin of rho
   ItemBufs items;
-  DevBuf y, x, c, g, h, d, bin_item, red_y, red_d;
+  DevBuf y, x, c, g, h, d;
+  PinnedBuf red;  // (n, mean, var) of Y, then of d, per design point
+  TimingEvent ev[3];
   // per design point of the last apply: cv = (n, mean, var of the
   // estimator, dof, coefficient of h used), plain = (n, mean, var of Y)
   std::vector<uint32_t> dp_ids;
@@ -101,6 +159,10 @@ struct CvState {
 // at once. Splitting shortens a plan only while its longest item sets the
 // makespan; beyond that its corrections and barriers cost time.
 uint32_t plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total);
+
+// Check n items (1 <= n < 2^32) and enqueue their upload into b on s.
+mrip_status upload_items(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n, uint64_t K,
+                         uint64_t long_min, bool bins, ItemBufs &b, hipStream_t s);
 
 }  // namespace mrip
 
@@ -204,8 +266,9 @@ struct mrip_ctx_s {
   mrip::DevBuf resume_order;            // the queue of a resumed plan
   mrip::DevBuf item_done;               // per item: 1 once the last plan run wrote its outputs
   uint64_t plan_limit = 0;              // plan runs stop after this many items (0 = none)
-  mrip::DevBuf it_dp, it_rep, it_n, it_lambda, it_mu, it_order, queue, dp_index, dp_offsets,
-      dp_stats;
+  mrip::ItemBufs items;
+  mrip::DevBuf queue;
+  mrip::PinnedBuf dp_stats;  // (n, mean, var) per design point, written by the reduction
   std::vector<uint32_t> dp_ids;
 
   // learned control variate

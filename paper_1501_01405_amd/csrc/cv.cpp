@@ -59,72 +59,12 @@ AdamArgs adam_args(float lr, float b1, float b2, float eps, uint64_t step) {
   return a;
 }
 
-// Upload items (SoA), their longest-first order (and how many of its first
-// items are long) and their dp grouping.
-mrip_status upload_items(mrip_ctx c, const mrip_plan_item *items, uint64_t n, uint64_t K,
-                         uint64_t long_min, ItemBufs &b) {
-  if (!items || n == 0) return bad(c, "empty item table");
-  if (n > 0xFFFFFFFFull) return bad(c, "item table too large");
-  std::vector<uint32_t> dp(n), rep(n), order(n), index(n);
-  std::vector<uint64_t> cust(n);
-  std::vector<float> lam(n), mu(n);
-  for (uint64_t i = 0; i < n; ++i) {
-    const mrip_plan_item &it = items[i];
-    if (it.customers < 1 || it.customers >= (1ull << 33)) return bad(c, "item customers out of range");
-    if (it.customers < K) return bad(c, "item shorter than the feature prefix");
-    if (!(it.lambda > 0.0f) || !(it.mu > 0.0f) || !std::isfinite(it.lambda) || !std::isfinite(it.mu))
-      return bad(c, "item rates must be finite and > 0");
-    dp[i] = it.dp;
-    rep[i] = it.rep;
-    cust[i] = it.customers;
-    lam[i] = it.lambda;
-    mu[i] = it.mu;
-    order[i] = index[i] = (uint32_t)i;
-  }
-  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b2) { return cust[a] > cust[b2]; });
-  std::stable_sort(index.begin(), index.end(), [&](uint32_t a, uint32_t b2) { return dp[a] < dp[b2]; });
-  b.dp_ids.clear();
-  b.group_offsets.clear();
-  for (uint64_t j = 0; j < n; ++j) {
-    if (j == 0 || dp[index[j]] != dp[index[j - 1]]) {
-      b.group_offsets.push_back(j);
-      b.dp_ids.push_back(dp[index[j]]);
-    }
-  }
-  b.group_offsets.push_back(n);
-  b.index_host = index;
-  b.max_customers = *std::max_element(cust.begin(), cust.end());
-  b.total_customers = 0;
-  for (uint64_t i = 0; i < n; ++i) b.total_customers += cust[i];
-  b.n_long = 0;  // items of at least long_min customers: a prefix of the order
-  while (b.n_long < n && cust[order[b.n_long]] >= long_min) ++b.n_long;
-  CV_TRY(c, b.dp.ensure(4 * n));
-  CV_TRY(c, b.rep.ensure(4 * n));
-  CV_TRY(c, b.n.ensure(8 * n));
-  CV_TRY(c, b.lambda.ensure(4 * n));
-  CV_TRY(c, b.mu.ensure(4 * n));
-  CV_TRY(c, b.order.ensure(4 * n));
-  CV_TRY(c, b.index.ensure(4 * n));
-  CV_TRY(c, b.offsets.ensure(8 * b.group_offsets.size()));
-  CV_TRY(c, hipMemcpy(b.dp.p, dp.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.rep.p, rep.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.n.p, cust.data(), 8 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.lambda.p, lam.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.mu.p, mu.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.order.p, order.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.index.p, index.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(c, hipMemcpy(b.offsets.p, b.group_offsets.data(), 8 * b.group_offsets.size(),
-                      hipMemcpyHostToDevice));
-  b.count = n;
-  return MRIP_OK;
-}
-
 // Run an item table through the persistent M/M/1 kernels (the plan's form:
 // items of at least long_min customers split over plan_split_for wavefronts)
 // with feature capture over the first K customers and the controls after
-// them; `ms` (nullable) gets the kernel time.
+// them; `ev` (nullable): two events recorded around the kernel.
 mrip_status run_items(mrip_ctx c, ItemBufs &b, uint64_t seed, uint64_t K, float *mean_w,
-                      float *feat, float *ctl, hipStream_t s, float *ms) {
+                      float *feat, float *ctl, hipStream_t s, TimingEvent *ev) {
   CvState &cv = c->cv;
   CV_TRY(c, cv.queue.ensure(256));
   CV_TRY(c, cv.scratch_t.ensure(4 * b.count));
@@ -132,37 +72,26 @@ mrip_status run_items(mrip_ctx c, ItemBufs &b, uint64_t seed, uint64_t K, float 
   Mm1Args a{};
   a.seed = seed;
   a.feature_prefix = K;
-  a.items.dp = b.dp.as<uint32_t>();
-  a.items.rep = b.rep.as<uint32_t>();
-  a.items.customers = b.n.as<uint64_t>();
-  a.items.lambda = b.lambda.as<float>();
-  a.items.mu = b.mu.as<float>();
-  a.items.order = b.order.as<uint32_t>();
+  a.items.dp = b.dp;
+  a.items.rep = b.rep;
+  a.items.customers = b.n;
+  a.items.lambda = b.lambda;
+  a.items.mu = b.mu;
+  a.items.order = b.order;
   a.queue_head = cv.queue.as<uint32_t>();
   a.mean_w = mean_w;
   a.mean_t = cv.scratch_t.as<float>();
   a.mean_i = cv.scratch_i.as<float>();
   a.features = feat;
   a.controls = ctl;
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  if (ms) {
-    CV_TRY(c, hipEventCreate(&e0));
-    CV_TRY(c, hipEventCreate(&e1));
-  }
   CV_TRY(c, launch_zero_u32(a.queue_head, 2, s));
-  if (ms) CV_TRY(c, hipEventRecord(e0, s));
+  if (ev) CV_TRY(c, ev[0].record(s));
   const uint32_t split = plan_split_for(c, b.max_customers, b.total_customers);
   if (split > 1 && b.n_long > 0)
     CV_TRY(c, launch_mm1_plan_split(a, b.count, b.n_long, split, c->plan_rpw, s));
   else
     CV_TRY(c, launch_mm1_plan(a, b.count, c->plan_rpw, c->plan_wg, s));
-  if (ms) {
-    CV_TRY(c, hipEventRecord(e1, s));
-    CV_TRY(c, hipEventSynchronize(e1));
-    CV_TRY(c, hipEventElapsedTime(ms, e0, e1));
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-  }
+  if (ev) CV_TRY(c, ev[1].record(s));
   return MRIP_OK;
 }
 
@@ -285,7 +214,9 @@ mrip_status mrip_cv_train(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n,
   cv.trained = false;
   cv.applied = false;
 
-  mrip_status st = upload_items(ctx, items, n, K, ctx->long_min, cv.train_items);
+  if (!items || n == 0) return bad(ctx, "empty item table");
+  if (n > 0xFFFFFFFFull) return bad(ctx, "item table too large");
+  mrip_status st = upload_items(ctx, items, n, K, ctx->long_min, false, cv.train_items, s);
   if (st != MRIP_OK) return st;
   ItemBufs &tb = cv.train_items;
   const size_t G = tb.dp_ids.size();
@@ -326,10 +257,9 @@ mrip_status mrip_cv_train(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n,
     for (uint64_t j = tb.group_offsets[g]; j < tb.group_offsets[g + 1]; ++j) group[index[j]] = (uint32_t)g;
   CV_TRY(ctx, cv.group.ensure(4 * n));
   CV_TRY(ctx, hipMemcpy(cv.group.p, group.data(), 4 * n, hipMemcpyHostToDevice));
-  CV_TRY(ctx, launch_reduce_f64_gather(cv.y_train.p, 1, tb.index.as<uint32_t>(),
-                                       tb.offsets.as<uint64_t>(), (uint32_t)G,
+  CV_TRY(ctx, launch_reduce_f64_gather(cv.y_train.p, 1, tb.index, tb.offsets, (uint32_t)G,
                                        cv.red_y.as<double>(), s));
-  CV_TRY(ctx, launch_multipliers(cv.c_train.as<float>(), tb.n.as<uint64_t>(), tb.mu.as<float>(), n,
+  CV_TRY(ctx, launch_multipliers(cv.c_train.as<float>(), tb.n, tb.mu, n,
                                  cv.z_train.as<float>(), cv.y_train.as<float>(),
                                  cv.group.as<uint32_t>(), cv.red_y.as<double>(),
                                  cv.t_train.as<float>(), cv.zt_train.as<float>(), s));
@@ -340,6 +270,7 @@ mrip_status mrip_cv_train(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n,
   double cs[20];
   CV_TRY(ctx, hipMemcpyAsync(cs, cv.colstats.p, sizeof(cs), hipMemcpyDeviceToHost, s));
   CV_TRY(ctx, hipStreamSynchronize(s));
+  tb.in_flight = false;
   cv.mean.assign(10, 0.f);
   cv.std_.assign(10, 1.f);
   float host_norm[20];
@@ -608,7 +539,9 @@ mrip_status mrip_cv_apply(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n,
   const uint64_t K = ctx->mm1.feature_prefix;
   hipStream_t s = (hipStream_t)hip_stream;
   cv.applied = false;
-  mrip_status st = upload_items(ctx, items, n, K, ctx->long_min, cv.items);
+  if (!items || n == 0) return bad(ctx, "empty item table");
+  if (n > 0xFFFFFFFFull) return bad(ctx, "item table too large");
+  mrip_status st = upload_items(ctx, items, n, K, ctx->long_min, true, cv.items, s);
   if (st != MRIP_OK) return st;
   const size_t G = cv.items.dp_ids.size();
   for (size_t g = 0; g < G; ++g)
@@ -620,50 +553,37 @@ mrip_status mrip_cv_apply(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n,
   CV_TRY(ctx, cv.g.ensure(16 * n));
   CV_TRY(ctx, cv.h.ensure(4 * n));
   CV_TRY(ctx, cv.d.ensure(4 * n));
-  CV_TRY(ctx, cv.bin_item.ensure(4 * n));
-  CV_TRY(ctx, cv.red_y.ensure(sizeof(double) * 3 * G));
-  CV_TRY(ctx, cv.red_d.ensure(sizeof(double) * 3 * G));
-  // each item's row of the coefficient table: its design point's bin of rho
-  std::vector<uint32_t> bins(n);
-  for (uint64_t i = 0; i < n; ++i) bins[i] = (uint32_t)cv.bin_of(items[i].lambda / items[i].mu);
-  CV_TRY(ctx, hipMemcpy(cv.bin_item.p, bins.data(), 4 * n, hipMemcpyHostToDevice));
+  CV_TRY(ctx, cv.red.ensure(sizeof(double) * 6 * G));
 
   st = run_items(ctx, cv.items, seed, K, cv.y.as<float>(), cv.x.as<float>(), cv.c.as<float>(), s,
-                 &cv.run_ms);
+                 cv.ev);
   if (st != MRIP_OK) return st;
 
   // inference in one kernel: g = net((x - mean) / std), the multipliers, h
   // and the residual Y - coef . (h, z_pre); then per design point (n, mean,
   // var) of Y and of the residual in one reduction launch
-  hipEvent_t e0, e1;
-  CV_TRY(ctx, hipEventCreate(&e0));
-  CV_TRY(ctx, hipEventCreate(&e1));
   CvInferArgs ia{};
   ia.mean = cv.norm.as<float>();
   ia.inv_std = cv.norm.as<float>() + 10;
   ia.ctl = cv.c.as<float>();
-  ia.customers = cv.items.n.as<uint64_t>();
-  ia.mu = cv.items.mu.as<float>();
-  ia.bin = cv.bin_item.as<uint32_t>();
+  ia.customers = cv.items.n;
+  ia.mu = cv.items.mu;
+  ia.bin = cv.items.bin;
   ia.coef = cv.coef_d.as<float>();
   ia.y = cv.y.as<float>();
   ia.g = cv.g.as<float>();
   ia.h = cv.h.as<float>();
   ia.d = cv.d.as<float>();
-  CV_TRY(ctx, hipEventRecord(e0, s));
   CV_TRY(ctx, launch_cv_infer(cv.theta.as<float>(), cv.x.as<float>(), n, ia, s));
-  CV_TRY(ctx, launch_reduce_f64_gather2(cv.y.as<float>(), cv.d.as<float>(),
-                                        cv.items.index.as<uint32_t>(),
-                                        cv.items.offsets.as<uint64_t>(), (uint32_t)G,
-                                        cv.red_y.as<double>(), cv.red_d.as<double>(), s));
-  CV_TRY(ctx, hipEventRecord(e1, s));
-  std::vector<double> ry(3 * G), rd(3 * G);
-  CV_TRY(ctx, hipMemcpyAsync(ry.data(), cv.red_y.p, 24 * G, hipMemcpyDeviceToHost, s));
-  CV_TRY(ctx, hipMemcpyAsync(rd.data(), cv.red_d.p, 24 * G, hipMemcpyDeviceToHost, s));
+  CV_TRY(ctx, launch_reduce_f64_gather2(cv.y.as<float>(), cv.d.as<float>(), cv.items.index,
+                                        cv.items.offsets, (uint32_t)G, (double *)cv.red.view,
+                                        (double *)cv.red.view + 3 * G, s));
+  CV_TRY(ctx, cv.ev[2].record(s));
   CV_TRY(ctx, hipStreamSynchronize(s));
-  CV_TRY(ctx, hipEventElapsedTime(&cv.infer_ms, e0, e1));
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  cv.items.in_flight = false;
+  CV_TRY(ctx, hipEventElapsedTime(&cv.run_ms, cv.ev[0].ev, cv.ev[1].ev));
+  CV_TRY(ctx, hipEventElapsedTime(&cv.infer_ms, cv.ev[1].ev, cv.ev[2].ev));
+  const double *ry = (const double *)cv.red.p, *rd = ry + 3 * G;
 
   cv.dp_ids = cv.items.dp_ids;
   cv.cv.assign(5 * G, 0.0);
@@ -710,7 +630,8 @@ mrip_status mrip_cv_stats(mrip_ctx ctx, uint32_t dp, double confidence, mrip_sta
     plain->mean = cv.plain[3 * g + 1];
     plain->var = cv.plain[3 * g + 2];
     plain->confidence = confidence;
-    plain->t_quantile = mrip::t_quantile(p, n - 1.0);
+    plain->t_quantile =
+        cvs && cv.cv[5 * g + 3] == n - 1.0 ? cvs->t_quantile : mrip::t_quantile(p, n - 1.0);
     plain->half_width = plain->t_quantile * std::sqrt(plain->var / n);
   }
   return MRIP_OK;

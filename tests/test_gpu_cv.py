@@ -218,3 +218,35 @@ def test_apply_rejects_a_design_point_with_one_replication(gpu):
         mrip.mrip_cv_apply(ctx.ctx, items[:3], seed=1, stream=mrip.current_stream())
     with pytest.raises(mrip.MripError):  # outputs of the training run: none behind this model
         mrip.mrip_cv_outputs(ctx.ctx, 5, 4)
+
+
+@pytest.mark.parametrize("n_dp,reps", [(1, 2), (3, 7), (33, 31)])
+def test_apply_takes_items_in_any_order(gpu, n_dp, reps):
+    # tables in the queue's and the design points' order go up unsorted,
+    # others are sorted first, and a second, larger table regrows the buffers:
+    # per item the same bits, per design point sums in another order
+    announce("cv item order", n_dp, reps)
+    theta, mean, std = _model()
+    rng = np.random.default_rng(n_dp)
+    coef = rng.normal(size=(BINS, NC)).astype(np.float32)
+    ctx = _ctx(2000)
+    mrip.mrip_cv_set_model(ctx.ctx, theta, mean, std, coef, 0.5, 0.95)
+    items = inputs.uniform_items(n_dp, reps, 2000, rng.uniform(0.4, 0.97, n_dp))
+    longest_first = np.sort(rng.integers(1500, 9000, n_dp))[::-1]
+    shuffled_n = rng.permutation(longest_first)
+    for customers in (np.full(n_dp, 2000), longest_first, shuffled_n):
+        items["customers"] = np.repeat(customers, reps)
+        results = []
+        for perm in (np.arange(n_dp * reps), rng.permutation(n_dp * reps)):
+            mrip.mrip_cv_apply(ctx.ctx, items[perm], seed=9)
+            out = [np.empty(n_dp * reps, np.float32) for _ in range(2)]
+            for w in range(2):
+                out[w][perm] = mrip.mrip_cv_outputs(ctx.ctx, w, n_dp * reps)
+            results.append((out, [mrip.mrip_cv_stats(ctx.ctx, d) for d in range(n_dp)]))
+        (a, sa), (b, sb) = results
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        for x, y in zip(sa, sb):
+            for k in range(2):
+                assert x[k]["n"] == y[k]["n"] == reps
+                for f in ("mean", "var", "half_width"):  # fp64 sums of at most 31 terms
+                    assert x[k][f] == pytest.approx(y[k][f], rel=1e-11)
