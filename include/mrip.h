@@ -456,10 +456,9 @@ MRIP_API mrip_status mrip_mlp_grad(const float *theta_dev, const float *x_dev, c
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * gradient as mrip_mlp_grad, bit for bit, with its per-64-sample partial
- * rows and its bf16 image of the weights in a fixed device array of the
- * library (MRIP_MLP_GRAD_NOALLOC_MAX / 64 rows of 18440 floats and 82960
- * bytes, about 4.8 MB, held by each GPU the library runs on until the
- * process ends) instead of an allocation. Calls no
+ * rows in a fixed device array of the library (MRIP_MLP_GRAD_NOALLOC_MAX / 64
+ * rows of 18440 floats, 4.7 MB, held by each GPU the library runs on until
+ * the process ends) instead of an allocation. Calls no
  * allocating routine and does not synchronise. n <= MRIP_MLP_GRAD_NOALLOC_MAX
  * (MRIP_E_INVAL beyond it); the other arguments as for mrip_mlp_grad. Every
  * call on one GPU shares that array: calls that overlap on one GPU (other

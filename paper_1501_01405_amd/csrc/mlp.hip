@@ -4,8 +4,8 @@
 // outputs are the coefficients of four zero-mean controls; training fits
 // sum_k g_k(x) z_k to a target with per-sample multipliers z.
 //
-// Layout. A workgroup of 4 wavefronts takes 64 samples, 16 per wave. Every
-// layer is computed transposed, activations as [hidden][sample]:
+// Layout. A workgroup takes 64 samples, 16 per wave (forward) or per pair of
+// waves (gradient). Every layer is computed transposed, activations as [hidden][sample]:
 //     Z1^T = W1 . X^T,  Z2^T = W2 . H1^T,  dH1^T = W2^T . dZ2^T
 // so a layer's output tile (lane l holds rows 4(l/16)+i, column l%16) is
 // already the next product's B operand up to a permutation of the
@@ -46,30 +46,26 @@ struct FwdLds {
   __bf16 w1[H][32 + 8];  // W1[h][f], f >= 10 zero
   float b1[H], b2[H], w3[DOUT][H], b3[DOUT];  // w3 bf16-rounded
 };
-// The gradient kernel's weights: FwdLds and W2^T, all in bf16 where a
-// product reads them. Kept in global memory in exactly this layout (the
-// training's Adam step rewrites it with the weights) and staged into LDS by
-// a flat 16-byte copy.
-struct MlpImage {
-  FwdLds f;
-  __bf16 w2t[H][H + 8];  // W2^T[h1][h2]
-};
-static_assert(sizeof(FwdLds) % 16 == 0 && sizeof(MlpImage) == MLP_IMAGE_BYTES,
-              "16-byte copies of the image");
 static_assert(offsetof(FwdLds, w3) == offsetof(FwdLds, b2) + 4 * H &&
                   offsetof(FwdLds, b3) == offsetof(FwdLds, w3) + 4 * DOUT * H,
               "b2, W3, b3 contiguous as in the flat parameters");
 
 struct BwdLds {
-  MlpImage m;            // m.f.w2 is reused for H2^T[h2][s] once the forward pass is done
+  FwdLds f;              // f.w2 is reused for H2^T[h2][s] once the forward pass is done
+  __bf16 w2t[H][H + 8];  // W2^T[h1][h2]
   __bf16 h1t[H][SP];     // H1^T[h1][s]
   __bf16 dz2t[H][SP];    // dZ2^T[h2][s]
   __bf16 dz1t[H][SP];    // dZ1^T[h1][s]
   __bf16 xt[16][SP];     // X^T[f][s], f < 16
   __bf16 dyt[DOUT][SP];  // dY^T[k][s]
-  float red[2][4][H];    // per-wave sums of db1, db2
-  float red_s[1 + DOUT][4];  // per-wave sums of loss and db3[k]
+  float red[2][4][H];    // sums over 16 samples of db1, db2; before them, the
+                         // first half of the outputs' sums, handed to the second
+  float red_s[1 + DOUT][4];  // sums over 16 samples of loss and db3[k]
+  float4 dy[TS];             // the output gradient per sample
+  bf16x8 dzb[8][2][64];      // dZ2 as the products read it: per wave, its two steps
 };
+static_assert(sizeof(BwdLds) <= 160 * 1024, "one workgroup's LDS");
+static_assert(sizeof(float4) * 4 * 64 <= sizeof(float) * 2 * 4 * H, "the handed sums fit");
 static_assert(sizeof(__bf16) * H * SP <= sizeof(__bf16) * H * (H + 8), "H2^T fits in W2's place");
 
 __device__ __forceinline__ __bf16 bf(float v) { return (__bf16)v; }
@@ -87,57 +83,59 @@ __device__ __forceinline__ bf16x8 load_perm(const __bf16 *row, int j, int g) {
   return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
-// The image value of flat parameter p (bf16 where a product reads it).
-__device__ __forceinline__ void image_put(MlpImage &m, uint32_t p, float v) {
-  if (p < (uint32_t)MLP_OFF_B1) {
-    m.f.w1[p / DIN][p % DIN] = bf(v);
-  } else if (p < (uint32_t)MLP_OFF_W2) {
-    m.f.b1[p - MLP_OFF_B1] = v;
-  } else if (p < (uint32_t)MLP_OFF_B2) {
-    const uint32_t q = p - MLP_OFF_W2, r = q / H, c = q % H;
-    m.f.w2[r][c] = bf(v);
-    m.w2t[c][r] = bf(v);
-  } else if (p < (uint32_t)MLP_OFF_W3) {
-    m.f.b2[p - MLP_OFF_B2] = v;
-  } else if (p < (uint32_t)MLP_OFF_B3) {
-    const uint32_t q = p - MLP_OFF_W3;
-    m.f.w3[q / H][q % H] = bfr(v);
-  } else {
-    m.f.b3[p - MLP_OFF_B3] = v;
-  }
-}
-
-// Stage FwdLds from the flat fp32 parameters (16-byte aligned), 256
-// threads: every thread issues all of its 16-byte loads before its first
-// store.
-__device__ __forceinline__ void stage_theta(const float *__restrict__ theta, FwdLds &L) {
-  const int tid = threadIdx.x;
+// Stage FwdLds from the flat fp32 parameters (16-byte aligned), and with
+// `w2t` W2 transposed as well, T threads: every thread issues all of its
+// 16-byte loads before its first store. W2 goes in 4 x 4 blocks (a thread
+// has four rows of one), 8 x 8 blocks a wave: whole 128-byte lines on the
+// way in, and every bank once per half-wave in the stores of either copy.
+template <int T>
+__device__ __forceinline__ void stage_theta(const float *__restrict__ theta, FwdLds &L,
+                                            __bf16 (*w2t)[H + 8] = nullptr) {
+  const int tid = threadIdx.x, lane = tid & 63;
   const float4 *t4 = reinterpret_cast<const float4 *>(theta);
-  constexpr int W2V = H * H / 4 / 256;  // 16 vectors of W2 per thread
-  constexpr int W1V = H * DIN / 4;      // 320 vectors of W1
+  constexpr int BLOCKS = H * H / 16 / T;  // 4 x 4 blocks of W2 per thread
+  constexpr int W1V = H * DIN / 4;        // 320 vectors of W1
   constexpr int TAILV = (H + DOUT * H + DOUT) / 4;  // b2, W3, b3: 161 vectors
   static_assert(MLP_OFF_W2 % 4 == 0 && MLP_OFF_B1 % 4 == 0 && MLP_OFF_B2 % 4 == 0, "float4 runs");
-  float4 w2v[W2V];
+  // block k of this thread: rows from r0(k), columns from c0(k)
+  const auto r0 = [&](int k) { return 32 * (((tid >> 6) + T / 64 * k) >> 2) + 4 * (lane >> 3); };
+  const auto c0 = [&](int k) { return 32 * (((tid >> 6) + T / 64 * k) & 3) + 4 * (lane & 7); };
+  float4 w2v[BLOCKS][4];
 #pragma unroll
-  for (int k = 0; k < W2V; ++k) w2v[k] = t4[MLP_OFF_W2 / 4 + tid + 256 * k];
+  for (int k = 0; k < BLOCKS; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w2v[k][i] = t4[(MLP_OFF_W2 + (r0(k) + i) * H + c0(k)) / 4];
   const float4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  const float4 w1a = t4[MLP_OFF_W1 / 4 + tid];
-  const float4 w1b = tid + 256 < W1V ? t4[MLP_OFF_W1 / 4 + 256 + tid] : zero4;
+  const float4 w1a = tid < W1V ? t4[MLP_OFF_W1 / 4 + tid] : zero4;
+  const float4 w1b = tid + T < W1V ? t4[MLP_OFF_W1 / 4 + T + tid] : zero4;
   const float4 b1v = tid < H / 4 ? t4[MLP_OFF_B1 / 4 + tid] : zero4;
   const float4 tv = tid < TAILV ? t4[MLP_OFF_B2 / 4 + tid] : zero4;
 #pragma unroll
-  for (int k = 0; k < W2V; ++k) {
-    const int e = tid + 256 * k, r = e >> 5, c0 = 4 * (e & 31);
-    *(bf16x4 *)&L.w2[r][c0] = bf16x4{bf(w2v[k].x), bf(w2v[k].y), bf(w2v[k].z), bf(w2v[k].w)};
+  for (int k = 0; k < BLOCKS; ++k) {
+    float v[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i][0] = w2v[k][i].x;
+      v[i][1] = w2v[k][i].y;
+      v[i][2] = w2v[k][i].z;
+      v[i][3] = w2v[k][i].w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      *(bf16x4 *)&L.w2[r0(k) + i][c0(k)] = bf16x4{bf(v[i][0]), bf(v[i][1]), bf(v[i][2]), bf(v[i][3])};
+      if (w2t)
+        *(bf16x4 *)&w2t[c0(k) + i][r0(k)] =
+            bf16x4{bf(v[0][i]), bf(v[1][i]), bf(v[2][i]), bf(v[3][i])};
+    }
   }
   auto put_w1 = [&](int q, float4 v) {
     const float f4[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) L.w1[(q + i) / DIN][(q + i) % DIN] = bf(f4[i]);
   };
-  put_w1(4 * tid, w1a);
-  if (tid + 256 < W1V) put_w1(4 * (256 + tid), w1b);
-  {  // zero columns 10..31 of row tid/2: 10..15 by even threads, 16..31 by odd ones
+  if (tid < W1V) put_w1(4 * tid, w1a);
+  if (tid + T < W1V) put_w1(4 * (T + tid), w1b);
+  if (tid < 2 * H) {  // zero columns 10..31 of row tid/2: 10..15 by even threads, 16..31 by odd ones
     const int r = tid >> 1;
     if (tid & 1) {
       *(uint4 *)&L.w1[r][16] = uint4{0u, 0u, 0u, 0u};
@@ -157,27 +155,6 @@ __device__ __forceinline__ void stage_theta(const float *__restrict__ theta, Fwd
       v.w = bfr(v.w);
     }
     reinterpret_cast<float4 *>(reinterpret_cast<char *>(&L) + offsetof(FwdLds, b2))[tid] = v;
-  }
-}
-
-// Flat copy of BYTES (a multiple of 16) from global memory into LDS, 256
-// threads, all loads of a thread issued before its first store.
-template <int BYTES>
-__device__ __forceinline__ void copy_to_lds(const void *__restrict__ src, void *dst) {
-  constexpr int V = BYTES / 16, PER = (V + 255) / 256;
-  const int tid = threadIdx.x;
-  const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
-  uint4 *d4 = reinterpret_cast<uint4 *>(dst);
-  uint4 v[PER];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = tid + 256 * k;
-    v[k] = e < V ? s4[e] : uint4{0u, 0u, 0u, 0u};
-  }
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = tid + 256 * k;
-    if (e < V) d4[e] = v[k];
   }
 }
 
@@ -259,7 +236,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float *theta, co
   const uint64_t s = (uint64_t)blockIdx.x * TS + 16 * w + c;
   const bool valid = s < n;
   const bf16x8 xb = load_x(x, s, valid, g);
-  stage_theta(theta, L);
+  stage_theta<256>(theta, L);
   __syncthreads();
   float z1[8][4], z2[8][4];
   const Out4 yh = forward_wave(L, xb, z1, z2);
@@ -280,7 +257,7 @@ __global__ __launch_bounds__(256) void cv_infer_kernel(const float *theta, const
   const uint64_t s = (uint64_t)blockIdx.x * TS + 16 * w + c;
   const bool valid = s < n;
   const bf16x8 xb = load_x(x, s, valid, g, a.mean, a.inv_std);
-  stage_theta(theta, L);
+  stage_theta<256>(theta, L);
   __syncthreads();
   float z1[8][4], z2[8][4];
   const Out4 o = forward_wave(L, xb, z1, z2);
@@ -316,166 +293,248 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Units t and t + 1 of this lane's sample, written as one word per lane: with
+// its neighbour's pair an even lane writes unit t of both samples, an odd
+// one unit t + 1 of both (m: the sum's rows from unit t).
+__device__ __forceinline__ void put_pair(__bf16 (*m)[SP], int sample, float v0, float v1) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bool odd = threadIdx.x & 1;
+  const uint32_t own = __builtin_bit_cast(uint32_t, bf16x2{bf(v0), bf(v1)});
+  const uint32_t other = __builtin_amdgcn_update_dpp(0, own, 0xB1, 0xF, 0xF, true);
+  // even: low halves (own, other); odd: high halves (other, own)
+  const uint32_t w = odd ? __builtin_amdgcn_perm(own, other, 0x07060302u)
+                         : __builtin_amdgcn_perm(other, own, 0x05040100u);
+  *(uint32_t *)&m[odd][sample & ~1] = w;
+}
+
 // Gradient of mean((sum_k g_k(x) z_k - y)^2) over n samples (z nullable:
 // z = e_0): one partial row per workgroup (MLP_PSTRIDE floats: the
 // MLP_NPARAMS gradients, then the loss sum). The output gradient
 // dy_k = 2 (pred - y) z_k / n is formed in fp32 and enters the products as
-// bf16. The weights come from their image (MlpImage).
-__global__ __launch_bounds__(256) void mlp_grad_kernel(const MlpImage *img, const float *x,
+// bf16.
+//
+// Latency bounds it: 1024 samples are 16 workgroups, each a chain of small
+// products. So two waves share 16 samples (half u of the second layer's
+// units and of the first layer's gradient each, two waves per SIMD), the
+// weights are staged from the parameters themselves, W2 in both
+// orientations (no launch that lays them out first), and the operands of
+// the weight gradients go to LDS two samples a word. Every sum is taken in
+// the order of the single wave that did this before (an output's sum over
+// the units passes from half 0 to half 1), so the bits are the same. 1024
+// samples: 12.2 us, 14.7 before, and no 2.4 us launch ahead of it.
+__global__ __launch_bounds__(512) void mlp_grad_kernel(const float *theta, const float *x,
                                                        const float *z, const float *y, uint64_t n,
                                                        float inv_n, float *partial) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   BwdLds &B = *reinterpret_cast<BwdLds *>(smem);
-  FwdLds &L = B.m.f;
+  FwdLds &L = B.f;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
-  const int sl = 16 * w + c;  // sample within the workgroup
+  const int q = w & 3, u = w >> 2;  // samples 16q.., half of the units; a SIMD has both halves
+  const int sl = 16 * q + c;        // sample within the workgroup
   const uint64_t s = (uint64_t)blockIdx.x * TS + sl;
   const bool valid = s < n;
   const uint64_t sc = valid ? s : 0;  // a readable row for the unconditional loads
   const bf16x8 xb = load_x(x, s, valid, g);
   const float4 zv = z ? *(const float4 *)(z + 4 * sc) : float4{1.0f, 0.0f, 0.0f, 0.0f};
   const float yv = y[sc];
-  copy_to_lds<sizeof(MlpImage)>(img, &B.m);
-  if (g < 2) {
+  stage_theta<512>(theta, L, B.w2t);
+  if (u == 0 && g < 2) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) B.xt[8 * g + i][sl] = xb[i];
   }
   __syncthreads();
 
-  float z1[8][4], z2[8][4];
-  const Out4 yh = forward_wave(L, xb, z1, z2);
-  const float zz[DOUT] = {zv.x, zv.y, zv.z, zv.w};
-  float pred = 0.0f;
+  // the first layer, all of it: the second one's operand
+  float z1[4][4];  // pre-activations of this half's units 16 (4u + t) + 4g + i
+  bf16x8 hb[4];
 #pragma unroll
-  for (int k = 0; k < DOUT; ++k) pred = fmaf(yh.v[k], zz[k], pred);
-  const float err = valid ? pred - yv : 0.0f;
-  const float e2 = 2.0f * err * inv_n;
-  float dy[DOUT], dyb[DOUT];
-#pragma unroll
-  for (int k = 0; k < DOUT; ++k) {
-    dy[k] = e2 * zz[k];
-    dyb[k] = bfr(dy[k]);
-  }
-
-  // the ReLU of the second layer
-  float dz2[8][4];
-#pragma unroll
-  for (int t = 0; t < 8; ++t)
+  for (int t = 0; t < 8; ++t) {
+    const bf16x8 a = *(const bf16x8 *)&L.w1[16 * t + c][8 * g];
+    const f32x4 acc = mfma(a, xb, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int h = 16 * t + 4 * g + i;
+      const float v = acc[i] + L.b1[16 * t + 4 * g + i];
+      hb[t >> 1][4 * (t & 1) + i] = bf(fmaxf(v, 0.0f));
+      if (t < 4) z1[t][i] = v;
+      else z1[t - 4][i] = u ? v : z1[t - 4][i];
+    }
+  }
+  // the second layer and the outputs' sums, this half
+  float z2[4][4], part[DOUT];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int h = 16 * (4 * u + t);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = mfma(load_perm(&L.w2[h + c][0], j, g), hb[j], acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z2[t][i] = acc[i] + L.b2[h + 4 * g + i];
+  }
+  const auto add_outputs = [&] {
+#pragma unroll
+    for (int k = 0; k < DOUT; ++k)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          part[k] = fmaf(L.w3[k][16 * (4 * u + t) + 4 * g + i], bfr(fmaxf(z2[t][i], 0.0f)), part[k]);
+  };
+  float4 *handed = reinterpret_cast<float4 *>(&B.red[0][0][0]) + 64 * q + lane;
+  if (u == 0) {
+#pragma unroll
+    for (int k = 0; k < DOUT; ++k) part[k] = 0.0f;
+    add_outputs();
+    *handed = float4{part[0], part[1], part[2], part[3]};
+  }
+  __syncthreads();  // every wave is past its reads of W2: H2^T takes its place
+  __bf16(*h2t)[SP] = reinterpret_cast<__bf16(*)[SP]>(&L.w2[0][0]);
+  if (u == 1) {
+    const float4 p0 = *handed;
+    part[0] = p0.x;
+    part[1] = p0.y;
+    part[2] = p0.z;
+    part[3] = p0.w;
+    add_outputs();
+    const float zz[DOUT] = {zv.x, zv.y, zv.z, zv.w};
+    float pred = 0.0f;
+#pragma unroll
+    for (int k = 0; k < DOUT; ++k) {
+      part[k] += __shfl_xor(part[k], 16, 64);
+      part[k] += __shfl_xor(part[k], 32, 64);
+      pred = fmaf(part[k] + L.b3[k], zz[k], pred);
+    }
+    const float err = valid ? pred - yv : 0.0f;
+    const float e2 = 2.0f * err * inv_n;
+    float dy[DOUT];
+#pragma unroll
+    for (int k = 0; k < DOUT; ++k) dy[k] = e2 * zz[k];
+    if (g == 0) {
+      B.dy[sl] = float4{dy[0], dy[1], dy[2], dy[3]};
+#pragma unroll
+      for (int k = 0; k < DOUT; ++k) B.dyt[k][sl] = bf(dy[k]);
+    }
+    // sums over the samples of the loss and db3
+    const float l2 = row16_sum(g == 0 ? err * err : 0.0f);
+    if (lane == 0) B.red_s[0][q] = l2;
+#pragma unroll
+    for (int k = 0; k < DOUT; ++k) {
+      const float d3 = row16_sum(g == 0 ? dy[k] : 0.0f);
+      if (lane == 0) B.red_s[1 + k][q] = d3;
+    }
+  }
+  // operands of the weight gradients ([unit][sample]): the layers' outputs
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      const int h = 16 * (4 * u + t) + 4 * g + i;
+      put_pair(&B.h1t[h], sl, fmaxf(z1[t][i], 0.0f), fmaxf(z1[t][i + 1], 0.0f));
+      put_pair(&h2t[h], sl, fmaxf(z2[t][i], 0.0f), fmaxf(z2[t][i + 1], 0.0f));
+    }
+  __syncthreads();
+
+  // the ReLU of the second layer, this half; the other half's from its wave
+  const float4 dyv = B.dy[sl];
+  const float dyb[DOUT] = {bfr(dyv.x), bfr(dyv.y), bfr(dyv.z), bfr(dyv.w)};
+  float dz2[4][4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int h = 16 * (4 * u + t) + 4 * g + i;
       float d = 0.0f;
 #pragma unroll
       for (int k = 0; k < DOUT; ++k) d = fmaf(L.w3[k][h], dyb[k], d);
       dz2[t][i] = z2[t][i] > 0.0f ? d : 0.0f;
     }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    bf16x8 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = bf(dz2[2 * j][i]);
+      v[4 + i] = bf(dz2[2 * j + 1][i]);
+    }
+    B.dzb[w][j][lane] = v;
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; i += 2)
+      put_pair(&B.dz2t[16 * (4 * u + t) + 4 * g + i], sl, dz2[t][i], dz2[t][i + 1]);
+  __syncthreads();
   // dH1^T = W2^T . dZ2^T, then the ReLU of the first layer
   bf16x8 db[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < 4; ++j) db[j] = B.dzb[q + 4 * (j >> 1)][j & 1][lane];
+  float dz1[4][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      db[j][i] = bf(dz2[2 * j][i]);
-      db[j][4 + i] = bf(dz2[2 * j + 1][i]);
-    }
-  float dz1[8][4];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
+  for (int t = 0; t < 4; ++t) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc = mfma(load_perm(&B.m.w2t[16 * t + c][0], j, g), db[j], acc);
+    for (int j = 0; j < 4; ++j)
+      acc = mfma(load_perm(&B.w2t[16 * (4 * u + t) + c][0], j, g), db[j], acc);
 #pragma unroll
     for (int i = 0; i < 4; ++i) dz1[t][i] = z1[t][i] > 0.0f ? acc[i] : 0.0f;
   }
-  __syncthreads();  // every wave is past its forward pass: W2's place takes H2^T
-
-  // stage the operands of the weight gradients ([unit][sample])
-  __bf16(*h2t)[SP] = reinterpret_cast<__bf16(*)[SP]>(&L.w2[0][0]);
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
+  for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int h = 16 * t + 4 * g + i;
-      B.h1t[h][sl] = bf(fmaxf(z1[t][i], 0.0f));
-      h2t[h][sl] = bf(fmaxf(z2[t][i], 0.0f));
-      B.dz2t[h][sl] = bf(dz2[t][i]);
-      B.dz1t[h][sl] = bf(dz1[t][i]);
-    }
-  if (g == 0) {
+    for (int i = 0; i < 4; i += 2)
+      put_pair(&B.dz1t[16 * (4 * u + t) + 4 * g + i], sl, dz1[t][i], dz1[t][i + 1]);
+  // sums over the 16 samples of db1, db2
 #pragma unroll
-    for (int k = 0; k < DOUT; ++k) B.dyt[k][sl] = bf(dy[k]);
-  }
-  // per-wave sums over samples of db1, db2, db3 and the loss
-#pragma unroll
-  for (int t = 0; t < 8; ++t)
+  for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int h = 16 * t + 4 * g + i;
+      const int h = 16 * (4 * u + t) + 4 * g + i;
       const float v1 = row16_sum(dz1[t][i]);
       const float v2 = row16_sum(dz2[t][i]);
       if (c == 0) {
-        B.red[0][w][h] = v1;
-        B.red[1][w][h] = v2;
+        B.red[0][q][h] = v1;
+        B.red[1][q][h] = v2;
       }
     }
-  {
-    const float l2 = row16_sum(g == 0 ? err * err : 0.0f);
-    if (lane == 0) B.red_s[0][w] = l2;
-#pragma unroll
-    for (int k = 0; k < DOUT; ++k) {
-      const float d3 = row16_sum(g == 0 ? dy[k] : 0.0f);
-      if (lane == 0) B.red_s[1 + k][w] = d3;
-    }
-  }
   __syncthreads();
 
   float *out = partial + (uint64_t)blockIdx.x * MLP_PSTRIDE;
-  // dW2[h2][h1] = sum_s dZ2^T[h2][s] H1^T[h1][s]: wave w owns h2 tiles 2w, 2w+1
+  // dW2[h2][h1] = sum_s dZ2^T[h2][s] H1^T[h1][s]: wave w owns h2 tile w
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int t2 = 2 * w + tt;
-#pragma unroll
-    for (int t1 = 0; t1 < 8; ++t1) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8 a = *(const bf16x8 *)&B.dz2t[16 * t2 + c][32 * j + 8 * g];
-        const bf16x8 b = *(const bf16x8 *)&B.h1t[16 * t1 + c][32 * j + 8 * g];
-        acc = mfma(a, b, acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out[MLP_OFF_W2 + (16 * t2 + 4 * g + i) * H + 16 * t1 + c] = acc[i];
-    }
-  }
-  // dW1[h1][f] = sum_s dZ1^T[h1][s] X^T[f][s] and
-  // dW3^T[h2][k] = sum_s H2^T[h2][s] dY^T[k][s]: wave w owns tiles 2w, 2w+1
-  const bf16x8 zero8 = {};
-#pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int t = 2 * w + tt;
-    f32x4 acc1 = {0.f, 0.f, 0.f, 0.f}, acc3 = {0.f, 0.f, 0.f, 0.f};
+  for (int t1 = 0; t1 < 8; ++t1) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const bf16x8 a1 = *(const bf16x8 *)&B.dz1t[16 * t + c][32 * j + 8 * g];
-      const bf16x8 b1 = *(const bf16x8 *)&B.xt[c][32 * j + 8 * g];
-      acc1 = mfma(a1, b1, acc1);
-      const bf16x8 a3 = *(const bf16x8 *)&h2t[16 * t + c][32 * j + 8 * g];
-      const bf16x8 b3 = c < DOUT ? *(const bf16x8 *)&B.dyt[c][32 * j + 8 * g] : zero8;
-      acc3 = mfma(a3, b3, acc3);
+      const bf16x8 a = *(const bf16x8 *)&B.dz2t[16 * w + c][32 * j + 8 * g];
+      const bf16x8 b = *(const bf16x8 *)&B.h1t[16 * t1 + c][32 * j + 8 * g];
+      acc = mfma(a, b, acc);
     }
-    if (c < DIN) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) out[MLP_OFF_W1 + (16 * t + 4 * g + i) * DIN + c] = acc1[i];
-    }
-    if (c < DOUT) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[MLP_OFF_W3 + c * H + 16 * t + 4 * g + i] = acc3[i];
-    }
+    for (int i = 0; i < 4; ++i) out[MLP_OFF_W2 + (16 * w + 4 * g + i) * H + 16 * t1 + c] = acc[i];
   }
-  // fixed-order sums of the four waves' rows: db1, db2
-  for (int e = tid; e < 2 * H; e += blockDim.x) {
-    const int r = e / H, h = e % H;
+  // dW1[h1][f] = sum_s dZ1^T[h1][s] X^T[f][s] and
+  // dW3^T[h2][k] = sum_s H2^T[h2][s] dY^T[k][s]: wave w owns tile w
+  const bf16x8 zero8 = {};
+  f32x4 acc1 = {0.f, 0.f, 0.f, 0.f}, acc3 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bf16x8 a1 = *(const bf16x8 *)&B.dz1t[16 * w + c][32 * j + 8 * g];
+    const bf16x8 b1 = *(const bf16x8 *)&B.xt[c][32 * j + 8 * g];
+    acc1 = mfma(a1, b1, acc1);
+    const bf16x8 a3 = *(const bf16x8 *)&h2t[16 * w + c][32 * j + 8 * g];
+    const bf16x8 b3 = c < DOUT ? *(const bf16x8 *)&B.dyt[c][32 * j + 8 * g] : zero8;
+    acc3 = mfma(a3, b3, acc3);
+  }
+  if (c < DIN) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[MLP_OFF_W1 + (16 * w + 4 * g + i) * DIN + c] = acc1[i];
+  }
+  if (c < DOUT) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[MLP_OFF_W3 + c * H + 16 * w + 4 * g + i] = acc3[i];
+  }
+  // fixed-order sums over the four groups of samples: db1, db2
+  if (tid < 2 * H) {
+    const int r = tid / H, h = tid % H;
     const float v = ((B.red[r][0][h] + B.red[r][1][h]) + B.red[r][2][h]) + B.red[r][3][h];
     out[(r == 0 ? MLP_OFF_B1 : MLP_OFF_B2) + h] = v;
   }
@@ -485,44 +544,25 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(const MlpImage *img, cons
   }
 }
 
-// The image of the flat parameters: one thread per parameter, through the
-// same image_put the Adam step uses, then one per padding element (zero).
-__global__ void mlp_pack_kernel(const float *theta, MlpImage *img) {
-  constexpr uint32_t RP = 8, FP = 40 - DIN;  // padding per row of W2 / W2^T, of W1
-  constexpr uint32_t PADS = 2 * H * RP + H * FP;
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < (uint32_t)MLP_NPARAMS) {
-    image_put(*img, e, theta[e]);
-    return;
-  }
-  const uint32_t q = e - MLP_NPARAMS;
-  if (q < H * RP)
-    img->f.w2[q / RP][H + q % RP] = bf(0.0f);
-  else if (q < 2 * H * RP)
-    img->w2t[(q - H * RP) / RP][H + (q - H * RP) % RP] = bf(0.0f);
-  else if (q < PADS)
-    img->f.w1[(q - 2 * H * RP) / FP][DIN + (q - 2 * H * RP) % FP] = bf(0.0f);
-}
-
 // grad[p] = sum over workgroups of partial[wg][p] in a fixed order (row 0
-// first; the loads of eight rows are issued together); the loss slot
-// becomes the mean squared error. With `theta` set, also one Adam step, and
-// with `img` set, the updated weights' image.
+// first; the loads of 16 rows are issued together); the loss slot becomes
+// the mean squared error. With `theta` set, also one Adam step. One wave per
+// workgroup, for the latency of as many CUs as there are waves.
 __global__ void grad_reduce_kernel(const float *partial, uint32_t n_wg, float inv_n, float *grad,
-                                   float *loss, float *theta, float *m, float *v, AdamArgs ad,
-                                   MlpImage *img) {
+                                   float *loss, float *theta, float *m, float *v, AdamArgs ad) {
   const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > (uint32_t)MLP_NPARAMS) return;
   float s = 0.0f;
   uint32_t k = 0;
-  for (; k + 8 <= n_wg; k += 8) {
-    float t[8];
+  for (; k < n_wg; k += 16) {
+    float t[16];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) t[j] = partial[(uint64_t)(k + j) * MLP_PSTRIDE + p];
+    for (uint32_t j = 0; j < 16; ++j)
+      t[j] = partial[(uint64_t)(k + j < n_wg ? k + j : k) * MLP_PSTRIDE + p];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) s += t[j];
+    for (uint32_t j = 0; j < 16; ++j)
+      if (k + j < n_wg) s += t[j];
   }
-  for (; k < n_wg; ++k) s += partial[(uint64_t)k * MLP_PSTRIDE + p];
   if (p == (uint32_t)MLP_NPARAMS) {
     if (loss) *loss = s * inv_n;
     return;
@@ -533,9 +573,7 @@ __global__ void grad_reduce_kernel(const float *partial, uint32_t n_wg, float in
     const float vv = ad.beta2 * v[p] + (1.0f - ad.beta2) * s * s;
     m[p] = mm;
     v[p] = vv;
-    const float nt = theta[p] - ad.lr * (mm / ad.bc1) / (sqrtf(vv / ad.bc2) + ad.eps);
-    theta[p] = nt;
-    if (img) image_put(*img, p, nt);
+    theta[p] -= ad.lr * (mm / ad.bc1) / (sqrtf(vv / ad.bc2) + ad.eps);
   }
 }
 
@@ -588,30 +626,23 @@ hipError_t launch_cv_infer(const float *theta, const float *x, uint64_t n, const
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_pack(const float *theta, void *img, hipStream_t s) {
-  constexpr uint32_t cells = MLP_NPARAMS + 2 * H * 8 + H * (40 - DIN);
-  hipLaunchKernelGGL(mlp_pack_kernel, dim3((cells + 255) / 256), dim3(256), 0, s, theta,
-                     (MlpImage *)img);
-  return hipGetLastError();
-}
-
-hipError_t launch_mlp_grad(const void *img, const float *x, const float *z, const float *y,
+hipError_t launch_mlp_grad(const float *theta, const float *x, const float *z, const float *y,
                            uint64_t n, float *partial, hipStream_t s) {
   const size_t lds = sizeof(BwdLds);
   hipError_t e = allow_lds(mlp_grad_kernel, lds);
   if (e != hipSuccess) return e;
   const uint64_t blocks = (n + TS - 1) / TS;
-  hipLaunchKernelGGL(mlp_grad_kernel, dim3((uint32_t)blocks), dim3(256), lds, s,
-                     (const MlpImage *)img, x, z, y, n, 1.0f / (float)n, partial);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3((uint32_t)blocks), dim3(512), lds, s, theta, x, z, y, n,
+                     1.0f / (float)n, partial);
   return hipGetLastError();
 }
 
 hipError_t launch_grad_reduce(const float *partial, uint32_t n_wg, uint64_t n, float *grad,
                               float *loss, float *theta, float *m, float *v, const AdamArgs &ad,
-                              void *img, hipStream_t s) {
-  const uint32_t threads = 256, blocks = (MLP_NPARAMS + 1 + threads - 1) / threads;
+                              hipStream_t s) {
+  const uint32_t threads = 64, blocks = (MLP_NPARAMS + 1 + threads - 1) / threads;
   hipLaunchKernelGGL(grad_reduce_kernel, dim3(blocks), dim3(threads), 0, s, partial, n_wg,
-                     1.0f / (float)n, grad, loss, theta, m, v, ad, (MlpImage *)img);
+                     1.0f / (float)n, grad, loss, theta, m, v, ad);
   return hipGetLastError();
 }
 
@@ -636,10 +667,7 @@ constexpr uint64_t NOALLOC_MAX_N = MRIP_MLP_GRAD_NOALLOC_MAX;
 constexpr uint64_t NOALLOC_ROWS = NOALLOC_MAX_N / TS;
 static_assert(NOALLOC_MAX_N % TS == 0, "whole partial rows");
 
-// the partial rows, then the weights' image
-constexpr uint64_t NOALLOC_IMAGE_OFF = NOALLOC_ROWS * MLP_PSTRIDE;  // floats
-static_assert(NOALLOC_IMAGE_OFF % 4 == 0 && MLP_IMAGE_BYTES % 4 == 0, "16-byte aligned image");
-__device__ __align__(256) float scratch[NOALLOC_IMAGE_OFF + MLP_IMAGE_BYTES / 4];
+__device__ __align__(256) float scratch[NOALLOC_ROWS * MLP_PSTRIDE];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
@@ -678,14 +706,11 @@ extern "C" MRIP_API mrip_status mrip_mlp_grad_noalloc(const float *theta_dev, co
   if (scratch_on_device(&part) != hipSuccess) return MRIP_E_HIP;
   hipStream_t s = (hipStream_t)hip_stream;
   const uint64_t rows = (n + TS - 1) / TS;
-  float *img = part + NOALLOC_IMAGE_OFF;
-  // every element of the image and every row the reduction reads is
-  // written first, by the pack and the gradient kernels
-  if (launch_mlp_pack(theta_dev, img, s) != hipSuccess) return MRIP_E_HIP;
-  if (launch_mlp_grad(img, x_dev, z_dev, y_dev, n, part, s) != hipSuccess) return MRIP_E_HIP;
+  // every row the reduction reads is written first, by the gradient kernel
+  if (launch_mlp_grad(theta_dev, x_dev, z_dev, y_dev, n, part, s) != hipSuccess) return MRIP_E_HIP;
   AdamArgs none{};
   if (launch_grad_reduce(part, (uint32_t)rows, n, grad_dev, loss_dev, nullptr, nullptr, nullptr,
-                         none, nullptr, s) != hipSuccess)
+                         none, s) != hipSuccess)
     return MRIP_E_HIP;
   return MRIP_OK;
 }

@@ -70,6 +70,29 @@ def test_gradient_matches_oracle(gpu, n, mult):
         assert np.all(gd["W3"][1:] == 0.0) and np.all(gd["b3"][1:] == 0.0)
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 1024, 1025])
+def test_gradient_at_the_edges_of_its_tiles(gpu, n):
+    # part-filled groups of 16 samples, one and two rows, 16 and 17 partial
+    # rows; one bf16 rounding that falls the other way in a layer of 128 units
+    # moves a norm by 2^-8 / sqrt(128), 3.5e-4
+    announce("mlp grad edges", n)
+    rng = np.random.default_rng(70 + n)
+    x = rng.normal(size=(n, 10)).astype(np.float32)
+    yt = rng.normal(size=n).astype(np.float32)
+    z = rng.normal(size=(n, 4)).astype(np.float32)
+    theta = _theta(2)
+    grad = torch.empty(mrip.MRIP_MLP_PARAMS, dtype=torch.float32, device="cuda")
+    loss = torch.empty(1, dtype=torch.float32, device="cuda")
+    mrip.mrip_mlp_grad(_dev(theta), _dev(x), _dev(z), _dev(yt), n, grad, loss,
+                       mrip.current_stream())
+    ref, ref_loss = omlp.backward(theta, x, yt, bf16=True, z=z)
+    gd, rd = omlp.unpack(grad.cpu().numpy().astype(np.float64)), omlp.unpack(ref)
+    for name in NAMES:
+        err = np.linalg.norm(gd[name] - rd[name]) / max(np.linalg.norm(rd[name]), 1e-30)
+        assert err < 1e-3, (name, err)
+    assert abs(float(loss.cpu()[0]) - ref_loss) <= 1e-4 * ref_loss
+
+
 def test_gradient_of_constant_network_is_bias_only(gpu):
     # W3 = 0: every gradient except dW3 and db3 vanishes; with prediction
     # c = b3 . z, db3_k = 2 mean((c - y) z_k)
