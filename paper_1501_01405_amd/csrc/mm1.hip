@@ -573,6 +573,11 @@ __global__ __launch_bounds__(ft_max_wg<FT>()) void mm1_wave_kernel(Mm1Args a, fl
 // totals through LDS), which gives each lane the system time before its
 // run; pass 2 re-reads the run from the saved state and applies Lindley's
 // recursion. No speculation: the scan is exact max-plus composition.
+// Vector instructions bound it, the streams' most of all, read twice: eight
+// outputs at a time (TausStream) they are 14 of a customer's 30 per pass,
+// where they were 32 of 48. 1024 replications of 20011 customers: 64 us,
+// was 92 (one wavefront per SIMD, which issues one instruction in five
+// cycles); 1024 of 1e5 on four wavefronts each 183, was 297.
 template <int LPR>
 __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, float cs) {
   constexpr int G = LPR < 64 ? LPR : 64;  // lanes of one replication inside a wavefront
@@ -605,23 +610,28 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
 
   // pass 1: the run's composite map T -> later(ma, T + mb)
   float ma = kBeforeAll, mb = 0.0f;
-  Taus t = t0;
   {
-    auto step = [&]() {
-      const float A = qa * log2_u01(taus_next(t));
-      const float S = log2_u01(taus_next(t));
+    TausStream ts(t0);
+    uint32_t x[8];
+    auto step = [&](uint32_t xa, uint32_t xs) {
+      const float A = qa * log2_u01(xa);
+      const float S = log2_u01(xs);
       const float bj = S - A;
       ma = later(S, ma + bj);
       mb = mb + bj;
     };
     uint32_t i = 0;
     for (; i + 4 <= m; i += 4) {
-      step();
-      step();
-      step();
-      step();
+      ts.next8(x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) step(x[2 * k], x[2 * k + 1]);
     }
-    for (; i < m; ++i) step();
+    if (i < m) {
+      ts.next8(x);
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (i + k < m) step(x[2 * k], x[2 * k + 1]);
+    }
   }
   // inclusive scan in lane order (earlier runs first)
 #pragma unroll
@@ -652,7 +662,7 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
   // pass 2: Lindley's recursion over the run, from the saved stream state,
   // in the map form of the wavefront engines: x = T + S - A, T <- later(x,
   // S), I = T - x; sums of T, S and I, the waits as their difference
-  t = t0;
+  Taus t = t0;
   Kahan kt, ks, ki;
   Feat ft;
   uint32_t i = 0;
@@ -685,14 +695,15 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
   // also the four controls, weighted by T_{n-1} where they are; plain fp32
   // sums over 8 customers, then one compensated add each
   Kahan kc[4];
+  TausStream ts(t);
   auto rest = [&](auto ctl_tag) {
     constexpr bool CTL = decltype(ctl_tag)::value;
     while (i < m) {
       const uint32_t e = min(m, i + 8);
       float st = 0.0f, ss = 0.0f, si = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, c3 = 0.0f;
-      auto step = [&]() {
-        const float A = qa * log2_u01(taus_next(t));
-        const float S = log2_u01(taus_next(t));
+      auto step = [&](uint32_t xa, uint32_t xs) {
+        const float A = qa * log2_u01(xa);
+        const float S = log2_u01(xs);
         if (CTL) {
           const float ds = __builtin_fmaf(cs, S, -a.es), da = __builtin_fmaf(cs, A, -a.ea);
           c0 += ds;
@@ -706,13 +717,23 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
         ss += S;
         si += T - x;
       };
+      uint32_t x[8];
       if (e - i == 8) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) step();
-        i = e;
+        for (int half = 0; half < 2; ++half) {
+          ts.next8(x);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) step(x[2 * k], x[2 * k + 1]);
+        }
       } else {
-        for (; i < e; ++i) step();
+        for (; i < e; i += 4) {
+          ts.next8(x);
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (i + k < e) step(x[2 * k], x[2 * k + 1]);
+        }
       }
+      i = e;
       kt.add(st);
       ks.add(ss);
       ki.add(si);
@@ -738,28 +759,33 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
   v[0] = group_sum_compensated((kt.sum - ks.sum) - (kt.comp - ks.comp), G);
   v[1] = group_sum_compensated(kt.value(), G);
   v[2] = group_sum_compensated(ki.value(), G);
-  v[3] = group_sum_compensated(ft.sa, G);
-  v[4] = group_sum_compensated(ft.ss, G);
-  v[5] = group_sum_compensated(ft.sw, G);
-  v[6] = group_sum_compensated(ft.st, G);
-  v[7] = (float)group_sum_i(ft.zeros, G);
-  v[8] = group_max(-ft.wmax, G);
-  v[9] = group_sum_compensated(ft.tlast, G);
-  v[10] = group_sum_compensated(ft.si, G);
+  if (K > 0) {
+    v[3] = group_sum_compensated(ft.sa, G);
+    v[4] = group_sum_compensated(ft.ss, G);
+    v[5] = group_sum_compensated(ft.sw, G);
+    v[6] = group_sum_compensated(ft.st, G);
+    v[7] = (float)group_sum_i(ft.zeros, G);
+    v[8] = group_max(-ft.wmax, G);
+    v[9] = group_sum_compensated(ft.tlast, G);
+    v[10] = group_sum_compensated(ft.si, G);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    v[11 + k] = group_sum_compensated(kc[k].value(), G);
-    v[15 + k] = group_sum_compensated(ft.pc[k], G);
+    for (int k = 0; k < 4; ++k) {
+      v[11 + k] = group_sum_compensated(kc[k].value(), G);
+      v[15 + k] = group_sum_compensated(ft.pc[k], G);
+    }
   }
+  const int sums = K > 0 ? 19 : 3;
   if (LPR > 64) {
     if (lane == 0) {
 #pragma unroll
-      for (int k = 0; k < 19; ++k) sh_f[wave][k] = v[k];
+      for (int k = 0; k < 19; ++k)
+        if (k < sums) sh_f[wave][k] = v[k];
     }
     __syncthreads();
     if (j == 0) {  // lane 0 of the replication's first wavefront
 #pragma unroll
       for (int k = 0; k < 19; ++k) {
+        if (k >= sums) break;
         float hi = sh_f[wave][k], lo = 0.0f;
         for (int w = wave + 1; w < wave + LPR / 64; ++w) {
           if (k == 8) {

@@ -104,6 +104,63 @@ __device__ __forceinline__ Taus taus_seed(uint32_t model, uint32_t dp, uint32_t 
   return t;
 }
 
+// Eight outputs at a time. A component's words are windows of 32 bits, S
+// bits apart, on one sequence with b[n + K] = b[n] ^ b[n + Q], hence also
+// b[n + 2K] = b[n] ^ b[n + 2Q]: from 64 bits of it the next 32 are two
+// windows and an exclusive or, whatever S is, and a window is one
+// instruction. That is 57 instructions for eight outputs (16, 10 and 23 for
+// the components, 8 to join them), where one step after the other takes 5
+// per component and 128.
+template <int K, int Q, int S>
+struct TausBits {
+  uint32_t h1, h0;  // the state's window, and the 32 bits after it
+
+  // 32 bits from bit `at` of the words w[0], w[1], ..
+  static __device__ __forceinline__ uint32_t window(const uint32_t *w, int at) {
+    return at % 32 == 0 ? w[at / 32]
+                        : __builtin_amdgcn_alignbit(w[at / 32], w[at / 32 + 1], 32 - at % 32);
+  }
+  static __device__ __forceinline__ uint32_t after(const uint32_t *w, int at) {  // bits at..at+31
+    return window(w, at - 2 * K) ^ window(w, at - 2 * K + 2 * Q);
+  }
+
+  // From a state whose low 32 - K bits are not the sequence's (a seed's, a
+  // jump's): first those, then 32 more, K - Q at a time.
+  __device__ __forceinline__ explicit TausBits(uint32_t z) {
+    constexpr int F = K - Q, R = 32 - K;
+    h1 = (z & (0xFFFFFFFFu << R)) | ((z ^ (z << Q)) >> K);
+    const uint32_t n1 = (h1 << R) ^ (h1 << (R + Q));
+    const uint32_t later = __builtin_amdgcn_alignbit(h1, n1, 32 - F);
+    const uint32_t n2 = (later << R) ^ (later << (R + Q));
+    h0 = (n1 & (0xFFFFFFFFu << (32 - F))) | (n2 >> F);
+  }
+  __device__ __forceinline__ void next8(uint32_t (&out)[8]) {
+    constexpr int WORDS = (8 * S + 31) / 32 + 1;
+    uint32_t w[WORDS + 1] = {h1, h0};
+#pragma unroll
+    for (int i = 2; i < WORDS; ++i) w[i] = after(w, 32 * i);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = window(w, S * (i + 1));
+    h0 = after(w, 8 * S + 32);
+    h1 = out[7];
+  }
+};
+
+struct TausStream {
+  TausBits<TAUS_K0, TAUS_Q0, TAUS_S0> a;
+  TausBits<TAUS_K1, TAUS_Q1, TAUS_S1> b;
+  TausBits<TAUS_K2, TAUS_Q2, TAUS_S2> c;
+  __device__ __forceinline__ explicit TausStream(const Taus &t) : a(t.z0), b(t.z1), c(t.z2) {}
+  __device__ __forceinline__ void next8(uint32_t (&x)[8]) {
+    uint32_t y[8], z[8];
+    a.next8(x);
+    b.next8(y);
+    c.next8(z);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = x[i] ^ y[i] ^ z[i];
+  }
+};
+
 // Advance by d outputs with the power-of-two tables.
 __device__ __forceinline__ void taus_skip(Taus &t, uint64_t d, const uint32_t *__restrict__ tables) {
   for (int j = 0; d != 0; ++j, d >>= 1)

@@ -109,6 +109,28 @@ def test_mm1_matches_oracle(gpu, mapping, rpw, wg, split, N, R, lam, K):
         assert np.abs(feat[:, 6] - res[1][:, 6]).max() <= 2.0 / K
 
 
+@pytest.mark.parametrize("run", [1, 2, 3, 4, 5, 7, 8, 9, 11, 13, 16, 31])
+def test_runs_of_every_remainder(gpu, run):
+    # outputs come eight at a time: runs per lane of every remainder by 4
+    # customers or points and by the 8 of a partial sum, with and without a
+    # feature prefix, short last lanes; the tolerance is the oracle test's
+    announce("taus88 runs", run)
+    for N in (64 * run - 2 if run > 2 else 64 * run, 64 * run):
+        for K in (0, N // 3):
+            ctx = _ctx(mrip.MRIP_MM1, mrip.mm1_params(0.9, 1.0, N, K), WAVE)
+            ctx.run(5, seed=run)
+            outs = np.stack([ctx.output(o).cpu().numpy() for o in range(3)], axis=1)
+            res = core.mm1_many(run, 5, N, 0.9, 1.0, features=K, threads=core.default_threads(),
+                                rng="taus88")
+            assert rel_err(outs, res[0] if K else res).max() <= TOL
+        points = [N, 1024 * 64 + N]  # a wavefront, a workgroup per replication
+        for p in points:
+            ctx = _ctx(mrip.MRIP_PI, mrip.pi_params(p), WAVE)
+            ctx.run(3, seed=run)
+            ref = core.pi_many(run, 3, p, threads=core.default_threads(), rng="taus88")
+            assert np.array_equal(ctx.output(0).cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("split", [1, 4])
 def test_mm1_wave_sampled_at_full_size(gpu, split):
     # 1024 x 1e5 (lambda 0.9) on taus88, WAVE: sampled replications
