@@ -952,7 +952,7 @@ mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n)
   if (b.count == 0) ctx->n_items = 0;  // the old plan's table is gone (a refused plan leaves it)
   if (st != MRIP_OK) return st;
   HIP_TRY(ctx, ctx->dp_stats.ensure(sizeof(double) * 3 * b.dp_ids.size()));
-  HIP_TRY(ctx, ctx->queue.ensure(256));
+  HIP_TRY(ctx, ctx->queue.ensure(4 * PLAN_QUEUE_WORDS));
   HIP_TRY(ctx, hipStreamSynchronize(nullptr));
   b.in_flight = false;
   ctx->n_items = n;
@@ -1021,7 +1021,7 @@ static mrip_status run_plan_impl(mrip_ctx ctx, uint64_t seed, hipStream_t s, con
   a.mean_w = (float *)outp[0];
   a.mean_t = (float *)outp[1];
   a.mean_i = (float *)outp[2];
-  HIP_TRY(ctx, launch_zero_u32(a.queue_head, 2, s));
+  HIP_TRY(ctx, launch_zero_u32(a.queue_head, PLAN_QUEUE_WORDS, s));
   st = record_begin(ctx, s);
   if (st != MRIP_OK) return st;
   if (n == 0) {

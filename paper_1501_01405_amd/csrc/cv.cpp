@@ -66,7 +66,7 @@ AdamArgs adam_args(float lr, float b1, float b2, float eps, uint64_t step) {
 mrip_status run_items(mrip_ctx c, ItemBufs &b, uint64_t seed, uint64_t K, float *mean_w,
                       float *feat, float *ctl, hipStream_t s, TimingEvent *ev) {
   CvState &cv = c->cv;
-  CV_TRY(c, cv.queue.ensure(256));
+  CV_TRY(c, cv.queue.ensure(4 * PLAN_QUEUE_WORDS));
   CV_TRY(c, cv.scratch_t.ensure(4 * b.count));
   CV_TRY(c, cv.scratch_i.ensure(4 * b.count));
   Mm1Args a{};
@@ -84,7 +84,7 @@ mrip_status run_items(mrip_ctx c, ItemBufs &b, uint64_t seed, uint64_t K, float 
   a.mean_i = cv.scratch_i.as<float>();
   a.features = feat;
   a.controls = ctl;
-  CV_TRY(c, launch_zero_u32(a.queue_head, 2, s));
+  CV_TRY(c, launch_zero_u32(a.queue_head, PLAN_QUEUE_WORDS, s));
   if (ev) CV_TRY(c, ev[0].record(s));
   const uint32_t split = plan_split_for(c, b.max_customers, b.total_customers);
   if (split > 1 && b.n_long > 0)

@@ -42,6 +42,11 @@ hipError_t launch_rw_wave(const RwArgs &a, uint32_t workgroup, hipStream_t s);
 // one_lane: one working lane per wavefront (the paper's WLP form)
 hipError_t launch_rw_simt(const RwArgs &a, bool one_lane, hipStream_t s);
 
+// The plan kernels' queue: two sets (split items, the rest) of PLAN_QUEUES
+// counters, each in a 128-byte line of its own.
+constexpr uint32_t PLAN_QUEUES = 16, PLAN_QUEUE_STRIDE = 32;
+constexpr uint32_t PLAN_QUEUE_WORDS = 2 * PLAN_QUEUES * PLAN_QUEUE_STRIDE;
+
 // ------------------------------------------------------------ M/M/1
 // Per-item parameters in structure-of-arrays form on the device.
 struct Mm1Items {
@@ -57,7 +62,7 @@ struct Mm1Args {
   uint64_t customers;           // uniform mode
   uint64_t feature_prefix;      // K (0 = no features)
   Mm1Items items;               // plan mode (items.dp != nullptr)
-  uint32_t *queue_head;         // plan mode: device counter, zero at launch
+  uint32_t *queue_head;         // plan mode: PLAN_QUEUE_WORDS device counters, zero at launch
   float *mean_w, *mean_t, *mean_i;
   float *features;              // n x 10 when feature_prefix > 0
   // n x 8 when feature_prefix > 0: the martingale controls over customers

@@ -186,3 +186,32 @@ def test_autotune_cache_round_trip(gpu, tmp_path, monkeypatch):
     a.run_plan(42)
     assert np.array_equal(a.output(0, n=len(items)).cpu().numpy(),
                           b.output(0, n=len(items)).cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 511, 512, 513, 4095, 4096, 4097, 4111, 4113, 9001])
+def test_every_unit_of_the_queue_is_served_once(gpu, n):
+    # unit counts around the counters, the workgroups and the wavefronts that
+    # take their first unit by number; equal items are the replications of a
+    # uniform run, whose bits every shape gives
+    announce("plan queue", n)
+    ref = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(0.9, 1.0, 700), WAVE)
+    ref.run(n, seed=4)
+    want = [ref.output(o).cpu().numpy() for o in range(3)]
+    items = inputs.uniform_items(1, n, 700, [0.9])
+    for rpw, split in ((1, 1), (2, 1), (4, 1), (1, 2), (2, 4), (1, 8)):
+        for long_share in (1.0,) if split == 1 else (1.0, 0.4):
+            # the longest-first order puts the longer items first
+            it = items.copy()
+            k = int(n * long_share)
+            it["customers"][:k] += 1 if long_share < 1.0 else 0
+            ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(0.9, 1.0, 700), WAVE)
+            ctx.set_shape(rpw, 256)
+            ctx.set_plan_split(split, 701 if long_share < 1.0 else 1)
+            ctx.plan_set(it)
+            ctx.run_plan(seed=4)
+            assert np.all(mrip.mrip_plan_done(ctx.ctx, n) == 1)
+            for o in range(3):
+                got = ctx.output(o, n=n).cpu().numpy()
+                rest = slice(k if long_share < 1.0 else 0, n)
+                assert np.array_equal(got[rest], want[o][rest]), (rpw, split, long_share, o)
+                assert np.all(np.isfinite(got)) and np.all(got > 0.0)
