@@ -44,7 +44,7 @@ hipError_t launch_rw_simt(const RwArgs &a, bool one_lane, hipStream_t s);
 
 // The plan kernels' queue: two sets (split items, the rest) of PLAN_QUEUES
 // counters, each in a 128-byte line of its own.
-constexpr uint32_t PLAN_QUEUES = 16, PLAN_QUEUE_STRIDE = 32;
+constexpr uint32_t PLAN_QUEUES = 64, PLAN_QUEUE_STRIDE = 32;
 constexpr uint32_t PLAN_QUEUE_WORDS = 2 * PLAN_QUEUES * PLAN_QUEUE_STRIDE;
 
 // ------------------------------------------------------------ M/M/1

@@ -830,36 +830,39 @@ __global__ __launch_bounds__(256) void mm1_taus_kernel(Mm1Args a, float ca, floa
 
 // The plans' queue. Atomic adds to one address from the whole chip take 15 ns
 // each, one after the other, and bound every plan of short items while there
-// was one counter: 10000 items of 1500 customers 166 us, now 68; 10000 of
-// 2500 with features 151, now 87; 16384 of 1e4 with features 286, now 253.
-// So the first unit of a wavefront (or workgroup) is its own number, and the
-// D units after those are dealt to QUEUES counters in lines of their own:
-// counter c serves c, c + QUEUES, .., still longest first. A wavefront pops
-// its own counter, and when that is used up looks at all of them (one load)
-// and goes on with the next that has units left. Counters only grow, so the
-// search ends.
+// was one counter. So the first unit of a wavefront (or workgroup) is its own
+// number, and the D units after those are dealt to QUEUES counters in lines
+// of their own: counter c serves c, c + QUEUES, .., still longest first. A
+// wavefront pops its own counter if a load says that it has units left (the
+// thousands that end together would otherwise queue up to be told no), else
+// it looks at all of them, one a lane, and goes on with the next that has.
+// Counters only grow, so the search ends. 10000 items of 1500 customers:
+// 166 us with one counter, 70 with 16 and no look, 51 with 64; 5200 of 1100:
+// 112, 61, 24; 16384 of 1e4 with features: 289, 251, 252.
 constexpr uint32_t QUEUES = PLAN_QUEUES, QUEUE_STRIDE = PLAN_QUEUE_STRIDE;
+static_assert(QUEUES == 64, "one counter per lane");
 constexpr uint64_t QUEUE_EMPTY = ~0ull;
 
 // The next of units 0..D-1 for this wavefront, or QUEUE_EMPTY; all lanes.
 __device__ __forceinline__ uint64_t pop_unit(uint32_t *heads, uint32_t home, uint64_t D) {
   const uint32_t lane = threadIdx.x & 63;
-  const auto held = [&](uint32_t c) { return D > c ? (D - c + QUEUES - 1) / QUEUES : 0; };
-  uint32_t c = home % QUEUES;
+  const auto has_left = [&](uint32_t c, uint64_t k) { return c + k * QUEUES < D; };
+  const auto head = [&](uint32_t c) {
+    return __hip_atomic_load(&heads[c * QUEUE_STRIDE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   if (D == 0) return QUEUE_EMPTY;
+  uint32_t c = home % QUEUES;
   for (;;) {
-    uint32_t k = 0;
-    if (lane == 0) k = atomicAdd(&heads[c * QUEUE_STRIDE], 1u);
-    k = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
-    if (k < held(c)) return c + (uint64_t)k * QUEUES;
-    bool left = false;
-    if (lane < QUEUES)
-      left = __hip_atomic_load(&heads[lane * QUEUE_STRIDE], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT) < held(lane);
-    const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(left);
+    if (has_left(c, (uint32_t)__builtin_amdgcn_readfirstlane((int)head(c)))) {
+      uint32_t k = 0;
+      if (lane == 0) k = atomicAdd(&heads[c * QUEUE_STRIDE], 1u);
+      k = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
+      if (has_left(c, k)) return c + (uint64_t)k * QUEUES;
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(has_left(lane, head(lane)));
     if (m == 0) return QUEUE_EMPTY;
-    const uint32_t after = m >> c;  // the first with units left, from c on
-    c = after ? c + (uint32_t)__builtin_ctz(after) : (uint32_t)__builtin_ctz(m);
+    const uint64_t after = m >> c;  // the first with units left, from c on
+    c = after ? c + (uint32_t)__builtin_ctzll(after) : (uint32_t)__builtin_ctzll(m);
   }
 }
 

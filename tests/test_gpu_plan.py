@@ -188,7 +188,8 @@ def test_autotune_cache_round_trip(gpu, tmp_path, monkeypatch):
                           b.output(0, n=len(items)).cpu().numpy())
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 511, 512, 513, 4095, 4096, 4097, 4111, 4113, 9001])
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 64, 65, 511, 512, 513, 4095, 4096, 4097, 4111, 4160,
+                               4161, 9001])
 def test_every_unit_of_the_queue_is_served_once(gpu, n):
     # unit counts around the counters, the workgroups and the wavefronts that
     # take their first unit by number; equal items are the replications of a
