@@ -361,11 +361,13 @@ MRIP_API mrip_status mrip_plan_stats(mrip_ctx ctx, uint32_t dp, double confidenc
  * over waves_per_item (1, 2, 4 or 8) wavefronts of a workgroup, served first
  * (longest first) at raised wavefront priority, since the longest items set
  * the plan's makespan; the rest go reps_per_wave per wavefront. Until this
- * call (or mrip_autotune) fixes it, a plan takes the fewest wavefronts per
- * long item, up to 8, that bring its longest item's share of its customers
- * down to its average per wavefront the device holds at once (16 per
- * compute unit), the same in every run of the plan (stopped at an item
- * limit or resumed): a plan of many equal long items is not split. */
+ * call (or mrip_autotune) fixes it, a plan chooses both by an estimate of
+ * its longest item's time and of all its work's (a plan with features: items
+ * of 65536 customers, the fewest wavefronts, up to 8, that bring the longest
+ * item's share of its customers down to the average per wavefront the device
+ * holds at once), the same in every run of the plan (stopped at an item
+ * limit or resumed). Sums are fp64: however items are split, a mean moves by
+ * the last bit of its fp32 value at most. */
 MRIP_API mrip_status mrip_set_plan_split(mrip_ctx ctx, uint32_t waves_per_item,
                                          uint64_t long_min);
 

@@ -964,20 +964,59 @@ mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n)
 }
 
 // Items of a longest-first order that count as long (a prefix of it).
-// The split of the uploaded plan's long items: decided on the whole plan
+static uint64_t count_long(const std::vector<uint64_t> &lpt, uint64_t n, uint64_t long_min) {
+  return (uint64_t)(std::partition_point(lpt.begin(), lpt.begin() + (ptrdiff_t)n,
+                                         [&](uint64_t c) { return c >= long_min; }) -
+                    lpt.begin());
+}
+
+// How the uploaded plan's long items are split: decided on the whole plan
 // (its longest item and all its customers), so a run stopped at an item
 // limit or resumed from saved outputs splits every item as the
 // uninterrupted run does and gives the same bits.
-static uint32_t plan_split_of(mrip_ctx ctx) {
-  uint64_t total = 0;
-  for (uint64_t n : ctx->lpt_customers) total += n;
-  return plan_split_for(ctx, ctx->lpt_customers.empty() ? 0 : ctx->lpt_customers[0], total);
-}
+struct PlanShape {
+  uint32_t split;
+  uint64_t long_min;
+};
 
-static uint64_t count_long(const std::vector<uint64_t> &lpt, uint64_t n, uint64_t long_min) {
-  uint64_t k = 0;
-  while (k < n && lpt[k] >= long_min) ++k;
-  return k;
+// Without features every form gives the same means (fp64 sums, rounded once),
+// and the plan takes the one whose estimate is lowest. In chunks of 1024 customers (620
+// instructions): the longest item alone takes 1.29 us a chunk on one
+// wavefront, 0.67, 0.333 and 0.269 on two, four and eight (eight share the
+// SIMDs of one compute unit); all of the work takes 1.046 us a chunk on one
+// SIMD, 3 % and 13 % more split in two and eight, and about 4 us more per
+// wavefront of each split item. The estimate is the root of the squares' sum
+// of the two. Items are split from 16384 customers, or from the length that
+// unsplit takes half as long as the longest does split: shorter ones cost
+// more in overhead than they hold up. Over 46 plans of 4 to 80 design points
+// of 20 to 40 replications, 1e3..1e4 to 3e4..1e6 customers, the chosen form
+// is 3 % slower than the best of 27 tried on average (17 % at most), and 1.8
+// times as fast as eight wavefronts for items of 65536 customers (0.988 at
+// worst); 64 x 32 of 1e4 to 1e6: 596 us that way, 474 on four from 16384.
+static PlanShape plan_shape_of(mrip_ctx ctx) {
+  const std::vector<uint64_t> &lpt = ctx->lpt_customers;
+  const uint64_t longest = lpt.empty() ? 0 : lpt[0];
+  uint64_t total = 0;
+  for (uint64_t n : lpt) total += n;
+  const uint32_t fixed = plan_split_for(ctx, longest, total);  // also finds out ctx->cus
+  if (ctx->plan_split_set || ctx->mm1.feature_prefix > 0) return {fixed, ctx->long_min};
+  constexpr double ALONE[4] = {1.29, 0.67, 0.333, 0.269}, MORE[4] = {1.0, 1.03, 1.0, 1.13};
+  const double chunks = (double)total / 1024.0 + 0.5 * (double)lpt.size();
+  PlanShape best{1, ctx->long_min};
+  double best_time = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    const uint64_t long_min = std::max<uint64_t>(
+        1, std::min<uint64_t>(16384, (uint64_t)(0.5 * (double)longest * ALONE[k] / ALONE[0])));
+    const double n_split = k == 0 ? 0.0 : (double)count_long(lpt, lpt.size(), long_min);
+    const double work = (chunks * 1.046 * MORE[k] + 4.0 * (1 << k) * n_split) / (4.0 * ctx->cus);
+    const double path = std::ceil((double)longest / 1024.0) * ALONE[k];
+    const double time = std::sqrt(work * work + path * path);
+    if (k == 0 || time < best_time) {
+      best_time = time;
+      if (k > 0) best = {1u << k, long_min};
+    }
+  }
+  return best;
 }
 
 // done (nullable): the per-item done flags the kernels set, cleared first
@@ -1067,15 +1106,15 @@ mrip_status mrip_run_plan(mrip_ctx ctx, uint64_t seed, void *hip_stream) {
   // the item limit stops the run after a prefix of the longest-first order
   const uint64_t n_run =
       ctx->plan_limit ? std::min<uint64_t>(ctx->n_items, ctx->plan_limit) : ctx->n_items;
+  const PlanShape shape = plan_shape_of(ctx);
   const uint64_t n_long =
-      std::min<uint64_t>(count_long(ctx->lpt_customers, ctx->n_items, ctx->long_min), n_run);
+      std::min<uint64_t>(count_long(ctx->lpt_customers, ctx->n_items, shape.long_min), n_run);
   const bool whole = n_run == ctx->n_items;
-  const uint32_t split = plan_split_of(ctx);
   uint8_t *done = nullptr;
   mrip_status st = done_flags(ctx, &done);
   if (st != MRIP_OK) return st;
   st = run_plan_impl(ctx, seed, (hipStream_t)hip_stream, ctx->items.order, n_run,
-                     n_long, ctx->plan_rpw, ctx->plan_wg, split, whole, done, true);
+                     n_long, ctx->plan_rpw, ctx->plan_wg, shape.split, whole, done, true);
   if (st != MRIP_OK) return st;
   ctx->last = whole ? RUN_PLAN : RUN_PLAN_PARTIAL;
   ctx->last_n = ctx->n_items;
@@ -1122,10 +1161,10 @@ mrip_status mrip_run_plan_resume(mrip_ctx ctx, uint64_t seed, const uint8_t *ski
   std::vector<uint8_t> flags(ctx->n_items);
   for (uint64_t i = 0; i < ctx->n_items; ++i) flags[i] = skip_done[i] ? 1 : 0;
   HIP_TRY(ctx, hipMemcpy(done, flags.data(), ctx->n_items, hipMemcpyHostToDevice));
-  const uint64_t n_long = count_long(todo_n, todo.size(), ctx->long_min);
-  const uint32_t split = plan_split_of(ctx);
+  const PlanShape shape = plan_shape_of(ctx);
+  const uint64_t n_long = count_long(todo_n, todo.size(), shape.long_min);
   st = run_plan_impl(ctx, seed, s, ctx->resume_order.as<uint32_t>(), todo.size(), n_long,
-                     ctx->plan_rpw, ctx->plan_wg, split, whole, done, false);
+                     ctx->plan_rpw, ctx->plan_wg, shape.split, whole, done, false);
   if (st != MRIP_OK) return st;
   ctx->last = whole ? RUN_PLAN : RUN_PLAN_PARTIAL;
   ctx->last_n = ctx->n_items;

@@ -216,3 +216,26 @@ def test_every_unit_of_the_queue_is_served_once(gpu, n):
                 rest = slice(k if long_share < 1.0 else 0, n)
                 assert np.array_equal(got[rest], want[o][rest]), (rpw, split, long_share, o)
                 assert np.all(np.isfinite(got)) and np.all(got > 0.0)
+
+
+@pytest.mark.parametrize("dps,reps,lo,hi", [(1, 1, 1, 1), (4, 20, 1000, 100000), (12, 30, 500, 20000),
+                                            (40, 30, 3000, 60000), (60, 32, 10000, 400000),
+                                            (40, 40, 2000, 2000)])
+def test_plan_in_its_own_shape_matches_the_unsplit_plan(gpu, dps, reps, lo, hi):
+    # plans whose own choice is one, two, four and eight wavefronts per long
+    # item, all of their items long or some; fp64 sums in another order,
+    # rounded once to fp32
+    announce("plan own shape", dps, reps, lo, hi)
+    items = inputs.plan_table(n_dp=dps, reps=reps, n_lo=lo, n_hi=hi, seed=dps) if hi > lo else \
+        inputs.uniform_items(dps, reps, lo, np.linspace(0.5, 0.95, dps))
+    outs = []
+    for own in (True, False):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+        if not own:
+            ctx.set_plan_split(1, 1)
+        ctx.plan_set(items)
+        ctx.run_plan(seed=6)
+        assert np.all(mrip.mrip_plan_done(ctx.ctx, len(items)) == 1)
+        outs.append([ctx.output(o, n=len(items)).cpu().numpy() for o in range(3)])
+    for a, b in zip(*outs):
+        assert rel_err(a, b).max() <= 2.0**-23
