@@ -157,25 +157,32 @@ __device__ __forceinline__ uint32_t moves_left(uint32_t g, uint32_t end) {
 }
 
 // Moves g .. end - 1 (g a multiple of 64) of walker w of replication rep,
-// from Philox blocks.
+// from Philox blocks, word by word.
+template <class Word>
+__device__ __forceinline__ void each_word(uint32_t g, uint32_t end, uint32_t w, uint32_t rep,
+                                          uint32_t k0, uint32_t k1, Word word) {
+  for (; g + 64u <= end; g += 64) {
+    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
+    word(b.x, 16u);
+    word(b.y, 16u);
+    word(b.z, 16u);
+    word(b.w, 16u);
+  }
+  if (g < end) {
+    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
+    word(b.x, moves_left(g, end));
+    word(b.y, moves_left(g + 16, end));
+    word(b.z, moves_left(g + 32, end));
+    word(b.w, moves_left(g + 48, end));
+  }
+}
+
 template <int SH>
 __device__ __forceinline__ void walk_blocks(uint32_t g, uint32_t end, uint32_t w, uint32_t rep,
                                             uint32_t k0, uint32_t k1, int &X, int &Y,
                                             uint8_t *map) {
-  for (; g + 64u <= end; g += 64) {
-    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
-    walk_word<SH>(b.x, 16u, X, Y, map);
-    walk_word<SH>(b.y, 16u, X, Y, map);
-    walk_word<SH>(b.z, 16u, X, Y, map);
-    walk_word<SH>(b.w, 16u, X, Y, map);
-  }
-  if (g < end) {
-    const Block4 b = philox(g >> 6, w, rep, TAG_RW, k0, k1);
-    walk_word<SH>(b.x, moves_left(g, end), X, Y, map);
-    walk_word<SH>(b.y, moves_left(g + 16, end), X, Y, map);
-    walk_word<SH>(b.z, moves_left(g + 32, end), X, Y, map);
-    walk_word<SH>(b.w, moves_left(g + 48, end), X, Y, map);
-  }
+  each_word(g, end, w, rep, k0, k1,
+            [&](uint32_t word, uint32_t n) { walk_word<SH>(word, n, X, Y, map); });
 }
 
 // Marked sites of replication slot i among those thread j of n counts.
@@ -255,6 +262,164 @@ __global__ __launch_bounds__(64 * WAVES) void rw_map_kernel(RwArgs a) {
   }
   __syncthreads();
   const int cnt = group_sum_i(count_sites<GRID>(map, wave, lane, 64), 64);
+  const int ssd = group_sum_i(sd, 64);
+  if (lane == 0 && r < a.n_reps) {
+    a.ssd[r] = ssd;
+    a.distinct[r] = cnt;
+  }
+}
+
+// Two moves a store. Every walker starts on a site with x + y even, so after
+// an even number of moves it is on one again, and the site between is a
+// neighbour of it: a byte per even site and direction says "was here and left
+// that way", which marks both sites of a pair of moves. In the 64-torus map
+// (SiteMap<64>) the direction takes byte 0's two free bits, so a site's four
+// directions are one word; byte 1's two free bits and the parity of the
+// sites used (a replication on the odd ones starts one site to the right)
+// number eight replications in the 64 KiB.
+struct PairMap {
+  static constexpr int SH = 2;
+  static constexpr uint32_t REPS = 8, ENDED = 2;  // ENDED: in direction 0's byte, the last site
+  static __device__ __forceinline__ int byte0(int x, uint32_t i) {
+    return (int)((uint32_t)x + (i >> 2)) << SH;
+  }
+  static __device__ __forceinline__ int byte1(int y, uint32_t i) {
+    return (int)((uint32_t)y << SH | (i & 3u));
+  }
+};
+
+// Moves 0 .. n - 1 (n <= 16) of a word by one walker at (X, Y), on an even
+// site unless n was odd.
+__device__ __forceinline__ void walk_pairs(uint32_t word, uint32_t n, int &X, int &Y,
+                                           uint8_t *map) {
+  constexpr uint32_t P1 = 1u << PairMap::SH, M1 = 256u - P1;
+  constexpr uint32_t TX = P1 | M1 << 8, TY = P1 << 16 | M1 << 24;
+  if (n >= 16u) {
+    uint32_t d[4], dx[4], dy[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      d[k] = (word >> (2 * k)) & 0x03030303u;  // moves k, 4 + k, 8 + k, 12 + k
+      dx[k] = __builtin_amdgcn_perm(0u, TX, d[k]);
+      dy[k] = __builtin_amdgcn_perm(0u, TY, d[k]);
+    }
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m % 2 == 0) map[map_address(X + (int)((d[m & 3] >> (8 * (m >> 2))) & 0xFFu), Y)] = 1;
+      X += (int)(int8_t)(dx[m & 3] >> (8 * (m >> 2)));
+      Y += (int)(int8_t)(dy[m & 3] >> (8 * (m >> 2)));
+    }
+  } else {
+    for (uint32_t m = 0; m < n; ++m) {
+      const uint32_t d = (word >> (2 * m)) & 3u;
+      if (m % 2 == 0) map[map_address(X + (int)d, Y)] = 1;
+      int ddx, ddy;
+      step_delta(d, ddx, ddy);
+      X += ddx << PairMap::SH;
+      Y += ddy << PairMap::SH;
+    }
+  }
+}
+
+// Visited sites of replication slot i among those lane j counts: even
+// sites, each with its right neighbour, an odd one, which was visited if one
+// of its four neighbours was left towards it.
+template <int GRID>
+__device__ __forceinline__ int count_pairs(const uint8_t *map, uint32_t i, int j) {
+  constexpr int COPIES = 64 / GRID, HALF = GRID / 2;
+  const auto odd_site = [](uint32_t left, uint32_t right, uint32_t below, uint32_t above) {
+    return (left & 0x1u) | (right & 0x100u) | (below & 0x10000u) | (above & 0x1000000u);
+  };
+  if constexpr (COPIES == 1) {
+    // a lane has two columns and half of the rows: its even sites and their
+    // right neighbours' right neighbours, row by row, are all it reads (a row
+    // is 1 KiB further on, so the addresses are constants)
+    const int k = j & 31;
+    const auto column = [&](int x, int p) {
+      return map + map_address((x + p) << PairMap::SH, PairMap::byte1(0, i));
+    };
+    // rows whose even sites are the even columns (p = 0) and the odd ones
+    const int odd_rows = (int)(i >> 2), y0 = (j >> 5) * 32 + odd_rows;  // y0: a p = 0 row
+    const uint8_t *h0 = column(2 * k, 0), *r0 = column(2 * k, 2), *h1 = column(2 * k, 1),
+                  *r1 = column(2 * k, 3);
+    const auto at = [](const uint8_t *c, int y) {
+      return *(const uint32_t *)(c + ((y & 63) << 10));
+    };
+    int cnt = 0;
+    uint32_t below = at(h1, y0 - 1);  // the p = 1 row under the first
+    for (int y = y0; y < y0 + 32; y += 2) {
+      const uint32_t a = at(h0, y), b = at(r0, y);          // p = 0
+      const uint32_t c = at(h1, y + 1), d = at(r1, y + 1);  // p = 1
+      const uint32_t e = at(r0, y + 2);                     // p = 0 again
+      cnt += (a != 0u) + (odd_site(a, b, below, c) != 0u);
+      cnt += (c != 0u) + (odd_site(c, d, b, e) != 0u);
+      below = c;
+    }
+    return cnt;
+  }
+  const auto word = [&](int x, int y) {  // a site's directions, over its copies
+    uint32_t w = 0;
+#pragma unroll
+    for (int cy = 0; cy < COPIES; ++cy)
+#pragma unroll
+      for (int cx = 0; cx < COPIES; ++cx)
+        w |= *(const uint32_t *)(map + map_address((x + cx * GRID) << PairMap::SH,
+                                                   PairMap::byte1(y + cy * GRID, i)));
+    return w;
+  };
+  int cnt = 0;
+  for (int v = j; v < HALF * GRID; v += 64) {
+    const int y = v / HALF, x = 2 * (v % HALF) + ((y + (int)(i >> 2)) & 1);
+    const uint32_t here = word(x, y), right = word(x + 2, y), below = word(x + 1, y - 1),
+                   above = word(x + 1, y + 1);
+    cnt += (here != 0u) + (odd_site(here, right, below, above) != 0u);
+  }
+  return cnt;
+}
+
+// One replication per wavefront, as rw_map_kernel, two moves a store: half
+// the stores, so vector instructions (4.8 a move) and the stores (3.4 cycles
+// a move and compute unit) overlap. 16384 replications of 64 x 1000 on 64 x
+// 64: 0.181 ms, 0.205 with a store per move.
+template <int GRID, int RNG>
+__global__ __launch_bounds__(64 * PairMap::REPS) void rw_pair_kernel(RwArgs a) {
+  static_assert(GRID <= 64, "the 64-torus");
+  constexpr int WAVES = (int)PairMap::REPS;
+  __shared__ __attribute__((aligned(16))) uint8_t map[65536];
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = threadIdx.x >> 6;
+  const uint64_t r = (uint64_t)blockIdx.x * WAVES + wave;
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  for (int i = threadIdx.x; i < 65536 / 16; i += 64 * WAVES)
+    ((uint4 *)map)[i] = uint4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  const bool active = r < a.n_reps && (uint32_t)lane < a.walkers;
+  int sd = 0, X = 0, Y = 0;
+  if (active) {
+    int x0, y0;
+    start_site((uint32_t)lane, GRID, x0, y0);
+    const int X0 = PairMap::byte0(x0, wave), Y0 = PairMap::byte1(y0, wave);
+    X = X0;
+    Y = Y0;
+    const uint32_t rep = (uint32_t)(a.rep0 + r);
+    if (RNG == RNG_TAUS88) {
+      Taus t = taus_seed(TAG_RW, 0u, rep, k0, k1);
+      taus_jump(t, a.taus_walk + (uint64_t)lane * TAUS_COLS);  // to the walker's run
+      uint32_t g = 0;
+      for (; g + 16u <= a.steps; g += 16) walk_pairs(taus_next(t), 16u, X, Y, map);
+      if (g < a.steps) walk_pairs(taus_next(t), a.steps - g, X, Y, map);
+    } else {
+      each_word(0u, a.steps, (uint32_t)lane, rep, k0, k1,
+                [&](uint32_t word, uint32_t n) { walk_pairs(word, n, X, Y, map); });
+    }
+    const int ux = (X - X0) >> PairMap::SH, uy = (Y - Y0) >> PairMap::SH;
+    sd = ux * ux + uy * uy;
+  }
+  __syncthreads();
+  // a walk of an even number of moves ends on an even site that it does not leave
+  if (active && a.steps % 2 == 0)
+    atomicOr((uint32_t *)(map + map_address(X, Y)), PairMap::ENDED);
+  __syncthreads();
+  const int cnt = group_sum_i(count_pairs<GRID>(map, wave, lane), 64);
   const int ssd = group_sum_i(sd, 64);
   if (lane == 0 && r < a.n_reps) {
     a.ssd[r] = ssd;
@@ -597,6 +762,23 @@ hipError_t map_launch(const RwArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Moves from which a chip full of walks marks two moves a store: counting
+// costs more there (16384 replications on 64 x 64: 200 moves 50.6 us with a
+// store per move, 53.3 with one per two; 400 88.5 / 85.0; 1000 205 / 181),
+// and with fewer replications latency bounds the walk, not the stores (1024
+// of 1000 moves 21.5 / 22.2, 4096 56.8 / 52.9).
+constexpr uint32_t RW_PAIR_MIN_STEPS = 400;
+
+template <int GRID>
+hipError_t pair_launch(const RwArgs &a, hipStream_t s) {
+  const dim3 g((uint32_t)((a.n_reps + PairMap::REPS - 1) / PairMap::REPS)), b(64 * PairMap::REPS);
+  if (a.rng == RNG_TAUS88)
+    hipLaunchKernelGGL((rw_pair_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a);
+  else
+    hipLaunchKernelGGL((rw_pair_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a);
+  return hipGetLastError();
+}
+
 template <int GRID>
 hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   const bool sites = a.walker_sites != nullptr, taus = a.rng == RNG_TAUS88;
@@ -618,8 +800,10 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
     return hipGetLastError();
   }
   if (!sites) {
-    if constexpr (GRID < 128)
-      if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
+    if constexpr (GRID < 128) {
+      if (a.n_reps >= RW_MAP8_MIN_REPS)
+        return a.steps >= RW_PAIR_MIN_STEPS ? pair_launch<GRID>(a, s) : map_launch<GRID, 8>(a, s);
+    }
     return map_launch<GRID, 4>(a, s);
   }
   const uint32_t wpb = wg / 64;

@@ -232,3 +232,23 @@ def test_walk_site_map_bit_exact(gpu, grid, walkers, steps, R, rng):
     ssd, dist = core.rw_many(11, ids, walkers, grid, steps, rng=rng)
     assert np.array_equal(ctx.output(0).cpu().numpy()[ids], ssd)
     assert np.array_equal(ctx.output(1).cpu().numpy()[ids], dist)
+
+
+@pytest.mark.parametrize("grid,walkers,steps,R", [
+    (64, 64, 399, 4096), (64, 64, 400, 4096), (64, 64, 401, 4099), (64, 1, 415, 4096),
+    (64, 35, 417, 4104), (32, 64, 448, 4097), (32, 7, 463, 4096), (16, 64, 400, 4096),
+    (16, 33, 2001, 4096)])
+@pytest.mark.parametrize("rng", ["philox", "taus88"])
+def test_walk_marked_by_pairs_bit_exact(gpu, grid, walkers, steps, R, rng):
+    # from 4096 replications and 400 moves two moves are marked by one store:
+    # even and odd lengths, ragged words and blocks, folded grids, every slot
+    # of a map (the first and last eight replications)
+    announce("walk pairs", grid, walkers, steps, R, rng)
+    ctx = mrip.Context(mrip.MRIP_RW, mrip.rw_params(walkers, grid, steps), WAVE)
+    if rng == "taus88":
+        ctx.set_rng(mrip.MRIP_RNG_TAUS88)
+    ctx.run(R, seed=21)
+    ids = [*range(8), 1777, *range(R - 8, R)]
+    essd, edist = core.rw_many(21, ids, walkers, grid, steps, rng=rng)
+    assert np.array_equal(ctx.output(0).cpu().numpy()[ids], essd)
+    assert np.array_equal(ctx.output(1).cpu().numpy()[ids], edist)
