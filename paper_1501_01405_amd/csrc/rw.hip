@@ -299,6 +299,7 @@ __device__ __forceinline__ void walk_pairs(uint32_t word, uint32_t n, int &X, in
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       d[k] = (word >> (2 * k)) & 0x03030303u;  // moves k, 4 + k, 8 + k, 12 + k
+      asm("" : "+v"(d[k]));  // bytes to add, not bit fields to extract first
       dx[k] = __builtin_amdgcn_perm(0u, TX, d[k]);
       dy[k] = __builtin_amdgcn_perm(0u, TY, d[k]);
     }
@@ -307,6 +308,7 @@ __device__ __forceinline__ void walk_pairs(uint32_t word, uint32_t n, int &X, in
       if (m % 2 == 0) map[map_address(X + (int)((d[m & 3] >> (8 * (m >> 2))) & 0xFFu), Y)] = 1;
       X += (int)(int8_t)(dx[m & 3] >> (8 * (m >> 2)));
       Y += (int)(int8_t)(dy[m & 3] >> (8 * (m >> 2)));
+      asm("" : "+v"(X), "+v"(Y));  // one addition per move (of a byte), not two fields and a sum
     }
   } else {
     for (uint32_t m = 0; m < n; ++m) {
@@ -377,9 +379,10 @@ __device__ __forceinline__ int count_pairs(const uint8_t *map, uint32_t i, int j
 }
 
 // One replication per wavefront, as rw_map_kernel, two moves a store: half
-// the stores, so vector instructions (4.8 a move) and the stores (3.4 cycles
-// a move and compute unit) overlap. 16384 replications of 64 x 1000 on 64 x
-// 64: 0.181 ms, 0.205 with a store per move.
+// the stores (3.4 cycles a move and compute unit), and as many vector
+// instructions (5 a move, four of them additions of a byte), which bound it.
+// 16384 replications of 64 x 1000 on 64 x 64: 0.145 ms, 0.205 with a store
+// per move.
 template <int GRID, int RNG>
 __global__ __launch_bounds__(64 * PairMap::REPS) void rw_pair_kernel(RwArgs a) {
   static_assert(GRID <= 64, "the 64-torus");
@@ -762,12 +765,14 @@ hipError_t map_launch(const RwArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Moves from which a chip full of walks marks two moves a store: counting
-// costs more there (16384 replications on 64 x 64: 200 moves 50.6 us with a
-// store per move, 53.3 with one per two; 400 88.5 / 85.0; 1000 205 / 181),
-// and with fewer replications latency bounds the walk, not the stores (1024
-// of 1000 moves 21.5 / 22.2, 4096 56.8 / 52.9).
-constexpr uint32_t RW_PAIR_MIN_STEPS = 400;
+// Replications and moves from which two moves are marked by one store:
+// counting the sites costs more there (16384 replications on 64 x 64: 100
+// moves 31.5 us with a store per move, 35.2 with one per two; 150 41 / 41;
+// 200 50 / 47; 300 69 / 59; 1000 205 / 145), and with few replications latency
+// bounds the walk, not the stores (1024 of 1000 moves 21.5 / 22.0; 2000 of
+// 400 17.8 / 15.6; 3000 of 200 16.0 / 16.4).
+constexpr uint64_t RW_PAIR_MIN_REPS = 2000;
+constexpr uint32_t RW_PAIR_MIN_STEPS = 256;
 
 template <int GRID>
 hipError_t pair_launch(const RwArgs &a, hipStream_t s) {
@@ -801,8 +806,9 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   }
   if (!sites) {
     if constexpr (GRID < 128) {
-      if (a.n_reps >= RW_MAP8_MIN_REPS)
-        return a.steps >= RW_PAIR_MIN_STEPS ? pair_launch<GRID>(a, s) : map_launch<GRID, 8>(a, s);
+      if (a.n_reps >= RW_PAIR_MIN_REPS && a.steps >= RW_PAIR_MIN_STEPS)
+        return pair_launch<GRID>(a, s);
+      if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
     }
     return map_launch<GRID, 4>(a, s);
   }

@@ -235,12 +235,12 @@ def test_walk_site_map_bit_exact(gpu, grid, walkers, steps, R, rng):
 
 
 @pytest.mark.parametrize("grid,walkers,steps,R", [
-    (64, 64, 399, 4096), (64, 64, 400, 4096), (64, 64, 401, 4099), (64, 1, 415, 4096),
-    (64, 35, 417, 4104), (32, 64, 448, 4097), (32, 7, 463, 4096), (16, 64, 400, 4096),
-    (16, 33, 2001, 4096)])
+    (64, 64, 255, 2000), (64, 64, 256, 2000), (64, 64, 257, 2003), (64, 1, 415, 2000),
+    (64, 35, 417, 4104), (32, 64, 448, 4097), (32, 7, 463, 2000), (16, 64, 256, 2000),
+    (16, 33, 2001, 2000)])
 @pytest.mark.parametrize("rng", ["philox", "taus88"])
 def test_walk_marked_by_pairs_bit_exact(gpu, grid, walkers, steps, R, rng):
-    # from 4096 replications and 400 moves two moves are marked by one store:
+    # from 2000 replications and 256 moves two moves are marked by one store:
     # even and odd lengths, ragged words and blocks, folded grids, every slot
     # of a map (the first and last eight replications)
     announce("walk pairs", grid, walkers, steps, R, rng)
