@@ -28,15 +28,30 @@ namespace {
 
 // mask = 2 mask + [u < t]: the borrow of u - t shifts straight into the mask
 // (v_sub_co_u32 then v_addc_co_u32), two instructions per bit where a
-// compare, a select and a shift-or would take three.
-__device__ __forceinline__ uint32_t shift_in_less(uint32_t mask, uint32_t u, uint32_t t) {
+// compare, a select and a shift-or would take three. A carry that the vector
+// ALU writes to scalar registers may be read by it two wait states later at
+// the earliest; the compiler sees to that for its own instructions only, so
+// the steps alternate between two carries (c = vcc and %[c]), each read after
+// the other one's two instructions, and the first and the last wait.
+#define FF_LESS(c, u, t) "v_sub_co_u32 %[tmp], " c ", %[" u "], %[" t "]\n\t"
+#define FF_SHIFT(c, m) "v_addc_co_u32 %[" m "], " c ", %[" m "], %[" m "], " c "\n\t"
+#define FF_C0 "vcc"
+#define FF_C1 "%[c]"
+
+// Both masks of one block's four cells, cell 3 first.
+__device__ __forceinline__ void shift_in_less(uint32_t &mp, uint32_t &mf, const Block4 &b,
+                                              uint32_t tp, uint32_t tf) {
   uint32_t tmp;
-  asm("v_sub_co_u32 %0, vcc, %2, %3\n\t"
-      "v_addc_co_u32 %1, vcc, %1, %1, vcc"
-      : "=&v"(tmp), "+v"(mask)
-      : "v"(u), "v"(t)
+  uint64_t c;
+  asm(FF_LESS(FF_C0, "w", "tp") FF_LESS(FF_C1, "w", "tf") "s_nop 0\n\t"
+      FF_SHIFT(FF_C0, "mp") FF_LESS(FF_C0, "z", "tp") FF_SHIFT(FF_C1, "mf") FF_LESS(FF_C1, "z", "tf")
+      FF_SHIFT(FF_C0, "mp") FF_LESS(FF_C0, "y", "tp") FF_SHIFT(FF_C1, "mf") FF_LESS(FF_C1, "y", "tf")
+      FF_SHIFT(FF_C0, "mp") FF_LESS(FF_C0, "x", "tp") FF_SHIFT(FF_C1, "mf") FF_LESS(FF_C1, "x", "tf")
+      FF_SHIFT(FF_C0, "mp") "s_nop 0\n\t"
+      FF_SHIFT(FF_C1, "mf")
+      : [tmp] "=&v"(tmp), [mp] "+&v"(mp), [mf] "+&v"(mf), [c] "=&s"(c)
+      : [w] "v"(b.w), [z] "v"(b.z), [y] "v"(b.y), [x] "v"(b.x), [tp] "v"(tp), [tf] "v"(tf)
       : "vcc");
-  return mask;
 }
 
 // Bits [u < TP] and [u < TF] for the 32 cells of one word: cells
@@ -48,17 +63,8 @@ __device__ __forceinline__ void draw_masks(uint32_t t, uint32_t q0, uint32_t rep
   // kept as a loop: eight inlined Philox blocks per word would stop the
   // callers' loops over the register-resident grid from unrolling
 #pragma unroll 2
-  for (int m = 7; m >= 0; --m) {
-    const Block4 b = philox(t, q0 + (uint32_t)m, rep, TAG_FF, k0, k1);
-    mp = shift_in_less(mp, b.w, tp);
-    mf = shift_in_less(mf, b.w, tf);
-    mp = shift_in_less(mp, b.z, tp);
-    mf = shift_in_less(mf, b.z, tf);
-    mp = shift_in_less(mp, b.y, tp);
-    mf = shift_in_less(mf, b.y, tf);
-    mp = shift_in_less(mp, b.x, tp);
-    mf = shift_in_less(mf, b.x, tf);
-  }
+  for (int m = 7; m >= 0; --m)
+    shift_in_less(mp, mf, philox(t, q0 + (uint32_t)m, rep, TAG_FF, k0, k1), tp, tf);
   ltp = mp;
   ltf = mf;
 }
@@ -90,23 +96,29 @@ __device__ __forceinline__ Words16 draw16(uint32_t c0_base, uint32_t c1, uint32_
 
 // mask = the bits [u < t] of the 16 cells shifted in, cell 15 first.
 __device__ __forceinline__ uint32_t less16(uint32_t mask, const Words16 &w, uint32_t t) {
-#pragma unroll
-  for (int j = 3; j >= 0; --j) {
-    uint32_t tmp;
-    asm("v_sub_co_u32 %0, vcc, %2, %6\n\t"
-        "v_addc_co_u32 %1, vcc, %1, %1, vcc\n\t"
-        "v_sub_co_u32 %0, vcc, %3, %6\n\t"
-        "v_addc_co_u32 %1, vcc, %1, %1, vcc\n\t"
-        "v_sub_co_u32 %0, vcc, %4, %6\n\t"
-        "v_addc_co_u32 %1, vcc, %1, %1, vcc\n\t"
-        "v_sub_co_u32 %0, vcc, %5, %6\n\t"
-        "v_addc_co_u32 %1, vcc, %1, %1, vcc"
-        : "=&v"(tmp), "+&v"(mask)
-        : "v"(w.b[j].w), "v"(w.b[j].z), "v"(w.b[j].y), "v"(w.b[j].x), "v"(t)
-        : "vcc");
-  }
+  uint32_t tmp;
+  uint64_t c;
+#define FF_NEXT(u0, u1)                                                      \
+  FF_SHIFT(FF_C0, "mask") FF_LESS(FF_C0, u0, "t") FF_SHIFT(FF_C1, "mask") \
+      FF_LESS(FF_C1, u1, "t")
+  asm(FF_LESS(FF_C0, "w3", "t") FF_LESS(FF_C1, "z3", "t") "s_nop 0\n\t"
+      FF_NEXT("y3", "x3") FF_NEXT("w2", "z2") FF_NEXT("y2", "x2") FF_NEXT("w1", "z1")
+      FF_NEXT("y1", "x1") FF_NEXT("w0", "z0") FF_NEXT("y0", "x0")
+      FF_SHIFT(FF_C0, "mask") "s_nop 0\n\t"
+      FF_SHIFT(FF_C1, "mask")
+      : [tmp] "=&v"(tmp), [mask] "+&v"(mask), [c] "=&s"(c)
+      : [w3] "v"(w.b[3].w), [z3] "v"(w.b[3].z), [y3] "v"(w.b[3].y), [x3] "v"(w.b[3].x),
+        [w2] "v"(w.b[2].w), [z2] "v"(w.b[2].z), [y2] "v"(w.b[2].y), [x2] "v"(w.b[2].x),
+        [w1] "v"(w.b[1].w), [z1] "v"(w.b[1].z), [y1] "v"(w.b[1].y), [x1] "v"(w.b[1].x),
+        [w0] "v"(w.b[0].w), [z0] "v"(w.b[0].z), [y0] "v"(w.b[0].y), [x0] "v"(w.b[0].x), [t] "v"(t)
+      : "vcc");
+#undef FF_NEXT
   return mask;
 }
+#undef FF_LESS
+#undef FF_SHIFT
+#undef FF_C0
+#undef FF_C1
 
 __device__ __forceinline__ uint32_t min16(const Words16 &w) {
   uint32_t m = 0xFFFFFFFFu;
