@@ -349,13 +349,13 @@ MRIP_API mrip_status mrip_set_plan_limit(mrip_ctx ctx, uint64_t max_items);
  * item's outputs are stored: done[i] = 1 if item i's outputs in the output
  * buffers are final (run by that plan run, or flagged in the skip_done
  * mask it resumed from), else 0. done: host array of n bytes, n = the
- * plan's item count (MRIP_E_INVAL otherwise); MRIP_E_STATE before a plan
- * run. Synchronises. The flags of a stopped run can be passed as skip_done
+ * plan's item count (MRIP_E_INVAL otherwise); MRIP_E_STATE before a run of
+ * this plan. Synchronises. The flags of a stopped run can be passed as skip_done
  * to mrip_run_plan_resume. */
 MRIP_API mrip_status mrip_plan_done(mrip_ctx ctx, uint8_t *done, uint64_t n);
 
 /* Stats of output 0 (mean W) over the items of design point `dp` in the
- * last plan run. Synchronises. */
+ * last run of this plan (MRIP_E_STATE before one). Synchronises. */
 MRIP_API mrip_status mrip_plan_stats(mrip_ctx ctx, uint32_t dp, double confidence, mrip_stats_t *out);
 
 /* Plans: items of at least long_min customers (0 = 65536) are each split

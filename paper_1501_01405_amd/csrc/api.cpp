@@ -949,17 +949,21 @@ mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n)
   ItemBufs &b = ctx->items;
   mrip_status st = upload_items(ctx, items, n, ctx->mm1.feature_prefix, ctx->long_min, false, b,
                                 nullptr);
-  if (b.count == 0) ctx->n_items = 0;  // the old plan's table is gone (a refused plan leaves it)
+  // a refused plan leaves the old one; from here on its table is gone, and so
+  // are its flags and statistics (which lie in the old plan's order and size)
+  if (st != MRIP_OK && b.count != 0) return st;
+  ctx->n_items = 0;
+  ctx->plan_ran = false;
   if (st != MRIP_OK) return st;
   HIP_TRY(ctx, ctx->dp_stats.ensure(sizeof(double) * 3 * b.dp_ids.size()));
   HIP_TRY(ctx, ctx->queue.ensure(4 * PLAN_QUEUE_WORDS));
   HIP_TRY(ctx, hipStreamSynchronize(nullptr));
   b.in_flight = false;
-  ctx->n_items = n;
   ctx->dp_ids = b.dp_ids;
   ctx->lpt_order = b.order_host;
   ctx->lpt_customers.resize(n);
   for (uint64_t j = 0; j < n; ++j) ctx->lpt_customers[j] = items[b.order_host[j]].customers;
+  ctx->n_items = n;
   return MRIP_OK;
 }
 
@@ -1117,6 +1121,7 @@ mrip_status mrip_run_plan(mrip_ctx ctx, uint64_t seed, void *hip_stream) {
                      n_long, ctx->plan_rpw, ctx->plan_wg, shape.split, whole, done, true);
   if (st != MRIP_OK) return st;
   ctx->last = whole ? RUN_PLAN : RUN_PLAN_PARTIAL;
+  ctx->plan_ran = true;
   ctx->last_n = ctx->n_items;
   return MRIP_OK;
 }
@@ -1167,6 +1172,7 @@ mrip_status mrip_run_plan_resume(mrip_ctx ctx, uint64_t seed, const uint8_t *ski
                      ctx->plan_rpw, ctx->plan_wg, shape.split, whole, done, false);
   if (st != MRIP_OK) return st;
   ctx->last = whole ? RUN_PLAN : RUN_PLAN_PARTIAL;
+  ctx->plan_ran = true;
   ctx->last_n = ctx->n_items;
   return MRIP_OK;
 }
@@ -1179,8 +1185,8 @@ mrip_status mrip_set_plan_limit(mrip_ctx ctx, uint64_t max_items) {
 
 mrip_status mrip_plan_done(mrip_ctx ctx, uint8_t *done, uint64_t n) {
   if (!ctx || !done) return MRIP_E_INVAL;
-  if (ctx->last != RUN_PLAN && ctx->last != RUN_PLAN_PARTIAL)
-    return (ctx->err = "no plan run yet"), MRIP_E_STATE;
+  if ((ctx->last != RUN_PLAN && ctx->last != RUN_PLAN_PARTIAL) || !ctx->plan_ran)
+    return (ctx->err = "no run of this plan yet"), MRIP_E_STATE;
   if (n != ctx->n_items) return inval(ctx, "n must be the plan's item count");
   HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
   HIP_TRY(ctx, hipMemcpy(done, ctx->item_done.p, n, hipMemcpyDeviceToHost));
@@ -1203,7 +1209,8 @@ mrip_status mrip_plan_stats(mrip_ctx ctx, uint32_t dp, double confidence, mrip_s
   if (!(confidence > 0.0 && confidence < 1.0)) return inval(ctx, "confidence must be in (0, 1)");
   if (ctx->last == RUN_PLAN_PARTIAL)
     return (ctx->err = "the last plan run stopped at its item limit: no statistics"), MRIP_E_STATE;
-  if (ctx->last != RUN_PLAN) return (ctx->err = "no plan run yet"), MRIP_E_STATE;
+  if (ctx->last != RUN_PLAN || !ctx->plan_ran)
+    return (ctx->err = "no run of this plan yet"), MRIP_E_STATE;
   auto it = std::lower_bound(ctx->dp_ids.begin(), ctx->dp_ids.end(), dp);
   if (it == ctx->dp_ids.end() || *it != dp) return inval(ctx, "no such design point");
   const size_t g = (size_t)(it - ctx->dp_ids.begin());

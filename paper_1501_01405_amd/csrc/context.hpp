@@ -259,7 +259,8 @@ struct mrip_ctx_s {
   std::string err;
 
   // plan
-  uint64_t n_items = 0, n_long = 0;
+  uint64_t n_items = 0;
+  bool plan_ran = false;                // a run of this plan wrote the flags and statistics
   std::vector<uint64_t> lpt_customers;  // customers in longest-first order
   std::vector<uint32_t> lpt_order;      // item indices in longest-first order
   mrip::DevBuf resume_order;            // the queue of a resumed plan

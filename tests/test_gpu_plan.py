@@ -239,3 +239,28 @@ def test_plan_in_its_own_shape_matches_the_unsplit_plan(gpu, dps, reps, lo, hi):
         outs.append([ctx.output(o, n=len(items)).cpu().numpy() for o in range(3)])
     for a, b in zip(*outs):
         assert rel_err(a, b).max() <= 2.0**-23
+
+
+def test_a_new_plan_has_no_flags_or_statistics_before_its_run(gpu):
+    # the old plan's lie in its own order and size; a refused plan keeps them
+    announce("plan replaced")
+    ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+    a, b = inputs.uniform_items(2, 5, 300, [0.5, 0.6]), inputs.uniform_items(70, 40, 200, [0.5] * 70)
+    ctx.plan_set(a)
+    ctx.run_plan(seed=1)
+    want = ctx.plan_stats(1)
+    bad = b.copy()
+    bad["customers"][-1] = 0
+    with pytest.raises(mrip.MripError):
+        ctx.plan_set(bad)
+    assert ctx.plan_stats(1) == want and np.all(mrip.mrip_plan_done(ctx.ctx, len(a)) == 1)
+    ctx.plan_set(b)
+    for call in (lambda: ctx.plan_stats(1), lambda: ctx.plan_stats(69),
+                 lambda: mrip.mrip_plan_done(ctx.ctx, len(b))):
+        with pytest.raises(mrip.MripError) as e:
+            call()
+        assert e.value.status == mrip.MRIP_E_STATE
+    ctx.run_plan(seed=1)
+    got = ctx.output(0, n=len(b)).cpu().numpy().astype(np.float64).reshape(70, 40)
+    assert ctx.plan_stats(69)["mean"] == pytest.approx(got[69].mean(), rel=1e-12)
+    assert np.all(mrip.mrip_plan_done(ctx.ctx, len(b)) == 1)
