@@ -315,6 +315,21 @@ mrip_status upload_taus_tables(mrip_ctx c) {
   return MRIP_OK;
 }
 
+// The replications' meeting slots of pi_parts_kernel: zero once, and left zero
+// by every run. As many as any run needs, so that they never move (a graph
+// that holds a run keeps their address); zeroed by a copy that is over when
+// this returns, so that no later run depends on a launch of this one's.
+mrip_status upload_pi_slots(mrip_ctx c) {
+  if (c->pi_slots_ready) return MRIP_OK;
+  const std::vector<uint64_t> zero(PI_MANY_GROUPS, 0);
+  HIP_TRY(c, c->pi_slots.ensure(zero.size() * sizeof(uint64_t)));
+  HIP_TRY(c, hipMemcpy(c->pi_slots.p, zero.data(), zero.size() * sizeof(uint64_t),
+                       hipMemcpyHostToDevice));
+  HIP_TRY(c, hipStreamSynchronize(nullptr));
+  c->pi_slots_ready = true;
+  return MRIP_OK;
+}
+
 mrip_status validate(mrip_model model, const void *params, mrip_mapping map, std::string &why) {
   if (!params) return why = "params is NULL", MRIP_E_INVAL;
   if (map != MRIP_MAP_AUTO && map != MRIP_MAP_SIMT && map != MRIP_MAP_WAVE &&
@@ -803,12 +818,8 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
     a.rng = ctx->rng;
     a.taus = ctx->taus_tables.as<uint32_t>();
     if (wave && pi_parts(n_reps, a.points, a.rng) > 1) {
-      // the replications' meeting slots: zero once, left zero by every run
-      const size_t need = n_reps * sizeof(uint64_t);
-      if (need > ctx->pi_slots.bytes) {
-        HIP_TRY(ctx, ctx->pi_slots.ensure(need));
-        HIP_TRY(ctx, launch_zero_u32(ctx->pi_slots.as<uint32_t>(), (uint32_t)(need / 4), s));
-      }
+      st = upload_pi_slots(ctx);
+      if (st != MRIP_OK) return st;
       a.slots = ctx->pi_slots.as<uint64_t>();
     }
     if (wave) HIP_TRY(ctx, launch_pi_wave(a, ctx->wg, s));

@@ -205,6 +205,7 @@ struct mrip_ctx_s {
   void *cur[MAX_OUT] = {};
   mrip::DevBuf scratch;
   mrip::DevBuf pi_slots;        // where a replication's workgroups meet (pi_parts_kernel)
+  bool pi_slots_ready = false;  // allocated and zeroed
   mrip::DevBuf walker_scratch;  // the walk's per-walker bitmaps
   mrip::DevBuf taus_walk;       // the walk's taus88 jump tables (its steps are fixed)
   mrip::DevBuf taus_run;        // the M/M/1 runs' taus88 jump tables (customers are fixed)

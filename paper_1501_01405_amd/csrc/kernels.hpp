@@ -141,7 +141,7 @@ struct PiArgs {
   float *estimate;  // 4 hits / points
   int rng;
   const uint32_t *taus;
-  // n_reps 64-bit words, zero before the launch and after it (pi_parts > 1)
+  // PI_MANY_GROUPS 64-bit words, zero before the launch and after it (pi_parts > 1)
   uint64_t *slots;
 };
 // Workgroups per replication of the WAVE form on Philox streams; 0 = one
@@ -151,6 +151,9 @@ struct PiArgs {
 // with the chip full (5000 x 1e5 points: 0.270 ms against 0.312 with a
 // wavefront each, whose last round is uneven).
 constexpr uint64_t PI_PARTS_MAX_REPS = 1ull << 22, PI_PARTS_MIN_POINTS = 4096;
+// Workgroups that runs of short and of longer replications are spread over
+// (pi_parts): from PI_MANY_GROUPS replications on, one each.
+constexpr uint64_t PI_SOME_GROUPS = 2048, PI_MANY_GROUPS = 8192;
 uint32_t pi_parts(uint64_t n_reps, uint64_t points, int rng);
 hipError_t launch_pi_wave(const PiArgs &a, uint32_t workgroup, hipStream_t s);
 hipError_t launch_pi_simt(const PiArgs &a, bool one_lane, hipStream_t s);

@@ -280,8 +280,8 @@ uint32_t pi_parts(uint64_t n_reps, uint64_t points, int rng) {
   // two workgroups per SIMD's worth of wavefronts (2048) if a wavefront then
   // keeps four iterations of 512 points, up to four times as many (which
   // evens out the last round) while it keeps eight
-  const uint64_t some = std::min((2048 + n_reps - 1) / n_reps, points / 8192);
-  const uint64_t many = std::min((8192 + n_reps - 1) / n_reps, points / 16384);
+  const uint64_t some = std::min((PI_SOME_GROUPS + n_reps - 1) / n_reps, points / 8192);
+  const uint64_t many = std::min((PI_MANY_GROUPS + n_reps - 1) / n_reps, points / 16384);
   return (uint32_t)std::max<uint64_t>(1, std::max(some, many));
 }
 
@@ -296,7 +296,7 @@ hipError_t launch_pi_wave(const PiArgs &a, uint32_t wg, hipStream_t s) {
     if (x >= 2) return wide_taus_launch<2>(a, s);
   }
   if (const uint32_t parts = pi_parts(a.n_reps, a.points, a.rng)) {
-    if (parts > 1 && !a.slots) return hipErrorInvalidValue;
+    if (parts > 1 && (!a.slots || a.n_reps >= PI_MANY_GROUPS)) return hipErrorInvalidValue;
     // blocks per wavefront: a whole number of 256-block iterations
     const uint64_t blocks = (a.points + 1) / 2;
     const uint32_t per = (uint32_t)((blocks + 1024ull * parts - 1) / (1024ull * parts) * 256u);

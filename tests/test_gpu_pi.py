@@ -90,3 +90,40 @@ def test_pi_shared_replications_bit_exact(gpu, points, R):
         ctx.run(n, seed=seed)
         assert np.array_equal(ctx.output(0).cpu().numpy(),
                               core.pi_many(seed, n, points, threads=threads))
+
+
+def test_a_captured_run_keeps_its_meeting_slots(gpu):
+    # a run whose replications meet in slots of the context, captured with
+    # bound outputs; runs of more replications on the same context between the
+    # replays leave the slots where they are (and zero)
+    import torch
+    announce("pi in a graph")
+    P, few, many = 100001, 30, 5000
+    params = mrip.pi_params(P)
+    ref = mrip.Context(mrip.MRIP_PI, params, WAVE)
+    ref.run(few, seed=5)
+    want = ref.output(0).cpu().numpy()
+    ref.run(many, seed=6)
+    want_many = ref.output(0).cpu().numpy()
+    ctx = mrip.Context(mrip.MRIP_PI, params, WAVE)
+    hits = torch.zeros(many, dtype=torch.int32, device="cuda")
+    estimate = torch.zeros(many, dtype=torch.float32, device="cuda")
+    ctx.bind_output(0, hits)
+    ctx.bind_output(1, estimate)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        ctx.run(few, seed=1, stream=s.cuda_stream)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            ctx.run(few, seed=5, stream=s.cuda_stream)
+        for _ in range(3):
+            ctx.run(many, seed=6, stream=s.cuda_stream)
+            s.synchronize()
+            assert np.array_equal(hits.cpu().numpy(), want_many)
+            hits.zero_()
+            g.replay()
+            s.synchronize()
+            assert np.array_equal(hits.cpu().numpy()[:few], want)
+            assert not hits[few:].any()
