@@ -265,7 +265,8 @@ MRIP_API mrip_status mrip_stats_back(mrip_ctx ctx, uint32_t back, uint32_t outpu
 /* Copy output `output` of the last run (n_reps values; 10 per replication
  * for M/M/1 features, 8 for the controls) to dst, a device pointer if
  * dst_is_device, else host.
- * `bytes` must be at least the output's size. Synchronises. */
+ * `bytes` must be at least the output's size. Synchronises: the run and the
+ * copy are over when it returns. */
 MRIP_API mrip_status mrip_outputs(mrip_ctx ctx, uint32_t output, void *dst, uint64_t bytes,
                          int dst_is_device);
 

@@ -912,11 +912,13 @@ mrip_status mrip_outputs(mrip_ctx ctx, uint32_t output, void *dst, uint64_t byte
   if (output >= scalar_outputs(ctx) && !vec) return inval(ctx, "no such output");
   const uint64_t need = ctx->last_n * 4 * (vec ? vector_width(ctx, output) : 1);
   if (bytes < need) return inval(ctx, "destination too small");
-  // after the run: a copy on the null stream follows that stream's work by
-  // itself, and a host wait here would be for the last output's copy (11 us)
+  // On the null stream, after the run (work of that stream by its order, any
+  // other stream's by a wait), and over when this returns: a copy between
+  // device buffers does not wait by itself.
   if (ctx->last_stream) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_stream));
   HIP_TRY(ctx, hipMemcpy(dst, ctx->cur[output], need,
                          dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost));
+  if (dst_is_device) HIP_TRY(ctx, hipStreamSynchronize(nullptr));
   return MRIP_OK;
 }
 

@@ -112,3 +112,27 @@ def test_timing_sample(gpu):
     ctx.run(64, seed=20)
     assert ctx.last_ms() > 0.0
     assert ctx.stats(0)["n"] == 64
+
+
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_outputs_are_there_when_the_call_returns(gpu, own_stream):
+    # a copy to a device buffer, read at once on a stream that does not wait
+    # for the null stream
+    announce("outputs on return", own_stream)
+    R = 4096
+    ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(0.9, 1.0, 400000), WAVE)
+    stream = torch.cuda.Stream().cuda_stream if own_stream else None
+    reader = torch.cuda.Stream()
+    dst, got = torch.full((2, R), -1.0, device="cuda")
+    # the context's buffers, and the reader's copy loaded
+    ctx.run(R, seed=2, stream=0 if stream is None else stream)
+    with torch.cuda.stream(reader):
+        got.copy_(dst)
+    torch.cuda.synchronize()
+    ctx.run(R, seed=3, stream=0 if stream is None else stream)
+    mrip.mrip_outputs(ctx.ctx, 0, dst, True)
+    with torch.cuda.stream(reader):
+        got.copy_(dst)
+    reader.synchronize()
+    assert np.array_equal(got.cpu().numpy(), ctx.output(0).cpu().numpy())
+    assert bool((got > 0).all())
