@@ -249,9 +249,10 @@ MRIP_API mrip_status mrip_set_rng(mrip_ctx ctx, mrip_rng rng);
 MRIP_API mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_stream);
 
 /* Mean, unbiased variance and Student-t interval of output `output` of the
- * last run (paper section 1). Waits for that run's reduction (it polls the
- * result in pinned memory, and sleeps when that takes more than about a
- * millisecond). MRIP_E_TOO_FEW if fewer than two replications. */
+ * last run (paper section 1). Waits for that run's reduction, of all its
+ * outputs (it polls the results in pinned memory, and waits for an event when
+ * that takes more than about a millisecond). MRIP_E_TOO_FEW if fewer than
+ * two replications. */
 MRIP_API mrip_status mrip_stats(mrip_ctx ctx, uint32_t output, double confidence, mrip_stats_t *out);
 
 /* The same for the run `back` runs before the last one (0 = the last, at

@@ -178,18 +178,27 @@ mrip_status flush_pending(mrip_ctx c) {
   return MRIP_OK;
 }
 
-// Wait for a run's statistics of one output: poll them in pinned memory (a
-// result is seen 5 us sooner than through its event), then, from about a
-// millisecond on, sleep until the event recorded after the reduction. A
-// reduction carried by the next run's kernel has no such event: there the
-// stream is asked now and then, and one that has drained without publishing
-// them, or reports an error, ends the wait with an error.
-mrip_status wait_stats(mrip_ctx c, uint64_t index, uint32_t output, double *mean_var) {
+// Wait for a run's reduction, all `outputs` of it (the caller may reuse the
+// buffers of those it does not ask for), and give output `output`'s mean and
+// variance: poll them in pinned memory (a result is seen 5 us sooner than
+// through its event), then, from about a millisecond on, wait for the event
+// recorded after the reduction. A reduction carried by the next run's kernel
+// has no such event: there the stream is asked now and then, and one that has
+// drained without publishing them, or reports an error, ends the wait with an
+// error.
+mrip_status wait_stats(mrip_ctx c, uint64_t index, uint32_t outputs, uint32_t output,
+                       double *mean_var) {
   const uint32_t slot = stats_slot(index);
   const mrip_ctx_s::DeferredStream d = c->deferred_stream[slot];
   const auto t0 = std::chrono::steady_clock::now();
+  const auto all_published = [&] {
+    double other[2];
+    for (uint32_t o = 0; o < outputs; ++o)
+      if (!published(c, index, o, o == output ? mean_var : other)) return false;
+    return true;
+  };
   for (uint32_t spin = 1;; ++spin) {
-    if (published(c, index, output, mean_var)) return MRIP_OK;
+    if (all_published()) return MRIP_OK;
     if ((spin & 255) != 0) continue;
     bool over = false;
     if (d.used) {
@@ -202,7 +211,7 @@ mrip_status wait_stats(mrip_ctx c, uint64_t index, uint32_t output, double *mean
       over = true;
     }
     if (over) {
-      if (published(c, index, output, mean_var)) return MRIP_OK;
+      if (all_published()) return MRIP_OK;
       c->err = "a run's statistics were not published";
       return MRIP_E_HIP;
     }
@@ -884,7 +893,7 @@ mrip_status mrip_stats_back(mrip_ctx ctx, uint32_t back, uint32_t output, double
     if (st != MRIP_OK) return st;
   }
   double nmv[3] = {(double)ctx->stats_n[slot]};
-  mrip_status st = wait_stats(ctx, idx, output, nmv + 1);
+  mrip_status st = wait_stats(ctx, idx, scalar_outputs(ctx), output, nmv + 1);
   if (st != MRIP_OK) return st;
   st = finish_stats(nmv, confidence, out);
   if (st == MRIP_E_TOO_FEW) ctx->err = "fewer than two replications";

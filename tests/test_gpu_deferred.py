@@ -136,3 +136,22 @@ def test_outputs_are_there_when_the_call_returns(gpu, own_stream):
     reader.synchronize()
     assert np.array_equal(got.cpu().numpy(), ctx.output(0).cpu().numpy())
     assert bool((got > 0).all())
+
+
+def test_statistics_wait_for_the_reduction_of_every_output(gpu):
+    # the second output is bound to host memory, which is reduced slowly over
+    # the bus; once the first one's statistics are there, the caller overwrites
+    # it at once
+    announce("stats wait for all outputs")
+    R = 100000
+    ref = mrip.Context(mrip.MRIP_PI, mrip.pi_params(100), WAVE)
+    ref.run(R, seed=8)
+    want = [ref.stats(o) for o in range(2)]
+    ctx = mrip.Context(mrip.MRIP_PI, mrip.pi_params(100), WAVE)
+    estimate = torch.empty(R, dtype=torch.float32, pin_memory=True)
+    ctx.bind_output(1, estimate)
+    for _ in range(3):
+        ctx.run(R, seed=8)
+        first = ctx.stats(0)
+        estimate.zero_()
+        assert [first, ctx.stats(1)] == want
