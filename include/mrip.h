@@ -195,12 +195,13 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
  * and workgroup size (64, 256 or 1024) of the one-wavefront-per-replication
  * kernels, for runs and for plans (mrip_autotune later sets the plans'
  * alone). Outputs do not depend on it. Defaults 1 and 256. Other forms
- * have a size that the model fixes: the walk (16 lanes per walker up to 768
- * replications, then workgroups of 4 or 8 wavefronts; with walker_sites 16
- * lanes per walker up to 2048 replications, then this shape), pi from 4096 points (one or more workgroups of four
- * wavefronts per replication; on taus88 streams, below 4096 replications of
- * at least 65536 points, 2 to 16 wavefronts), and the forest fire (one to
- * eight wavefronts per replication). */
+ * have a size that the model fixes: the walk (16 lanes per walker, or, with
+ * many replications for its walkers or few moves, workgroups of 4 or 8
+ * wavefronts; with walker_sites 16 lanes per walker up to 2048 replications,
+ * then this shape), pi from 4096
+ * points (one or more workgroups of four wavefronts per replication; on
+ * taus88 streams, below 4096 replications of at least 65536 points, 2 to 16
+ * wavefronts), and the forest fire (one to eight wavefronts per replication). */
 MRIP_API mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t reps_per_wave, uint32_t workgroup);
 
 /* Wavefronts per replication for mrip_run on an M/M/1 WAVE context: 1, 2,

@@ -8,8 +8,8 @@
 // With few replications that form leaves the chip idle and each wave walks
 // its 1000 steps one after the other. The walk is a prefix sum of
 // independent moves, so rw_seg_kernel cuts every walker's steps into 16
-// segments, one lane each (a workgroup per replication): pass 1 counts a
-// segment's net displacement (popcounts of the move fields), a 16-lane
+// segments, one lane each: pass 1 counts a segment's net displacement
+// (popcounts of the move fields), a 16-lane
 // exclusive scan gives each segment its start, and pass 2 replays the
 // segment from there, marking the sites. Both forms give identical outputs;
 // the launcher picks by the number of replications.
@@ -27,6 +27,8 @@
 // 2(t&15) of output w ceil(T/16) + (t>>4) of the replication's stream: each
 // walker reads a contiguous run, so a WAVE lane jumps to its walker's run and
 // a SIMT lane reads the stream in order, walker after walker.
+#include <algorithm>
+
 #include "device.hpp"
 #include "kernels.hpp"
 #include "taus.hpp"
@@ -626,31 +628,47 @@ __device__ __forceinline__ int segment_scan(int v, uint32_t sgi) {
   return v;
 }
 
-// One workgroup per replication, 16 lanes per walker; pass 2 marks the sites
-// in the byte map (slot 0).
-template <int GRID, int RNG>
-__global__ __launch_bounds__(1024) void rw_seg_kernel(RwArgs a, uint32_t seg) {
+// 16 lanes per walker, pass 2 marks the sites in the byte map. A workgroup
+// takes `reps` replications of `threads` threads (whole wavefronts) each, one
+// per map slot: the map fills the LDS of half a compute unit, so with few
+// walkers a replication to a workgroup would leave most of it idle (4 walkers
+// x 1000 steps, 600 replications: 12.2 us, 8.6 with several and their counting
+// shared by idle wavefronts).
+template <int GRID, int RNG, bool ONE>
+__global__ __launch_bounds__(1024) void rw_seg_kernel(RwArgs a, uint32_t seg, uint32_t threads,
+                                                      uint32_t reps) {
   using S = SiteMap<GRID>;
   __shared__ __attribute__((aligned(16))) uint8_t map[65536];
-  __shared__ int sh_red[16];
+  __shared__ int sh_sd[16], sh_cnt[4][16];
   const int tid = threadIdx.x;
-  const uint32_t w = (uint32_t)tid >> 4, sgi = (uint32_t)tid & 15u;
-  const uint32_t rep = (uint32_t)(a.rep0 + blockIdx.x);
+  // wave-uniform: the slot's replication and this thread's place in it
+  if (ONE) {  // one replication to a workgroup
+    threads = blockDim.x;
+    reps = 1;
+  }
+  const uint32_t slot =
+      ONE ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)tid / threads));
+  const uint32_t t = (uint32_t)tid - slot * threads;
+  const uint64_t r = slot < reps ? (uint64_t)blockIdx.x * reps + slot : a.n_reps;
+  const uint32_t w = t >> 4, sgi = t & 15u;
+  const uint32_t rep = (uint32_t)(a.rep0 + r);
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  for (int v = tid; v < 16 * S::TORUS; v += blockDim.x)  // slot 0's rows
-    *(uint4 *)(map + ((v >> 4) << (S::SH + 8)) + 16 * (v & 15)) = uint4{0u, 0u, 0u, 0u};
+  // the rows of the slots in use (1 + LOW of them share rows)
+  for (uint32_t b = 0; b < (reps + S::LOW) >> S::SH; ++b)
+    for (uint32_t v = tid; v < 16u * S::TORUS; v += blockDim.x)
+      *(uint4 *)(map + (((v >> 4) << S::SH | b) << 8) + 16 * (v & 15)) = uint4{0u, 0u, 0u, 0u};
   __syncthreads();
-  const bool active = w < a.walkers;
-  const uint32_t t0 = min(a.steps, sgi * seg), t1 = min(a.steps, t0 + seg);
+  const bool active = w < a.walkers && r < a.n_reps;
+  const uint32_t t0 = min(a.steps, sgi * seg), t1 = active ? min(a.steps, t0 + seg) : t0;
   const Segment s1 = segment_pass1<RNG>(a, rep, w, sgi, t0, t1, k0, k1);
   const int sx = segment_scan(s1.dx, sgi), sy = segment_scan(s1.dy, sgi);
   if (active) {
     int x0, y0;
     start_site(w, GRID, x0, y0);
-    if (sgi == 0) map[map_address(S::byte0(x0, 0), S::byte1(y0, 0))] = 1;
+    if (sgi == 0) map[map_address(S::byte0(x0, slot), S::byte1(y0, slot))] = 1;
     // pass 2: the segment's moves from its (unwrapped) start
-    int X = S::byte0(x0 + sx - s1.dx, 0);
-    int Y = S::byte1(y0 + sy - s1.dy, 0);
+    int X = S::byte0(x0 + sx - s1.dx, slot);
+    int Y = S::byte1(y0 + sy - s1.dy, slot);
     if (t0 < t1) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -666,12 +684,25 @@ __global__ __launch_bounds__(1024) void rw_seg_kernel(RwArgs a, uint32_t seg) {
   }
   __syncthreads();
   // the walkers' squared end displacements (the last segment's lane holds the
-  // walker's total) and the marked sites
-  const int sd = block_sum_i((active && sgi == 15) ? sx * sx + sy * sy : 0, sh_red);
-  const int cnt = block_sum_i(count_sites<GRID>(map, 0, tid, blockDim.x), sh_red);
-  if (tid == 0) {
-    a.ssd[blockIdx.x] = sd;
-    a.distinct[blockIdx.x] = cnt;
+  // walker's total) and the marked sites: each replication's threads count
+  // its own, or, if some wavefronts have none, all threads count all
+  const int sd = group_sum_i((active && sgi == 15) ? sx * sx + sy * sy : 0, 64);
+  const bool own = ONE || threads * reps == blockDim.x;
+  for (uint32_t i = own ? slot : 0u; i < (own ? slot + 1 : reps); ++i) {
+    const int cnt = group_sum_i(count_sites<GRID>(map, i, own ? (int)t : tid,
+                                                  own ? (int)threads : (int)blockDim.x), 64);
+    if ((tid & 63) == 0) sh_cnt[own ? 0 : i][tid >> 6] = cnt;
+  }
+  if ((tid & 63) == 0) sh_sd[tid >> 6] = sd;
+  __syncthreads();
+  if (t == 0 && r < a.n_reps) {
+    int all = 0, sites = 0;
+    const uint32_t first = (uint32_t)tid >> 6, last = first + threads / 64;
+    for (uint32_t i = first; i < last; ++i) all += sh_sd[i];
+    for (uint32_t i = own ? first : 0u; i < (own ? last : blockDim.x / 64); ++i)
+      sites += sh_cnt[own ? 0 : slot][i];
+    a.ssd[r] = all;
+    a.distinct[r] = sites;
   }
 }
 
@@ -739,13 +770,31 @@ __global__ __launch_bounds__(1024) void rw_seg_sites_kernel(RwArgs a, uint32_t s
   }
 }
 
-// Replications up to which the segmented form is used: below, one wavefront
-// per replication leaves the chip idle; above, its single pass over the moves
-// is cheaper (64 walkers x 1000 steps, segmented / one wavefront: 32
-// replications 10.2 / 22 us, 512 16 / 22, 700 20.4 / 22.6, 1024 25 / 22.5; on
-// taus88 streams every segment lane first jumps to its place, two tables of
-// 88 columns: 256 replications 26.0 / 26.7 us, 400 39 / 27).
-constexpr uint64_t RW_SEG_MAX_REPS = 768, RW_SEG_MAX_REPS_TAUS88 = 256;
+// Whether the segmented form is used, for walkers that take `waves`
+// wavefronts per replication in it (16 lanes a walker). Up to 512
+// replications (256 on taus88 streams, whose segment lanes jump to their
+// place first, two tables of 88 columns) its own time is all there is, and
+// only short walks are over before it. Beyond, a replication's share of the
+// chip grows with its walkers, while the sequential forms take one wavefront
+// whatever their number: up to four wavefronts the segmented form wins at any
+// number of replications from some hundred moves on, with more only while
+// they are few in all. Kernel times on 64 x 64, segmented / sequential (us), by
+// walkers x moves: 64 x 1000, 300 replications 14.7 / 21.3, 768 20 / 21, 1000
+// 24.6 / 21.2; 64 x 100, 300 14.7 / 7.4; 35 x 1000, 1000 17.4 / 21.2, 2000
+// 28.8 / 26.5; 16 x 1000, 1000 11.1 / 21.4, 12288 62 / 110; 16 x 256, 600 9.6 /
+// 9.2, 12288 49 / 37; 4 x 1000, 1000 8.5 / 36, 12288 24 / 117; 4 x 128, 1000
+// 9.2 / 8.6; 4 x 64, 300 8.3 / 7.4. taus88: 16 x 600, 300 16.4 / 18.9, 1000
+// 24.3 / 19.4; 16 x 3000, 4096 93 / 127; 4 x 256, 1000 15.5 / 17.0, 4096
+// 24.5 / 21.7; 4 x 600, 4096 25.7 / 38.
+bool use_segments(uint32_t waves, uint64_t n_reps, uint32_t steps, bool taus) {
+  if (taus) {
+    if (n_reps <= 256) return steps >= std::min(256u, 100u * waves);
+    return n_reps <= 512 ? steps >= 128u * waves : waves <= 4 && steps >= 512u * waves;
+  }
+  if (n_reps <= 512) return steps >= std::min(160u, 40u * waves);
+  return (waves <= 4 || n_reps * waves <= 12288u) &&
+         steps >= std::min(1000u, 132u + 12u * waves * waves);
+}
 // ... and with per-walker site counts (1000 steps: 44 / 83 us at 1024
 // replications, 79 / 87 at 2048, 149 / 146 at 4096; taus88 57 / 56 at 512).
 constexpr uint64_t RW_SITES_SEG_MAX_REPS = 2048, RW_SITES_SEG_MAX_REPS_TAUS88 = 512;
@@ -785,33 +834,7 @@ hipError_t pair_launch(const RwArgs &a, hipStream_t s) {
 }
 
 template <int GRID>
-hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
-  const bool sites = a.walker_sites != nullptr, taus = a.rng == RNG_TAUS88;
-  const uint64_t seg_max =
-      sites ? (taus ? RW_SITES_SEG_MAX_REPS_TAUS88 : RW_SITES_SEG_MAX_REPS)
-            : (taus ? RW_SEG_MAX_REPS_TAUS88 : RW_SEG_MAX_REPS);
-  if (a.n_reps <= seg_max) {
-    // 16 lanes per walker; segments of whole Philox blocks (64 moves)
-    const uint32_t threads = (16u * a.walkers + 63u) / 64u * 64u;
-    const uint32_t seg = (a.steps + 16u * 64u - 1u) / (16u * 64u) * 64u;
-    const dim3 g((uint32_t)a.n_reps), b(threads);
-    if (a.rng == RNG_TAUS88) {
-      if (sites) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
-      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
-    } else {
-      if (sites) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
-      else hipLaunchKernelGGL((rw_seg_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
-    }
-    return hipGetLastError();
-  }
-  if (!sites) {
-    if constexpr (GRID < 128) {
-      if (a.n_reps >= RW_PAIR_MIN_REPS && a.steps >= RW_PAIR_MIN_STEPS)
-        return pair_launch<GRID>(a, s);
-      if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
-    }
-    return map_launch<GRID, 4>(a, s);
-  }
+hipError_t sites_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   const uint32_t wpb = wg / 64;
   const uint64_t blocks = (a.n_reps + wpb - 1) / wpb;
   const size_t lds = ((size_t)wpb * (GRID * GRID / 32) + 1) * sizeof(uint32_t);  // + spare
@@ -821,6 +844,42 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   else
     hipLaunchKernelGGL((rw_sites_kernel<GRID, RNG_PHILOX>), g, b, lds, s, a);
   return hipGetLastError();
+}
+
+template <int GRID>
+hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
+  const bool sites = a.walker_sites != nullptr, taus = a.rng == RNG_TAUS88;
+  // 16 lanes per walker; segments of whole Philox blocks (64 moves)
+  const uint32_t threads = (16u * a.walkers + 63u) / 64u * 64u;
+  const uint32_t seg = (a.steps + 16u * 64u - 1u) / (16u * 64u) * 64u;
+  if (sites) {
+    if (a.n_reps > (taus ? RW_SITES_SEG_MAX_REPS_TAUS88 : RW_SITES_SEG_MAX_REPS))
+      return sites_launch<GRID>(a, wg, s);
+    const dim3 g((uint32_t)a.n_reps), b(threads);
+    if (taus) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
+    else hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
+    return hipGetLastError();
+  }
+  const uint32_t waves = threads / 64;
+  if (use_segments(waves, a.n_reps, a.steps, taus)) {
+    // a workgroup's replications: as many as put two workgroups on each of 256
+    // compute units, and fit; one alone has its map cleared by four wavefronts
+    const uint32_t most = std::min<uint32_t>(1024u / threads, SiteMap<GRID>::REPS);
+    const uint32_t reps = (uint32_t)std::min<uint64_t>(most, (a.n_reps + 511) / 512);
+    const dim3 g((uint32_t)((a.n_reps + reps - 1) / reps));
+    const dim3 b(std::max(threads * reps, 256u));
+#define MRIP_SEG(RN, ONE) \
+  hipLaunchKernelGGL((rw_seg_kernel<GRID, RN, ONE>), g, b, 0, s, a, seg, threads, reps)
+    if (taus) { if (reps == 1) MRIP_SEG(RNG_TAUS88, true); else MRIP_SEG(RNG_TAUS88, false); }
+    else { if (reps == 1) MRIP_SEG(RNG_PHILOX, true); else MRIP_SEG(RNG_PHILOX, false); }
+#undef MRIP_SEG
+    return hipGetLastError();
+  }
+  if constexpr (GRID < 128) {
+    if (a.n_reps >= RW_PAIR_MIN_REPS && a.steps >= RW_PAIR_MIN_STEPS) return pair_launch<GRID>(a, s);
+    if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
+  }
+  return map_launch<GRID, 4>(a, s);
 }
 
 template <int GRID>

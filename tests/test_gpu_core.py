@@ -252,3 +252,51 @@ def test_walk_marked_by_pairs_bit_exact(gpu, grid, walkers, steps, R, rng):
     essd, edist = core.rw_many(21, ids, walkers, grid, steps, rng=rng)
     assert np.array_equal(ctx.output(0).cpu().numpy()[ids], essd)
     assert np.array_equal(ctx.output(1).cpu().numpy()[ids], edist)
+
+
+def _rw(W, G, T, R, rng, seed):
+    ctx = mrip.Context(mrip.MRIP_RW, mrip.rw_params(W, G, T), WAVE)
+    if rng == "taus88":
+        ctx.set_rng(mrip.MRIP_RNG_TAUS88)
+    ctx.run(R, seed=seed)
+    return [ctx.output(o).cpu().numpy() for o in range(2)]
+
+
+@pytest.mark.parametrize("W,G,T,R,rng", [
+    (64, 64, 1000, 768, "philox"), (64, 64, 160, 512, "philox"), (64, 16, 1500, 768, "philox"),
+    (35, 128, 1000, 1365, "philox"), (7, 32, 179, 512, "philox"), (64, 64, 400, 256, "taus88"),
+    (33, 128, 1300, 512, "taus88"), (4, 64, 128, 512, "taus88")])
+def test_walk_segments_agree_with_walks_in_order(gpu, W, G, T, R, rng):
+    # R replications take the segmented form, R + 1 the sequential one: every
+    # output of the first R
+    announce("rw segments against order", W, G, T, R, rng)
+    a, b = _rw(W, G, T, R, rng, 9), _rw(W, G, T, R + 1, rng, 9)
+    for o in range(2):
+        assert np.array_equal(a[o], b[o][:R])
+
+
+@pytest.mark.parametrize("W,T", [(1, 144), (4, 144), (8, 180), (12, 240), (16, 324), (20, 432),
+                                 (64, 160)])
+def test_walk_segments_from_so_many_moves_on(gpu, W, T):
+    # both sides of the line in moves against the oracle
+    announce("rw segment line", W, T)
+    R = 512 if W == 64 else 600
+    ids = [0, 1, R // 2, R - 1]
+    for steps in (T - 1, T):
+        got = _rw(W, 64, steps, R, "philox", 10)
+        ssd, dist = core.rw_many(10, ids, W, 64, steps)
+        assert np.array_equal(got[0][ids], ssd) and np.array_equal(got[1][ids], dist)
+
+
+@pytest.mark.parametrize("W,R", [(1, 513), (4, 1537), (4, 8191), (5, 513), (8, 4096), (9, 1000),
+                                 (12, 2049), (13, 700), (16, 2047), (16, 513), (21, 1500)])
+@pytest.mark.parametrize("G,T", [(16, 460), (64, 1025), (128, 4100)])
+@pytest.mark.parametrize("rng", ["philox", "taus88"])
+def test_walk_segments_of_several_replications_per_workgroup(gpu, W, R, G, T, rng):
+    # two to sixteen replications in a workgroup's map, wavefronts without one,
+    # and a last workgroup that is not full
+    announce("rw segments, several replications", W, R, G, T, rng)
+    got = _rw(W, G, T, R, rng, 12)
+    ids = sorted({*range(17), R // 2, *range(R - 17, R)})
+    ssd, dist = core.rw_many(12, ids, W, G, T, rng=rng, threads=core.default_threads())
+    assert np.array_equal(got[0][ids], ssd) and np.array_equal(got[1][ids], dist)
