@@ -198,7 +198,7 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
  * have a size that the model fixes: the walk (16 lanes per walker, or, with
  * many replications for its walkers or few moves, workgroups of 4 or 8
  * wavefronts; with walker_sites 16 lanes per walker up to 2048 replications,
- * then this shape), pi from 4096
+ * then this shape, as for many replications of very few moves), pi from 4096
  * points (one or more workgroups of four wavefronts per replication; on
  * taus88 streams, below 4096 replications of at least 65536 points, 2 to 16
  * wavefronts), and the forest fire (one to eight wavefronts per replication). */

@@ -16,7 +16,8 @@
 //
 // Optionally every walker also marks a bitmap of its own, in global memory,
 // and output 2 is the sum over walkers of their popcounts; those forms
-// (rw_sites_kernel, rw_seg_sites_kernel) keep the union as a bitmap in LDS.
+// (rw_bits_kernel, rw_seg_sites_kernel) keep the union as a bitmap in LDS, as
+// many short walks do (short_walks).
 //
 // SIMT mapping: one replication per lane; the lane walks its walkers one
 // after the other and keeps the replication's bitmap in global memory, the
@@ -432,65 +433,104 @@ __global__ __launch_bounds__(64 * PairMap::REPS) void rw_pair_kernel(RwArgs a) {
   }
 }
 
-// The walk with per-walker site counts: the union's bitmap (grid^2 bits) in
-// LDS, set with atomic ors, and a bitmap of its own per walker in global
-// memory.
-template <int GRID, int RNG>
-__global__ void rw_sites_kernel(RwArgs a) {
+// One replication per wavefront on a bitmap of the visited sites (grid^2
+// bits) in LDS, set with atomic ors. PW: with per-walker site counts, a bitmap
+// of its own per walker in global memory. Without, the form of short walks
+// (short_walks): a walk clears and counts 2 KiB at most, not its share of the
+// byte map's 64. Vector instructions bound it (some 12 a move).
+template <int GRID, int RNG, bool PW>
+__global__ __launch_bounds__(1024) void rw_bits_kernel(RwArgs a) {
   constexpr int WORDS = GRID * GRID / 32;
-  constexpr int WB = WB_OWN;
+  constexpr int LOG_ROWB = GRID == 16 ? 1 : GRID == 32 ? 2 : GRID == 64 ? 3 : 4, ROWB = 1 << LOG_ROWB;
+  constexpr int WB = PW ? WB_OWN : WB_NONE;
   extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t r = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   uint32_t *bm = lds + wave * WORDS;
+  // in bytes; a power of two apart, so a word's address in the map is or-ed in
+  const uint32_t base = (uint32_t)wave * (4 * WORDS);
   for (int i = lane; i < WORDS; i += 64) bm[i] = 0u;
   __syncthreads();
 
   const bool active = r < a.n_reps && (uint32_t)lane < a.walkers;
   const uint32_t w = (uint32_t)lane;
-  const int x0 = (int)(((w % 8u) * (GRID / 8) + GRID / 16) % GRID);
-  const int y0 = (int)(((w / 8u) * (GRID / 8) + GRID / 16) % GRID);
-  int X = x0, Y = y0;
-  uint32_t *spare = lds + (blockDim.x >> 6) * WORDS;
-  if (active) mark(bm, y0 * GRID + x0);
-  // this walker's own bitmap (global memory, owned by this lane)
-  uint32_t *wb = nullptr;
+  int sd = 0, mine = 0;
   if (active) {
-    wb = a.walker_bitmaps + (r * a.walkers + w) * WORDS;
-    for (int i = 0; i < WORDS; ++i) wb[i] = 0u;
-    mark_walker<WB>(wb, y0 * GRID + x0, true);
-  }
-
-  if (RNG == RNG_TAUS88) {
-    Taus t = taus_seed(TAG_RW, 0u, (uint32_t)(a.rep0 + r), k0, k1);
-    taus_jump(t, a.taus_walk + (uint64_t)w * TAUS_COLS);  // to walker w's run
-    for (uint32_t g = 0; g < a.steps; g += 16)
-      walk16<GRID, true, WB>(taus_next(t), g, a.steps, active, X, Y, bm, spare, wb);
-  } else {
-    for (uint32_t g = 0; g < a.steps; g += 64) {
-      const Block4 b = philox(g >> 6, w, (uint32_t)(a.rep0 + r), TAG_RW, k0, k1);
-      walk16<GRID, true, WB>(b.x, g, a.steps, active, X, Y, bm, spare, wb);
-      walk16<GRID, true, WB>(b.y, g + 16, a.steps, active, X, Y, bm, spare, wb);
-      walk16<GRID, true, WB>(b.z, g + 32, a.steps, active, X, Y, bm, spare, wb);
-      walk16<GRID, true, WB>(b.w, g + 48, a.steps, active, X, Y, bm, spare, wb);
+    int x0, y0;
+    start_site(w, GRID, x0, y0);
+    int X = x0;
+    // this walker's own bitmap (global memory, owned by this lane)
+    uint32_t *wb = nullptr;
+    if (PW) {
+      wb = a.walker_bitmaps + (r * a.walkers + w) * WORDS;
+      for (int i = 0; i < WORDS; ++i) wb[i] = 0u;
+      mark_walker<WB>(wb, y0 * GRID + x0, true);
     }
+    // YB is Y in bytes of a row; the word that holds the walker's site, in
+    // bytes, and the bits of it visited since the walker entered it: they reach
+    // LDS when it leaves, which half the moves do not (x moves stay in a word
+    // 31 times in 32)
+    int YB = y0 * ROWB;
+    const auto word_at = [&] {
+      return (((uint32_t)YB & (uint32_t)(GRID * ROWB - 1) & ~(uint32_t)(ROWB - 1) & ~3u) | base) |
+             (GRID > 32 ? __builtin_amdgcn_ubfe((uint32_t)X, 5, GRID == 128 ? 2 : 1) << 2 : 0u);
+    };
+    const auto bit = [&] {
+      return 1u << (GRID > 16 ? (uint32_t)X & 31u : ((uint32_t)YB & 2u) << 3 | ((uint32_t)X & 15u));
+    };
+    uint32_t at = word_at(), bits = bit();
+    const auto flush = [&] { atomicOr((uint32_t *)((char *)lds + at), bits); };
+    const auto move = [&](int dx, int dy) {
+      X += dx;
+      YB += dy * ROWB;
+      const uint32_t now = word_at();
+      if (now != at) {
+        flush();
+        bits = 0u;
+      }
+      at = now;
+      bits |= bit();
+      if (PW) mark_walker<WB>(wb, ((YB >> LOG_ROWB) & (GRID - 1)) * GRID + (X & (GRID - 1)), true);
+    };
+    const auto walk = [&](uint32_t word, uint32_t n) {
+      // the moves' dx and dy as 2-bit fields, each one extract away
+      constexpr uint32_t M = 0x55555555u;
+      const uint32_t lo = word & M, hi = (word >> 1) & M;
+      const int DX = (int)((hi ^ M) | (lo & ~hi) << 1), DY = (int)(hi | (hi & lo) << 1);
+      if (n >= 16u) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          move(__builtin_amdgcn_sbfe(DX, 2 * i, 2), __builtin_amdgcn_sbfe(DY, 2 * i, 2));
+      } else {
+        for (uint32_t i = 0; i < n; ++i)
+          move(__builtin_amdgcn_sbfe(DX, 2 * i, 2), __builtin_amdgcn_sbfe(DY, 2 * i, 2));
+      }
+    };
+    const uint32_t rep = (uint32_t)(a.rep0 + r);
+    if (RNG == RNG_TAUS88) {
+      Taus t = taus_seed(TAG_RW, 0u, rep, k0, k1);
+      taus_jump(t, a.taus_walk + (uint64_t)w * TAUS_COLS);  // to walker w's run
+      for (uint32_t g = 0; g < a.steps; g += 16) walk(taus_next(t), a.steps - g);
+    } else {
+      each_word(0u, a.steps, w, rep, k0, k1, walk);
+    }
+    flush();
+    const int ux = X - x0, uy = (YB >> LOG_ROWB) - y0;
+    sd = ux * ux + uy * uy;
+    if (PW)
+      for (int i = 0; i < WORDS; ++i) mine += __popc(wb[i]);
   }
   __syncthreads();
   int cnt = 0;
   for (int i = lane; i < WORDS; i += 64) cnt += __popc(bm[i]);
   cnt = group_sum_i(cnt, 64);
-  const int ux = X - x0, uy = Y - y0;
-  const int sd = active ? ux * ux + uy * uy : 0;
   const int ssd = group_sum_i(sd, 64);
-  int mine = 0;
-  if (active)
-    for (int i = 0; i < WORDS; ++i) mine += __popc(wb[i]);
-  mine = group_sum_i(mine, 64);
+  if (PW) mine = group_sum_i(mine, 64);
   if (lane == 0 && r < a.n_reps) {
     a.ssd[r] = ssd;
     a.distinct[r] = cnt;
-    a.walker_sites[r] = mine;
+    if (PW) a.walker_sites[r] = mine;
   }
 }
 
@@ -804,6 +844,19 @@ constexpr uint64_t RW_SITES_SEG_MAX_REPS = 2048, RW_SITES_SEG_MAX_REPS_TAUS88 = 
 // compute unit's LDS, so eight keep more wavefronts on it (8192: 111 / 107).
 constexpr uint64_t RW_MAP8_MIN_REPS = 4096;
 
+// Moves up to which many replications walk on a bitmap: clearing and counting
+// the byte map is most of a short walk's time, the more the larger the torus
+// (of 128 x 128 four fill the map). Bitmap / byte map, 64 walkers (us):
+// 64 x 64, 12288 replications of 10 moves 10.3 / 14.5, of 32 15.2 / 16.7, of 48
+// 18.8 / 19.0, of 64 22.7 / 20.6; 4096 of 24 7.6 / 7.7, of 48 10.7 / 9.7; 128 x
+// 128, 12288 of 10 10.5 / 25.7, of 100 31.5 / 38, of 128 38 / 39; 16 x 16, 40000
+// of 10 22 / 46, of 48 53 / 60.
+template <int GRID>
+bool short_walks(uint64_t n_reps, uint32_t steps) {
+  if (n_reps < 2000) return false;
+  return n_reps < 8192 ? steps <= (GRID == 128 ? 80 : 24) : steps <= (GRID == 128 ? 120 : 48);
+}
+
 template <int GRID, int WAVES>
 hipError_t map_launch(const RwArgs &a, hipStream_t s) {
   const dim3 g((uint32_t)((a.n_reps + WAVES - 1) / WAVES)), b(64 * WAVES);
@@ -833,16 +886,16 @@ hipError_t pair_launch(const RwArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int GRID>
-hipError_t sites_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
+template <int GRID, bool PW>
+hipError_t bits_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   const uint32_t wpb = wg / 64;
   const uint64_t blocks = (a.n_reps + wpb - 1) / wpb;
-  const size_t lds = ((size_t)wpb * (GRID * GRID / 32) + 1) * sizeof(uint32_t);  // + spare
+  const size_t lds = (size_t)wpb * (GRID * GRID / 32) * sizeof(uint32_t);
   const dim3 g((uint32_t)blocks), b(wg);
   if (a.rng == RNG_TAUS88)
-    hipLaunchKernelGGL((rw_sites_kernel<GRID, RNG_TAUS88>), g, b, lds, s, a);
+    hipLaunchKernelGGL((rw_bits_kernel<GRID, RNG_TAUS88, PW>), g, b, lds, s, a);
   else
-    hipLaunchKernelGGL((rw_sites_kernel<GRID, RNG_PHILOX>), g, b, lds, s, a);
+    hipLaunchKernelGGL((rw_bits_kernel<GRID, RNG_PHILOX, PW>), g, b, lds, s, a);
   return hipGetLastError();
 }
 
@@ -854,7 +907,7 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   const uint32_t seg = (a.steps + 16u * 64u - 1u) / (16u * 64u) * 64u;
   if (sites) {
     if (a.n_reps > (taus ? RW_SITES_SEG_MAX_REPS_TAUS88 : RW_SITES_SEG_MAX_REPS))
-      return sites_launch<GRID>(a, wg, s);
+      return bits_launch<GRID, true>(a, wg, s);
     const dim3 g((uint32_t)a.n_reps), b(threads);
     if (taus) hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_TAUS88>), g, b, 0, s, a, seg);
     else hipLaunchKernelGGL((rw_seg_sites_kernel<GRID, RNG_PHILOX>), g, b, 0, s, a, seg);
@@ -875,6 +928,7 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
 #undef MRIP_SEG
     return hipGetLastError();
   }
+  if (short_walks<GRID>(a.n_reps, a.steps)) return bits_launch<GRID, false>(a, wg, s);
   if constexpr (GRID < 128) {
     if (a.n_reps >= RW_PAIR_MIN_REPS && a.steps >= RW_PAIR_MIN_STEPS) return pair_launch<GRID>(a, s);
     if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);

@@ -300,3 +300,22 @@ def test_walk_segments_of_several_replications_per_workgroup(gpu, W, R, G, T, rn
     ids = sorted({*range(17), R // 2, *range(R - 17, R)})
     ssd, dist = core.rw_many(12, ids, W, G, T, rng=rng, threads=core.default_threads())
     assert np.array_equal(got[0][ids], ssd) and np.array_equal(got[1][ids], dist)
+
+
+@pytest.mark.parametrize("G,T,R", [
+    (16, 24, 2000), (32, 25, 2001), (64, 0, 2000), (64, 1, 2003), (64, 17, 2000), (64, 48, 8192),
+    (64, 49, 8192), (16, 47, 8195), (128, 80, 2000), (128, 81, 2001), (128, 120, 8192),
+    (128, 65, 8193)])
+@pytest.mark.parametrize("W", [1, 33, 64])
+@pytest.mark.parametrize("rng", ["philox", "taus88"])
+def test_short_walks_bit_exact(gpu, G, T, R, W, rng):
+    # many short walks mark a bitmap: both sides of the lines in moves, walks
+    # that end inside a word or a block, and a last workgroup that is not full;
+    # the first 900 replications alone walk on the byte map
+    announce("rw short walks", G, T, R, W, rng)
+    got, few = _rw(W, G, T, R, rng, 13), _rw(W, G, T, 900, rng, 13)
+    ids = sorted({0, 1, 2, 3, R // 2, R - 2, R - 1})
+    ssd, dist = core.rw_many(13, ids, W, G, T, rng=rng)
+    assert np.array_equal(got[0][ids], ssd) and np.array_equal(got[1][ids], dist)
+    for o in range(2):
+        assert np.array_equal(got[o][:900], few[o])
