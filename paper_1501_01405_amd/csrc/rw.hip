@@ -867,14 +867,16 @@ hipError_t map_launch(const RwArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Replications and moves from which two moves are marked by one store:
-// counting the sites costs more there (16384 replications on 64 x 64: 100
-// moves 31.5 us with a store per move, 35.2 with one per two; 150 41 / 41;
-// 200 50 / 47; 300 69 / 59; 1000 205 / 145), and with few replications latency
-// bounds the walk, not the stores (1024 of 1000 moves 21.5 / 22.0; 2000 of
-// 400 17.8 / 15.6; 3000 of 200 16.0 / 16.4).
+// Replications, and moves of all a replication's walkers, from which two
+// moves are marked by one store: counting the sites costs more there, whatever
+// the walkers (16384 replications of 64 walkers on 64 x 64: 100 moves 31.5 us
+// with a store per move, 35.2 with one per two; 150 41 / 41; 200 50 / 47; 300
+// 69 / 59; 1000 205 / 145; 12288 of 35 walkers: 256 moves 39 / 42, 600 76 / 75,
+// 1000 117 / 112), and with few replications latency bounds the walk, not the
+// stores (1024 of 1000 moves 21.5 / 22.0; 2000 of 400 17.8 / 15.6; 3000 of 200
+// 16.0 / 16.4).
 constexpr uint64_t RW_PAIR_MIN_REPS = 2000;
-constexpr uint32_t RW_PAIR_MIN_STEPS = 256;
+constexpr uint64_t RW_PAIR_MIN_MOVES = 64 * 256;  // a replication's, over all walkers
 
 template <int GRID>
 hipError_t pair_launch(const RwArgs &a, hipStream_t s) {
@@ -930,7 +932,7 @@ hipError_t wave_launch(const RwArgs &a, uint32_t wg, hipStream_t s) {
   }
   if (short_walks<GRID>(a.n_reps, a.steps)) return bits_launch<GRID, false>(a, wg, s);
   if constexpr (GRID < 128) {
-    if (a.n_reps >= RW_PAIR_MIN_REPS && a.steps >= RW_PAIR_MIN_STEPS) return pair_launch<GRID>(a, s);
+    if (a.n_reps >= RW_PAIR_MIN_REPS && (uint64_t)a.steps * a.walkers >= RW_PAIR_MIN_MOVES) return pair_launch<GRID>(a, s);
     if (a.n_reps >= RW_MAP8_MIN_REPS) return map_launch<GRID, 8>(a, s);
   }
   return map_launch<GRID, 4>(a, s);

@@ -319,3 +319,15 @@ def test_short_walks_bit_exact(gpu, G, T, R, W, rng):
     assert np.array_equal(got[0][ids], ssd) and np.array_equal(got[1][ids], dist)
     for o in range(2):
         assert np.array_equal(got[o][:900], few[o])
+
+
+@pytest.mark.parametrize("G,W,T,R", [(64, 64, 256, 2000), (64, 35, 469, 2001), (32, 17, 964, 3000),
+                                     (16, 64, 257, 2007)])
+@pytest.mark.parametrize("rng", ["philox", "taus88"])
+def test_walk_pairs_agree_with_a_store_per_move(gpu, G, W, T, R, rng):
+    # R replications are marked two moves a store, the first 1999 of them alone
+    # a move a store: from 16384 moves over all the walkers
+    announce("rw pairs against moves", G, W, T, R, rng)
+    a, b = _rw(W, G, T, R, rng, 14), _rw(W, G, T, 1999, rng, 14)
+    for o in range(2):
+        assert np.array_equal(a[o][:1999], b[o])
