@@ -366,10 +366,11 @@ MRIP_API mrip_status mrip_plan_stats(mrip_ctx ctx, uint32_t dp, double confidenc
  * (longest first) at raised wavefront priority, since the longest items set
  * the plan's makespan; the rest go reps_per_wave per wavefront. Until this
  * call (or mrip_autotune) fixes it, a plan chooses both by an estimate of
- * its longest item's time and of all its work's (a plan with features: items
- * of 65536 customers, the fewest wavefronts, up to 8, that bring the longest
- * item's share of its customers down to the average per wavefront the device
- * holds at once), the same in every run of the plan (stopped at an item
+ * its slowest item's time and of all its work's, from the items' lengths and
+ * loads (near critical load a split item's parts take long to meet). A plan
+ * with features takes items of 65536 customers as long and the fewest
+ * wavefronts, up to 8, that bring the longest item's share of its customers
+ * down to the average per wavefront the device holds at once. Either is the same in every run of the plan (stopped at an item
  * limit or resumed). Sums are fp64: however items are split, a mean moves by
  * the last bit of its fp32 value at most. */
 MRIP_API mrip_status mrip_set_plan_split(mrip_ctx ctx, uint32_t waves_per_item,

@@ -388,8 +388,8 @@ mrip_status validate(mrip_model model, const void *params, mrip_mapping map, std
 
 }  // namespace
 
-uint32_t mrip::plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total) {
-  if (ctx->plan_split_set) return ctx->plan_split;
+// Compute units of the device.
+static uint32_t device_cus(mrip_ctx ctx) {
   if (ctx->cus == 0) {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -398,9 +398,14 @@ uint32_t mrip::plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total) {
     else
       ctx->cus = 256;
   }
+  return ctx->cus;
+}
+
+uint32_t mrip::plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total) {
+  if (ctx->plan_split_set) return ctx->plan_split;
   // wavefronts the chip holds at once in the feature-free kernels: four
   // per SIMD, four SIMDs per compute unit
-  const uint64_t slots = 16ull * ctx->cus;
+  const uint64_t slots = 16ull * device_cus(ctx);
   uint32_t x = 1;
   while (x < ctx->plan_split && (double)longest * (double)slots > (double)total * x) x *= 2;
   return x;
@@ -960,6 +965,99 @@ mrip_status mrip_last_run_ms(mrip_ctx ctx, float *ms) {
 
 // ------------------------------------------------------------------ plan
 
+// Items of a longest-first order that count as long (a prefix of it).
+static uint64_t count_long(const std::vector<uint64_t> &lpt, uint64_t n, uint64_t long_min) {
+  return (uint64_t)(std::partition_point(lpt.begin(), lpt.begin() + (ptrdiff_t)n,
+                                         [&](uint64_t c) { return c >= long_min; }) -
+                    lpt.begin());
+}
+
+// How the uploaded plan's long items are split: decided on the whole plan, so
+// a run stopped at an item limit or resumed from saved outputs splits every
+// item as the uninterrupted run does and gives the same bits. Without
+// features every form gives the same means (fp64 sums, rounded once), and the
+// plan takes the one whose estimate is lowest (estimate_shape).
+static PlanShape plan_shape_of(mrip_ctx ctx) {
+  if (!ctx->plan_split_set && ctx->mm1.feature_prefix == 0) return ctx->plan_shape;
+  return {plan_split_for(ctx, ctx->items.max_customers, ctx->items.total_customers), ctx->long_min};
+}
+
+// Times in us. In chunks of 1024 customers (620 instructions): the longest
+// item alone takes 1.29 a chunk on one wavefront, 0.67, 0.333 and 0.269 on two,
+// four and eight (eight share the SIMDs of one compute unit); all of the work
+// takes 1.046 a chunk on one SIMD, 3 % and 13 % more split in two and eight,
+// and about 4 more per wavefront of each split item. Items are split from
+// 16384 customers, or from the length that unsplit takes half as long as the
+// longest does split (shorter ones cost more in overhead than they hold up),
+// into parts of two chunks and more of the longest.
+//
+// A split item's parts start from an empty system and are run again until
+// they meet their true trajectory, which takes until the queue has emptied:
+// 0.005 / (1 - rho)^2 each, twice that for the slowest one, while that is
+// short against a part. Above, the parts wait for one another, and where the
+// queue never empties all but the first are run again in turn, at 1.45 a chunk.
+// While they wait their wavefronts fill the chip: a correction costs 1.9, 2.8
+// and 4.2 times its length in work.
+//
+// The estimate is the root of the squares' sum of the slowest item and the
+// work. Over 46 plans of 4 to 80 design points of 20 to 40 replications, 1e3..1e4
+// to 3e4..1e6 customers, loads 0.5 to 0.95, the chosen form is 3 % slower than
+// the best of 27 tried on average (17 % at most), and 1.8 times as fast as eight
+// wavefronts for items of 65536 customers (0.988 at worst); 64 x 32 of 1e4 to
+// 1e6: 596 that way, 474 on four from 16384. Over 406 plans of 16 to 3000
+// equal items of 8000 to 1e6 customers at 14 loads from 0.5 to 1.2 it is 2 %
+// slower than the best of four, 14 % without the corrections' cost and up to
+// 3.7 times (900 items of 1e5 at load 1.1: 434, 145 with it).
+struct PlanEstimate {
+  static constexpr double CHUNK = 1.046, AGAIN = 1.45;
+  static constexpr double ALONE[4] = {1.29, 0.67, 0.333, 0.269}, MORE[4] = {1.0, 1.03, 1.0, 1.13},
+                          HELD[4] = {0.0, 1.9, 2.8, 4.2};
+  // the length that counts as long where the longest is split over 1 << k
+  static uint64_t long_min(uint64_t longest, int k) {
+    return std::max<uint64_t>(
+        1, std::min<uint64_t>(16384, (uint64_t)(0.5 * (double)longest * ALONE[k] / ALONE[0])));
+  }
+  // a part's correction until it meets its trajectory
+  static double meeting(float lambda, float mu) {
+    const double idle = std::max(1e-4, 1.0 - (double)lambda / (double)mu);
+    return 0.005 / (idle * idle);
+  }
+};
+
+// lpt: the items' customers, longest first; meeting: theirs in that order.
+static PlanShape estimate_shape(const std::vector<uint64_t> &lpt, const std::vector<double> &meeting,
+                                uint64_t total, uint32_t cus) {
+  using E = PlanEstimate;
+  const uint64_t n = lpt.size(), longest = lpt[0];
+  const double chunks = (double)total / 1024.0 + 0.5 * (double)n;
+  PlanShape best{1, 65536};
+  double best_time = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    const int waves = 1 << k;
+    if (k > 0 && (longest + 1023) / 1024 < 2u * waves) break;
+    const uint64_t long_min = E::long_min(longest, k);
+    const uint64_t n_split = k == 0 ? 0 : count_long(lpt, n, long_min);
+    double slowest = n_split < n ? std::ceil((double)lpt[n_split] / 1024.0) * E::ALONE[0] : 0.0;
+    double corrections = 0.0;
+    for (uint64_t j = 0; j < n_split; ++j) {
+      const double len = std::ceil((double)lpt[j] / 1024.0);
+      const double most = E::AGAIN * len * (waves - 1) / waves;  // every part but the first again
+      const double one = meeting[j], two = 2.0 * one;
+      const double slow = two * 20.0 < most ? two : most * two / (most + two);
+      corrections += one * 20.0 < most ? one : most * one / (most + one);
+      slowest = std::max(slowest, len * E::ALONE[k] + slow);
+    }
+    const double work = (chunks * E::CHUNK * E::MORE[k] + 4.0 * waves * (double)n_split +
+                         E::HELD[k] * corrections) / (4.0 * cus);
+    const double time = std::sqrt(work * work + slowest * slowest);
+    if (k == 0 || time < best_time) {
+      best_time = time;
+      if (k > 0) best = {(uint32_t)waves, long_min};
+    }
+  }
+  return best;
+}
+
 mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n) {
   if (!ctx) return MRIP_E_INVAL;
   if (philox_only(ctx) != MRIP_OK) return MRIP_E_UNSUPPORTED;
@@ -984,65 +1082,15 @@ mrip_status mrip_plan_set(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n)
   ctx->dp_ids = b.dp_ids;
   ctx->lpt_order = b.order_host;
   ctx->lpt_customers.resize(n);
-  for (uint64_t j = 0; j < n; ++j) ctx->lpt_customers[j] = items[b.order_host[j]].customers;
+  std::vector<double> meeting(n);
+  for (uint64_t j = 0; j < n; ++j) {
+    const mrip_plan_item &it = items[b.order_host[j]];
+    ctx->lpt_customers[j] = it.customers;
+    meeting[j] = PlanEstimate::meeting(it.lambda, it.mu);
+  }
+  ctx->plan_shape = estimate_shape(ctx->lpt_customers, meeting, b.total_customers, device_cus(ctx));
   ctx->n_items = n;
   return MRIP_OK;
-}
-
-// Items of a longest-first order that count as long (a prefix of it).
-static uint64_t count_long(const std::vector<uint64_t> &lpt, uint64_t n, uint64_t long_min) {
-  return (uint64_t)(std::partition_point(lpt.begin(), lpt.begin() + (ptrdiff_t)n,
-                                         [&](uint64_t c) { return c >= long_min; }) -
-                    lpt.begin());
-}
-
-// How the uploaded plan's long items are split: decided on the whole plan
-// (its longest item and all its customers), so a run stopped at an item
-// limit or resumed from saved outputs splits every item as the
-// uninterrupted run does and gives the same bits.
-struct PlanShape {
-  uint32_t split;
-  uint64_t long_min;
-};
-
-// Without features every form gives the same means (fp64 sums, rounded once),
-// and the plan takes the one whose estimate is lowest. In chunks of 1024 customers (620
-// instructions): the longest item alone takes 1.29 us a chunk on one
-// wavefront, 0.67, 0.333 and 0.269 on two, four and eight (eight share the
-// SIMDs of one compute unit); all of the work takes 1.046 us a chunk on one
-// SIMD, 3 % and 13 % more split in two and eight, and about 4 us more per
-// wavefront of each split item. The estimate is the root of the squares' sum
-// of the two. Items are split from 16384 customers, or from the length that
-// unsplit takes half as long as the longest does split: shorter ones cost
-// more in overhead than they hold up. Over 46 plans of 4 to 80 design points
-// of 20 to 40 replications, 1e3..1e4 to 3e4..1e6 customers, the chosen form
-// is 3 % slower than the best of 27 tried on average (17 % at most), and 1.8
-// times as fast as eight wavefronts for items of 65536 customers (0.988 at
-// worst); 64 x 32 of 1e4 to 1e6: 596 us that way, 474 on four from 16384.
-static PlanShape plan_shape_of(mrip_ctx ctx) {
-  const std::vector<uint64_t> &lpt = ctx->lpt_customers;
-  const uint64_t longest = lpt.empty() ? 0 : lpt[0];
-  uint64_t total = 0;
-  for (uint64_t n : lpt) total += n;
-  const uint32_t fixed = plan_split_for(ctx, longest, total);  // also finds out ctx->cus
-  if (ctx->plan_split_set || ctx->mm1.feature_prefix > 0) return {fixed, ctx->long_min};
-  constexpr double ALONE[4] = {1.29, 0.67, 0.333, 0.269}, MORE[4] = {1.0, 1.03, 1.0, 1.13};
-  const double chunks = (double)total / 1024.0 + 0.5 * (double)lpt.size();
-  PlanShape best{1, ctx->long_min};
-  double best_time = 0.0;
-  for (int k = 0; k < 4; ++k) {
-    const uint64_t long_min = std::max<uint64_t>(
-        1, std::min<uint64_t>(16384, (uint64_t)(0.5 * (double)longest * ALONE[k] / ALONE[0])));
-    const double n_split = k == 0 ? 0.0 : (double)count_long(lpt, lpt.size(), long_min);
-    const double work = (chunks * 1.046 * MORE[k] + 4.0 * (1 << k) * n_split) / (4.0 * ctx->cus);
-    const double path = std::ceil((double)longest / 1024.0) * ALONE[k];
-    const double time = std::sqrt(work * work + path * path);
-    if (k == 0 || time < best_time) {
-      best_time = time;
-      if (k > 0) best = {1u << k, long_min};
-    }
-  }
-  return best;
 }
 
 // done (nullable): the per-item done flags the kernels set, cleared first

@@ -151,9 +151,16 @@ struct CvState {
   float run_ms = 0.f, infer_ms = 0.f;
 };
 
+// Wavefronts per long item of a plan, and the customers from which an item is.
+struct PlanShape {
+  uint32_t split = 1;
+  uint64_t long_min = 65536;
+};
+
 // Wavefronts per long item for a plan run whose longest item has `longest`
 // customers out of `total`: as fixed by mrip_set_plan_split or the
-// autotuner, else the fewest (up to plan_split) that bring the longest
+// autotuner, else, for a plan with features (others choose by their items'
+// times), the fewest (up to plan_split) that bring the longest
 // item's share down to the run's average work per wavefront the chip holds
 // at once. Splitting shortens a plan only while its longest item sets the
 // makespan; beyond that its corrections and barriers cost time.
@@ -177,9 +184,9 @@ struct mrip_ctx_s {
   // the plans' shape: mrip_set_shape sets it with the runs' one, the
   // autotuner alone (it never touches the runs' shape)
   uint32_t plan_rpw = 1, plan_wg = 256;
-  // plans: wavefronts per long item (1 = none) and what counts as long;
-  // until mrip_set_plan_split or the autotuner fixes it, plan_split is the
-  // most a run uses (plan_split_for)
+  // plans: wavefronts per long item (1 = none) and what counts as long, as
+  // mrip_set_plan_split or the autotuner fixed them; until then plan_split is
+  // the most a run uses (plan_split_for, or plan_shape of the uploaded plan)
   uint32_t plan_split = 8;
   uint64_t long_min = 65536;
   bool plan_split_set = false;
@@ -264,6 +271,7 @@ struct mrip_ctx_s {
   bool plan_ran = false;                // a run of this plan wrote the flags and statistics
   std::vector<uint64_t> lpt_customers;  // customers in longest-first order
   std::vector<uint32_t> lpt_order;      // item indices in longest-first order
+  mrip::PlanShape plan_shape;           // the plan's own choice (without features)
   mrip::DevBuf resume_order;            // the queue of a resumed plan
   mrip::DevBuf item_done;               // per item: 1 once the last plan run wrote its outputs
   uint64_t plan_limit = 0;              // plan runs stop after this many items (0 = none)

@@ -264,3 +264,25 @@ def test_a_new_plan_has_no_flags_or_statistics_before_its_run(gpu):
     got = ctx.output(0, n=len(b)).cpu().numpy().astype(np.float64).reshape(70, 40)
     assert ctx.plan_stats(69)["mean"] == pytest.approx(got[69].mean(), rel=1e-12)
     assert np.all(mrip.mrip_plan_done(ctx.ctx, len(b)) == 1)
+
+
+@pytest.mark.parametrize("dps,rho", [(30, 1.1), (30, 1.0), (30, 0.995), (6, 1.2)])
+def test_a_plan_near_critical_load_is_not_split_to_its_loss(gpu, dps, rho):
+    # a split item's parts meet their true trajectory when the queue empties:
+    # where it hardly does they are run again one after another, which took
+    # 900 items of 1e5 customers three times as long as whole items do. Kernel
+    # times, the best of eight; the values are those of the unsplit plan
+    announce("plan near critical load", dps, rho)
+    items = inputs.uniform_items(dps, 30, 100000, [rho] * dps)
+    ms, outs = [], []
+    for own in (True, False):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+        if not own:
+            ctx.set_plan_split(1, 1)
+        ctx.plan_set(items)
+        for _ in range(9):
+            ctx.run_plan(seed=7)
+        outs.append(ctx.output(0, n=len(items)).cpu().numpy())
+        ms.append(min(ctx.history_ms(8)))
+    assert rel_err(*outs).max() <= 2.0**-23
+    assert ms[0] <= 1.5 * ms[1]
