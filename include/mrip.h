@@ -400,7 +400,10 @@ MRIP_API mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_i
  * file, mrip_autotune first looks up the plan's key there and, when found,
  * installs that shape without timing; otherwise it times the shapes and
  * stores the winner. The file holds one line per key: the key, reps per
- * wavefront, workgroup, wavefronts per long item and milliseconds. */
+ * wavefront, workgroup, wavefronts per long item, milliseconds, and the
+ * customers from which an item counts as long (a line without them, as
+ * mrip_tune_cache_put writes, is used where mrip_set_plan_split fixed that
+ * number or the plan has features, and timed anew elsewhere). */
 typedef struct {
   uint32_t reps_per_wave, workgroup, plan_split;
   float ms;

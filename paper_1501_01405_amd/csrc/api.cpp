@@ -599,7 +599,7 @@ mrip_status mrip_set_plan_split(mrip_ctx ctx, uint32_t waves_per_item, uint64_t 
   if (ctx->model != MRIP_MM1) return inval(ctx, "plans are defined for the M/M/1 engine");
   ctx->plan_split = waves_per_item;
   ctx->plan_split_set = true;
-  ctx->long_min = long_min > 0 ? long_min : 65536;
+  ctx->long_min = ctx->long_min_fixed = long_min > 0 ? long_min : 65536;
   return MRIP_OK;
 }
 
@@ -1303,14 +1303,14 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
   DevBuf sub;
   if (calib_items > 0 && calib_items < ctx->n_items) {
     // an evenly strided slice of the longest-first order keeps its length mix
-    std::vector<uint32_t> full(ctx->n_items), pick;
+    std::vector<uint32_t> full(ctx->n_items), slice;
     HIP_TRY(ctx, hipMemcpy(full.data(), order, 4 * ctx->n_items, hipMemcpyDeviceToHost));
     const double stride = (double)ctx->n_items / (double)calib_items;
-    for (uint64_t j = 0; j < calib_items; ++j) pick.push_back(full[(uint64_t)(j * stride)]);
-    HIP_TRY(ctx, sub.ensure(4 * pick.size()));
-    HIP_TRY(ctx, hipMemcpy(sub.p, pick.data(), 4 * pick.size(), hipMemcpyHostToDevice));
+    for (uint64_t j = 0; j < calib_items; ++j) slice.push_back(full[(uint64_t)(j * stride)]);
+    HIP_TRY(ctx, sub.ensure(4 * slice.size()));
+    HIP_TRY(ctx, hipMemcpy(sub.p, slice.data(), 4 * slice.size(), hipMemcpyHostToDevice));
     order = sub.as<uint32_t>();
-    n = pick.size();
+    n = slice.size();
   }
   // the slice's lengths in longest-first order decide which items are long
   std::vector<uint64_t> lpt(n);
@@ -1320,7 +1320,12 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
     const double stride = (double)ctx->n_items / (double)n;
     for (uint64_t j = 0; j < n; ++j) lpt[j] = ctx->lpt_customers[(uint64_t)(j * stride)];
   }
-  const uint64_t n_long = count_long(lpt, n, ctx->long_min);
+  // What counts as long: as mrip_set_plan_split fixed it, else 65536 customers
+  // and, where plans choose for themselves, the length their estimate takes
+  // for that many wavefronts (so that the shape an untuned run takes is among
+  // those timed, with other groupings of the rest).
+  const uint64_t base_min = ctx->long_min_fixed ? ctx->long_min_fixed : 65536;
+  const uint64_t n_long = count_long(lpt, n, base_min);
   // the cache named by MRIP_TUNE_CACHE: a stored shape for this kind of
   // plan on this kind of GPU is installed without timing
   const char *cache = std::getenv("MRIP_TUNE_CACHE");
@@ -1335,7 +1340,11 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
     use_cache = mrip_tune_key(ctx->model, ctx->mapping, n, n_long, lpt.empty() ? 0 : lpt[0],
                               prop.gcnArchName, (uint32_t)cus, key, sizeof key) == MRIP_OK;
     mrip_tune_entry e{};
-    if (use_cache && mrip_tune_cache_get(cache, key, &e) == MRIP_OK &&
+    uint64_t e_long = 0;
+    // an entry that does not say what counts as long was timed with a fixed
+    // length, and is taken where one is
+    if (use_cache && tune_cache_get(cache, key, &e, &e_long) == MRIP_OK &&
+        (e_long > 0 || ctx->long_min_fixed || ctx->mm1.feature_prefix > 0) &&
         (e.reps_per_wave == 1 || e.reps_per_wave == 2 || e.reps_per_wave == 4) &&
         (e.workgroup == 64 || e.workgroup == 256 || e.workgroup == 1024) &&
         (e.plan_split == 1 || e.plan_split == 2 || e.plan_split == 4 || e.plan_split == 8)) {
@@ -1343,28 +1352,42 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
       ctx->plan_wg = e.workgroup;
       ctx->plan_split = e.plan_split;
       ctx->plan_split_set = true;
+      ctx->long_min = ctx->long_min_fixed || e_long == 0 ? base_min : e_long;
       if (best_rpw) *best_rpw = e.reps_per_wave;
       if (best_wg)
-        *best_wg = (e.plan_split > 1 && n_long > 0) ? (e.plan_split == 8 ? 512u : 256u) : e.workgroup;
+        *best_wg = (e.plan_split > 1 && count_long(lpt, n, ctx->long_min) > 0)
+                       ? (e.plan_split == 8 ? 512u : 256u)
+                       : e.workgroup;
       if (best_ms) *best_ms = e.ms;
       return MRIP_OK;
     }
   }
-  struct Shape { uint32_t rpw, wg, split; };
+  struct Shape {
+    uint32_t rpw, wg, split;
+    uint64_t long_min, n_long;
+  };
   std::vector<Shape> shapes;
   for (uint32_t r : {1u, 2u, 4u})
-    for (uint32_t w : {64u, 256u, 1024u}) shapes.push_back({r, w, 1});
-  if (n_long > 0)
-    for (uint32_t r : {1u, 2u, 4u})
-      for (uint32_t x : {2u, 4u, 8u}) shapes.push_back({r, 256u, x});
+    for (uint32_t w : {64u, 256u, 1024u}) shapes.push_back({r, w, 1, base_min, 0});
+  for (int k = 1; k < 4; ++k) {
+    const uint64_t own_min = ctx->long_min_fixed || ctx->mm1.feature_prefix > 0
+                                 ? base_min
+                                 : PlanEstimate::long_min(ctx->lpt_customers[0], k);
+    const uint64_t own_long = count_long(lpt, n, own_min);
+    for (uint32_t r : {1u, 2u, 4u}) {
+      if (n_long > 0) shapes.push_back({r, 256u, 1u << k, base_min, n_long});
+      if (own_long > n_long) shapes.push_back({r, 256u, 1u << k, own_min, own_long});
+    }
+  }
   float best = 1e30f;
-  uint32_t br = ctx->plan_rpw, bw = ctx->plan_wg, bx = ctx->plan_split;
+  Shape pick{ctx->plan_rpw, ctx->plan_wg, ctx->plan_split, ctx->long_min, n_long};
   for (const Shape &sh : shapes) {
     float t_min = 1e30f;
     // the first launch warms up; the best of four more, since shapes a few
     // per cent apart swap places in single timings
     for (int rep = 0; rep < 5; ++rep) {
-      mrip_status st = run_plan_impl(ctx, seed, s, order, n, n_long, sh.rpw, sh.wg, sh.split, false);
+      mrip_status st =
+          run_plan_impl(ctx, seed, s, order, n, sh.n_long, sh.rpw, sh.wg, sh.split, false);
       if (st != MRIP_OK) return st;
       float ms = 0.f;
       st = last_launch_ms(ctx, &ms);
@@ -1373,24 +1396,24 @@ mrip_status mrip_autotune(mrip_ctx ctx, uint64_t seed, uint64_t calib_items, voi
     }
     if (t_min < best) {
       best = t_min;
-      br = sh.rpw;
-      bw = sh.wg;
-      bx = sh.split;
+      pick = sh;
     }
   }
-  ctx->plan_split = bx;
+  ctx->plan_split = pick.split;
   ctx->plan_split_set = true;
-  ctx->plan_rpw = br;
-  ctx->plan_wg = bw;
+  ctx->long_min = pick.long_min;
+  ctx->plan_rpw = pick.rpw;
+  ctx->plan_wg = pick.wg;
   ctx->last = RUN_NONE;  // outputs of the timing runs are partial
   if (use_cache) {
-    const mrip_tune_entry e{br, bw, bx, best};
-    (void)mrip_tune_cache_put(cache, key, &e);  // a cache that cannot be written is only slower
+    const mrip_tune_entry e{pick.rpw, pick.wg, pick.split, best};
+    // a cache that cannot be written is only slower
+    (void)tune_cache_put(cache, key, &e, pick.long_min);
   }
-  if (best_rpw) *best_rpw = br;
+  if (best_rpw) *best_rpw = pick.rpw;
   // the workgroup size actually launched: a split plan launches 256
   // threads per workgroup for 2 or 4 wavefronts per item, 512 for 8
-  if (best_wg) *best_wg = (bx > 1 && n_long > 0) ? (bx == 8 ? 512u : 256u) : bw;
+  if (best_wg) *best_wg = (pick.split > 1 && pick.n_long > 0) ? (pick.split == 8 ? 512u : 256u) : pick.wg;
   if (best_ms) *best_ms = best;
   return MRIP_OK;
 }

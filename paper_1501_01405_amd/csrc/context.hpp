@@ -166,6 +166,12 @@ struct PlanShape {
 // makespan; beyond that its corrections and barriers cost time.
 uint32_t plan_split_for(mrip_ctx ctx, uint64_t longest, uint64_t total);
 
+// The autotuner's cache with the length of a long item (tune_cache.cpp).
+mrip_status tune_cache_get(const char *path, const char *key, mrip_tune_entry *out,
+                           uint64_t *long_min);
+mrip_status tune_cache_put(const char *path, const char *key, const mrip_tune_entry *e,
+                           uint64_t long_min);
+
 // Check n items (1 <= n < 2^32) and enqueue their upload into b on s.
 mrip_status upload_items(mrip_ctx ctx, const mrip_plan_item *items, uint64_t n, uint64_t K,
                          uint64_t long_min, bool bins, ItemBufs &b, hipStream_t s);
@@ -189,6 +195,7 @@ struct mrip_ctx_s {
   // the most a run uses (plan_split_for, or plan_shape of the uploaded plan)
   uint32_t plan_split = 8;
   uint64_t long_min = 65536;
+  uint64_t long_min_fixed = 0;  // as mrip_set_plan_split fixed it (0: it did not)
   bool plan_split_set = false;
   uint32_t cus = 0;  // compute units of the device (queried on first use)
   // stream source of mrip_run (MRIP_RNG_*) and, for taus88, its jump tables

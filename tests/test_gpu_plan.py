@@ -286,3 +286,43 @@ def test_a_plan_near_critical_load_is_not_split_to_its_loss(gpu, dps, rho):
         ms.append(min(ctx.history_ms(8)))
     assert rel_err(*outs).max() <= 2.0**-23
     assert ms[0] <= 1.5 * ms[1]
+
+
+@pytest.mark.parametrize("dps,reps,lo,hi", [(5, 6, 50000, 50000), (20, 30, 3000, 60000),
+                                            (64, 32, 10000, 1000000)])
+def test_a_tuned_plan_takes_no_longer_than_an_untuned_one(gpu, dps, reps, lo, hi, tmp_path,
+                                                          monkeypatch):
+    # the tuner times the forms that an untuned plan chooses from, also where
+    # no item has the 65536 customers that long once meant, and stores what it
+    # counted as long; an entry without that is timed anew
+    announce("autotune against the plan's own shape", dps, reps, lo, hi)
+    items = inputs.plan_table(n_dp=dps, reps=reps, n_lo=lo, n_hi=hi, seed=4) if hi > lo else \
+        inputs.uniform_items(dps, reps, lo, [0.7] * dps)
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("MRIP_TUNE_CACHE", str(path))
+
+    def kernel_ms(ctx):
+        for _ in range(9):
+            ctx.run_plan(seed=8)
+        return min(ctx.history_ms(8))
+
+    a = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+    a.plan_set(items)
+    own = kernel_ms(a)
+    a.autotune(8)
+    tuned = kernel_ms(a)
+    assert a.shape()["plan_split"] > 1  # every such plan gains by splitting
+    assert tuned <= 1.1 * own
+    line = path.read_text().split()
+    assert len(line) == 6 and int(line[3]) == a.shape()["plan_split"]
+    b = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+    b.plan_set(items)
+    b.autotune(8)
+    assert b.shape()["plan_split"] == a.shape()["plan_split"]
+    assert path.read_text().split() == line  # the stored shape, untimed
+    assert kernel_ms(b) <= 1.1 * tuned
+    mrip.mrip_tune_cache_put(path, line[0], 1, 256, 1, 0.001)
+    c = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(), WAVE)
+    c.plan_set(items)
+    c.autotune(8)
+    assert c.shape()["plan_split"] > 1 and len(path.read_text().split()) == 6
