@@ -9,6 +9,7 @@
 // series to third order inside a bracket: one or two evaluations of the tail
 // where an interval asks for it (0.35 us for 63 degrees of freedom and 0.975,
 // where Newton from a bracket's middle took eight evaluations and 5.7 us).
+// From ten thousand degrees of freedom on the expansion is the quantile.
 #include <cmath>
 
 namespace mrip {
@@ -72,14 +73,28 @@ double t_upper_tail(double t, double nu, double log_beta, double &pdf) {
 }
 
 // Standard normal quantile of an upper tail q < 1/2: a rational starting
-// value (Abramowitz and Stegun 26.2.23, 4.5e-4) and one third-order step.
-double normal_upper(double q) {
+// value (Abramowitz and Stegun 26.2.23, 4.5e-4) and third-order steps, of
+// which one leaves some 1e-13 and two leave rounding.
+double normal_upper(double q, int steps) {
   const double w = std::sqrt(-2.0 * std::log(q));
   double z = w - (2.515517 + w * (0.802853 + w * 0.010328)) /
                      (1.0 + w * (1.432788 + w * (0.189269 + w * 0.001308)));
-  const double pdf = std::exp(-0.5 * z * z) * 0.3989422804014327;
-  const double u = (0.5 * std::erfc(z * 0.7071067811865476) - q) / pdf;
-  return z + u * (1.0 + u * (0.5 * z + u * (2.0 * z * z + 1.0) / 6.0));
+  for (int i = 0; i < steps; ++i) {
+    const double pdf = std::exp(-0.5 * z * z) * 0.3989422804014327;
+    const double u = (0.5 * std::erfc(z * 0.7071067811865476) - q) / pdf;
+    z += u * (1.0 + u * (0.5 * z + u * (2.0 * z * z + 1.0) / 6.0));
+  }
+  return z;
+}
+
+// The expansion of t in powers of 1 / nu (Abramowitz and Stegun 26.7.5) at the
+// normal quantile z.
+double t_expansion(double z, double nu) {
+  const double z2 = z * z, v = 1.0 / nu;
+  const double g1 = (z2 + 1.0) / 4, g2 = ((5.0 * z2 + 16.0) * z2 + 3.0) / 96;
+  const double g3 = (((3.0 * z2 + 19.0) * z2 + 17.0) * z2 - 15.0) / 384;
+  const double g4 = ((((79.0 * z2 + 776.0) * z2 + 1482.0) * z2 - 1920.0) * z2 - 945.0) / 92160;
+  return z * (1.0 + v * (g1 + v * (g2 + v * (g3 + v * g4))));
 }
 
 }  // namespace
@@ -88,15 +103,15 @@ double t_quantile(double p, double nu) {
   if (!(p >= 0.5 && p < 1.0) || !(nu > 0.0)) return std::nan("");
   if (p == 0.5) return 0.0;
   const double target = 1.0 - p;  // upper-tail probability
+  // From here on the expansion is exact to rounding (its next term is below
+  // 1e-15 for any tail a double's p has), and the tail below is less and less
+  // so: a log1p(r) of large a rounds to more than the steps' end asks for
+  // (4.3e9 degrees of freedom: 62 us and an error of 1e-8 that way).
+  if (nu >= 1e4) return t_expansion(normal_upper(target, 2), nu);
   const double log_beta = 0.5723649429247001 - log_gamma_ratio(0.5 * nu);  // log sqrt(pi) - ...
   double lo = 0.0, hi = INFINITY, pdf, t;
   if (nu >= 4.0 && target > 1e-12) {
-    // Abramowitz and Stegun 26.7.5
-    const double z = normal_upper(target), z2 = z * z, v = 1.0 / nu;
-    const double g1 = (z2 + 1.0) / 4, g2 = ((5.0 * z2 + 16.0) * z2 + 3.0) / 96;
-    const double g3 = (((3.0 * z2 + 19.0) * z2 + 17.0) * z2 - 15.0) / 384;
-    const double g4 = ((((79.0 * z2 + 776.0) * z2 + 1482.0) * z2 - 1920.0) * z2 - 945.0) / 92160;
-    t = z * (1.0 + v * (g1 + v * (g2 + v * (g3 + v * g4))));
+    t = t_expansion(normal_upper(target, 1), nu);
   } else {
     double step = 1.0;
     while (t_upper_tail(step, nu, log_beta, pdf) > target) {

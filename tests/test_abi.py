@@ -74,6 +74,42 @@ def test_t_quantile_against_the_exact_tail(dof):
         assert tail(q * (1 - d)) > target > tail(q * (1 + d)), (p, dof)
 
 
+@pytest.mark.parametrize("dof", [9998, 10000, 16384, 65536])
+def test_t_quantile_of_many_degrees_of_freedom(dof):
+    # From 10000 on the quantile is an expansion at the normal one. Its tail
+    # (erfc) and its steps round to a few units: 1e-15 of t where the tail is
+    # steepest for its size (at 0.55), 4e-15 allowed. Below, the tail of the t
+    # law itself rounds, by a log1p of 2e-16 of some 5000: 1e-12.
+    from decimal import Decimal, getcontext
+    getcontext().prec = 40
+    d = Decimal("4e-15") if dof >= 10000 else Decimal("1e-12")
+
+    def tail(t):
+        r = Decimal(dof) + t * t
+        x = Decimal(dof) / r
+        term = total = Decimal(1)
+        for k in range(2, dof, 2):
+            term *= x * (k - 1) / k
+            total += term
+            if term < Decimal("1e-38"):
+                break
+        return (1 - total * t / r.sqrt()) / 2
+
+    for p in (0.55, 0.9, 0.975, 0.9995, 1 - 2.0**-38):
+        q, target = Decimal(mrip.mrip_t_quantile(p, dof)), 1 - Decimal(p)
+        assert tail(q * (1 - d)) > target > tail(q * (1 + d)), (p, dof)
+
+
+@pytest.mark.parametrize("p,z", [(0.975, 1.9599639845400542355), (0.995, 2.5758293035489007610),
+                                 (0.9995, 3.2905267314919255)])
+def test_t_quantile_tends_to_the_normal_one(p, z):
+    # z (1 + (z^2 + 1) / (4 nu)) beyond that; the constants are of the decimal
+    # p, which a double is 1e-16 off: 1e-15 to 1e-13 of z
+    for dof in (4294967295.0, 1e12, 1e300, float("inf")):
+        want = z * (1 + (z * z + 1) / (4 * dof))
+        assert abs(mrip.mrip_t_quantile(p, dof) - want) <= 2e-13 * want
+
+
 def _create(model, params, mapping=mrip.MRIP_MAP_AUTO):
     ctx = mrip.ctx_t()
     rc = mrip.load().mrip_create(C.byref(ctx), model, C.byref(params), mapping)
