@@ -205,10 +205,10 @@ MRIP_API void mrip_destroy(mrip_ctx ctx);
 MRIP_API mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t reps_per_wave, uint32_t workgroup);
 
 /* Wavefronts per replication for mrip_run on an M/M/1 WAVE context: 1, 2,
- * 4 or 8 (default 1; needs reps_per_wave = 1). At the default, runs on
- * Philox streams that would leave the device idle are split all the same,
- * to the same values. With more than one, the
- * wavefronts of a workgroup (256 threads, or 512 for 8) each take an equal
+ * 4 or 8 (default 1; needs reps_per_wave = 1). Until this call or
+ * mrip_set_shape fixes the shape, runs on Philox streams that would leave the
+ * device idle are split all the same, to the same values. With more than one,
+ * the wavefronts of a workgroup (256 threads, or 512 for 8) each take an equal
  * run of the replication's customers from an empty system; then every part
  * at once re-runs its leading chunks from the carry its predecessor ended
  * with until the two trajectories meet (Lindley's recursion forgets its
@@ -377,9 +377,10 @@ MRIP_API mrip_status mrip_set_plan_split(mrip_ctx ctx, uint32_t waves_per_item,
                                          uint64_t long_min);
 
 /* Current launch shape: reps_per_wave, workgroup and wavefronts per
- * replication of mrip_run, wavefronts per long plan item (any may be NULL;
- * before mrip_set_plan_split or mrip_autotune fixes it, the most a plan run
- * may use). */
+ * replication of mrip_run (1 until mrip_set_split; a run may take more until
+ * it or mrip_set_shape fixes the shape), wavefronts per long plan item (before
+ * mrip_set_plan_split or mrip_autotune fixes it, the most a plan run may use).
+ * Any may be NULL. */
 MRIP_API mrip_status mrip_get_shape(mrip_ctx ctx, uint32_t *reps_per_wave, uint32_t *workgroup,
                                     uint32_t *split, uint32_t *plan_split);
 

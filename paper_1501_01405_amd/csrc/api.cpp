@@ -561,6 +561,7 @@ mrip_status mrip_set_shape(mrip_ctx ctx, uint32_t rpw, uint32_t wg) {
   if (rpw != 1 && ctx->split != 1) return inval(ctx, "a split replication needs reps_per_wave = 1");
   ctx->rpw = ctx->plan_rpw = rpw;
   ctx->wg = ctx->plan_wg = wg;
+  ctx->run_shape_set = true;
   return MRIP_OK;
 }
 
@@ -574,6 +575,7 @@ mrip_status mrip_set_split(mrip_ctx ctx, uint32_t waves_per_rep) {
   if (waves_per_rep > 4 && ctx->rng != MRIP_RNG_PHILOX)
     return (ctx->err = "taus88 replications split over at most 4 wavefronts"), MRIP_E_UNSUPPORTED;
   ctx->split = waves_per_rep;
+  ctx->run_shape_set = true;
   return MRIP_OK;
 }
 
@@ -622,10 +624,10 @@ uint64_t lanes_per_rep(mrip_ctx c) {
   return 64;
 }
 
-// Wavefronts per replication of an M/M/1 run in the default shape (one
-// wavefront per replication, unless mrip_set_split says otherwise): runs
-// that leave SIMDs idle, or end in an uneven last round, are split as
-// mrip_set_split would, which gives the same bits. The lines follow kernel
+// Wavefronts per replication of an M/M/1 run whose shape neither
+// mrip_set_shape nor mrip_set_split fixed: runs that leave SIMDs idle, or end
+// in an uneven last round, are split as mrip_set_split would, which gives the
+// same bits. The lines follow kernel
 // times over customers x replications (us for 1 / 2 / 4 / 8 wavefronts, rho
 // 0.9): 4000 x 300 10.3 / 8.8 / 9.9 / -, 7000 x 1500 21.9 / 17.8 / 24.9 / -,
 // 10000 x 300 19.0 / 11.4 / 10.6 / -, 10000 x 2048 28.4 / 28.9 / 34.2 / -, 20000
@@ -683,8 +685,7 @@ mrip_status mrip_run(mrip_ctx ctx, uint64_t n_reps, uint64_t seed, void *hip_str
   for (uint32_t o = 0; o < mrip_ctx_s::MAX_OUT; ++o) overlap = overlap && !ctx->bound[o].p;
   const bool wave = ctx->mapping == MRIP_MAP_WAVE;
   uint32_t split = ctx->split;  // wavefronts per M/M/1 replication
-  if (ctx->model == MRIP_MM1 && wave && split == 1 && ctx->rpw == 1 &&
-      ctx->rng == MRIP_RNG_PHILOX)
+  if (ctx->model == MRIP_MM1 && wave && !ctx->run_shape_set && ctx->rng == MRIP_RNG_PHILOX)
     split = default_split(ctx, n_reps);
   // the headline form, one kernel per run, times itself
   const bool self_timed = kSelfTimedLaunch && ctx->model == MRIP_MM1 && wave && ctx->split > 1 &&

@@ -187,6 +187,7 @@ struct mrip_ctx_s {
   mrip_pi_params pi;
   uint32_t rpw = 1, wg = 256;
   uint32_t split = 1;  // wavefronts per M/M/1 replication in mrip_run
+  bool run_shape_set = false;  // by mrip_set_shape or mrip_set_split: taken as it is
   // the plans' shape: mrip_set_shape sets it with the runs' one, the
   // autotuner alone (it never touches the runs' shape)
   uint32_t plan_rpw = 1, plan_wg = 256;

@@ -243,3 +243,24 @@ def test_mm1_default_shape_same_bits_for_any_replications(gpu, N, lam, K):
     ctx.run(1300, seed=4)
     for o in range(3):
         assert np.array_equal(ctx.output(o).cpu().numpy(), last[o])
+
+
+@pytest.mark.parametrize("fix", ["split", "shape"])
+def test_mm1_unsplit_runs_can_be_asked_for(gpu, fix):
+    # 32 replications of 1e5 customers in the default shape take a wavefront
+    # group each and a third of the time; once the shape is fixed it is taken as
+    # it is (one wavefront each), to the same bits
+    announce("mm1 explicit shape", fix)
+    ms, outs = [], []
+    for explicit in (False, True):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(0.9, 1.0, 100000), WAVE)
+        if explicit and fix == "split":
+            ctx.set_split(1)
+        elif explicit:
+            ctx.set_shape(1, 256)
+        for _ in range(9):
+            ctx.run(32, seed=5)
+        ms.append(min(ctx.history_ms(8)))
+        outs.append([ctx.output(o).cpu().numpy() for o in range(3)])
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
+    assert ms[1] > 2.0 * ms[0]
