@@ -627,17 +627,20 @@ uint64_t lanes_per_rep(mrip_ctx c) {
 // Wavefronts per replication of an M/M/1 run whose shape neither
 // mrip_set_shape nor mrip_set_split fixed: runs that leave SIMDs idle, or end
 // in an uneven last round, are split as mrip_set_split would, which gives the
-// same bits. The lines follow kernel
-// times over customers x replications (us for 1 / 2 / 4 / 8 wavefronts, rho
-// 0.9): 4000 x 300 10.3 / 8.8 / 9.9 / -, 7000 x 1500 21.9 / 17.8 / 24.9 / -,
-// 10000 x 300 19.0 / 11.4 / 10.6 / -, 10000 x 2048 28.4 / 28.9 / 34.2 / -, 20000
-// x 700 29.5 / 24.6 / 21.0 / 25.2, 20000 x 4096 87 / 84 / 92 / 94, 20000 x 8192
-// 166 / 174 / 185 / -, 1e5 x 32 115 / 65 / 34.4 / 32.4, 1e5 x 1024 119 / 108 /
-// 101 / 102, 54321 x 4096 225 / 211 / 208 / 217. A part's correction lasts until
-// its queue has emptied, so near critical load only idle SIMDs pay for it
-// (20000 customers, rho 0.95: 300 replications 29.2 / 22.2 / 19.6, 1024 31.4 /
-// 32.3 / 32.9; rho 0.97: 54321 x 300 67 / 56 / 50, 20000 x 300 29.0 / 29.4 /
-// 29.0; rho 0.99: 1e5 x 300 117 / 137 / 166) and above that nothing is split.
+// same bits. The lines follow kernel times, all taken between the same
+// markers on the stream, over customers x replications (us for 1 / 2 / 4 / 8
+// wavefronts, load 0.9): 4096 x 300 9.6 / 9.8 / 11.2 / 12.4, 6500 x 512 13.9 /
+// 13.0 / 15.4 / 16.8, 8000 x 300 14.7 / 11.9 / 11.4 / 17.4, 8000 x 1500 23.8 /
+// 21.2 / 22.3 / 43.5, 20000 x 704 29.6 / 28.1 / 24.0 / 26.3, 20000 x 4096 92 / 87
+// / 88 / 100, 1e5 x 30 117 / 68 / 37.9 / 33.0, 1e5 x 1024 123 / 112 / 105 / 105. A
+// part's correction lasts until its queue has emptied, so near critical load
+// only long runs on idle SIMDs gain (8200 customers, load 0.95: 300 replications
+// 15.7 / 18.4 / 15.8, 512 16.2 / 18.8 / 18.9; load 0.96: 512 16.1 / 19.0 / 19.7;
+// 20000, load 0.95: 300 28.4 / 24.3 / 22.1, 1024 30.8 / 35.5 / 36.2; load 0.97:
+// 50000 x 300 61 / 57 / 52, 20000 x 300 28.3 / 32.2 / 31.2; load 0.99: 1e5 x 300
+// 117 / 137 / 166) and above that nothing is split. Over 4112 runs of 1500 to 4e5
+// customers, 1 to 4096 replications, loads 0.5 to 0.975, with features and
+// without, the chosen form is 8 % slower than the unsplit one at most.
 static uint32_t default_split(mrip_ctx c, uint64_t n_reps) {
   const uint64_t chunk = 1024;  // customers a wavefront takes at a time
   const uint64_t chunks = (c->mm1.customers + chunk - 1) / chunk;
@@ -653,14 +656,16 @@ static uint32_t default_split(mrip_ctx c, uint64_t n_reps) {
       max2 = ft ? 1024 : 4096;
       max4 = ft ? 512 : 704;
     } else if (chunks >= 8) {
-      max2 = ft ? 1024 : 1500;
-      max4 = 320;
+      max2 = ft ? 512 : rho <= 0.905 ? 1500 : 640;
+      max4 = 300;
     } else if (chunks >= 4) {
-      max2 = ft ? 512 : 640;
+      max2 = 512;
     }
   } else if (rho <= 0.96) {
-    if (chunks >= 8) max2 = max4 = 512;
-    else if (chunks >= 4) max2 = 512;
+    if (chunks >= 16) max2 = max4 = ft && chunks < 24 && rho > 0.952 ? 300 : 512;
+    else if (chunks >= 8) max2 = max4 = rho <= 0.935 ? 512 : rho <= 0.952 ? 300 : 100;
+    else if (chunks >= 4 && ft) max2 = rho <= 0.935 ? 512 : 30;
+    else if (chunks >= 4) max2 = rho <= 0.925 ? 100 : rho <= 0.935 ? 30 : 1;
   } else if (rho <= 0.975) {
     if (chunks >= 48) max2 = max4 = 512;
   }

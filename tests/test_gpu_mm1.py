@@ -264,3 +264,21 @@ def test_mm1_unsplit_runs_can_be_asked_for(gpu, fix):
         outs.append([ctx.output(o).cpu().numpy() for o in range(3)])
     assert all(np.array_equal(a, b) for a, b in zip(*outs))
     assert ms[1] > 2.0 * ms[0]
+
+
+@pytest.mark.parametrize("N,lam,R", [(8200, 0.96, 512), (8200, 0.95, 512), (5000, 0.95, 300),
+                                     (6500, 0.96, 300), (4096, 0.9, 640)])
+def test_mm1_default_shape_is_no_slower_than_the_unsplit_one(gpu, N, lam, R):
+    # runs whose parts' corrections cost more than idle SIMDs give (15 to 25 %
+    # slower when split). Kernel times between markers on the stream, the best
+    # of thirty; the lines leave 8 % at most
+    announce("mm1 default shape against unsplit", N, lam, R)
+    ms = []
+    for explicit in (False, True):
+        ctx = mrip.Context(mrip.MRIP_MM1, mrip.mm1_params(lam, 1.0, N), WAVE)
+        if explicit:
+            ctx.set_split(1)
+        for _ in range(32):
+            ctx.run(R, seed=6)
+        ms.append(min(ctx.history_ms(30)))
+    assert ms[0] <= 1.12 * ms[1]
