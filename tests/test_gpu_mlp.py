@@ -93,6 +93,36 @@ def test_gradient_at_the_edges_of_its_tiles(gpu, n):
     assert abs(float(loss.cpu()[0]) - ref_loss) <= 1e-4 * ref_loss
 
 
+@pytest.mark.parametrize("rows", [31, 32, 33, 47, 48, 49, 64, 65])
+def test_gradient_over_many_rows(gpu, rows):
+    # partial rows around the 32 and 16 that are summed at a time, the last one
+    # of a few samples; both entry points sum the same rows in the same order
+    announce("mlp grad rows", rows)
+    n = 64 * rows - (59 if rows % 2 else 0)
+    rng = np.random.default_rng(rows)
+    x = rng.normal(size=(n, 10)).astype(np.float32)
+    yt = rng.normal(size=n).astype(np.float32)
+    z = rng.normal(size=(n, 4)).astype(np.float32)
+    theta = _theta(2)
+    ref, ref_loss = omlp.backward(theta, x, yt, bf16=True, z=z)
+    rd = omlp.unpack(ref)
+    args = [_dev(a) for a in (theta, x, z, yt)]
+    grads = []
+    for call in (mrip.mrip_mlp_grad, mrip.mrip_mlp_grad_noalloc):
+        if n > mrip.MRIP_MLP_GRAD_NOALLOC_MAX and call is mrip.mrip_mlp_grad_noalloc:
+            continue
+        grad = torch.empty(mrip.MRIP_MLP_PARAMS, dtype=torch.float32, device="cuda")
+        loss = torch.empty(1, dtype=torch.float32, device="cuda")
+        call(*args, n, grad, loss, mrip.current_stream())
+        grads.append(grad.cpu().numpy())
+        gd = omlp.unpack(grads[-1].astype(np.float64))
+        for name in NAMES:  # as at the tiles' edges
+            err = np.linalg.norm(gd[name] - rd[name]) / max(np.linalg.norm(rd[name]), 1e-30)
+            assert err < 1e-3, (name, err)
+        assert abs(float(loss.cpu()[0]) - ref_loss) <= 1e-4 * ref_loss
+    assert all(np.array_equal(g, grads[0]) for g in grads)
+
+
 def test_gradient_of_constant_network_is_bias_only(gpu):
     # W3 = 0: every gradient except dW3 and db3 vanishes; with prediction
     # c = b3 . z, db3_k = 2 mean((c - y) z_k)
