@@ -326,3 +326,28 @@ def test_a_tuned_plan_takes_no_longer_than_an_untuned_one(gpu, dps, reps, lo, hi
     c.plan_set(items)
     c.autotune(8)
     assert c.shape()["plan_split"] > 1 and len(path.read_text().split()) == 6
+
+
+@pytest.mark.parametrize("rpw", [1, 2, 4])
+@pytest.mark.parametrize("dps,reps,lo,hi", [(30, 30, 2000, 100000), (64, 32, 1500, 8000),
+                                            (3, 37, 1000, 20000)])
+def test_a_plan_in_large_workgroups_spreads_its_longest_items(gpu, dps, reps, lo, hi, rpw):
+    # a wavefront's first unit is its number: every item is served whatever
+    # the workgroup, with the same bits, and the longest sixteen don't share
+    # one compute unit (2.8 to 3.2 times the time of workgroups of 256 with
+    # the 900 items here; 1.1 to 1.3 times spread out)
+    announce("plan in workgroups of 1024", dps, reps, lo, hi, rpw)
+    items = inputs.plan_table(n_dp=dps, reps=reps, n_lo=lo, n_hi=hi, seed=3)
+    ms, out = {}, {}
+    for wg in (64, 256, 1024):
+        ctx = _plan_ctx(items, rpw, wg)
+        for _ in range(9):
+            ctx.run_plan(seed=8)
+        ms[wg] = min(ctx.history_ms(8))
+        out[wg] = [ctx.output(o).cpu().numpy() for o in range(3)]
+        assert ctx.plan_done().all()
+    for o in range(3):
+        assert np.array_equal(out[64][o], out[256][o])
+        assert np.array_equal(out[64][o], out[1024][o])
+    if dps == 30:
+        assert ms[1024] < 1.5 * ms[256]
