@@ -640,7 +640,7 @@ uint64_t lanes_per_rep(mrip_ctx c) {
 // 50000 x 300 61 / 57 / 52, 20000 x 300 28.3 / 32.2 / 31.2; load 0.99: 1e5 x 300
 // 117 / 137 / 166) and above that nothing is split. Over 4112 runs of 1500 to 4e5
 // customers, 1 to 4096 replications, loads 0.5 to 0.975, with features and
-// without, the chosen form is 8 % slower than the unsplit one at most.
+// without, the chosen form is 9 % slower than the unsplit one at most.
 static uint32_t default_split(mrip_ctx c, uint64_t n_reps) {
   const uint64_t chunk = 1024;  // customers a wavefront takes at a time
   const uint64_t chunks = (c->mm1.customers + chunk - 1) / chunk;

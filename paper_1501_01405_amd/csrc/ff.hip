@@ -155,7 +155,7 @@ __device__ __forceinline__ void word_masks(uint32_t c0_base, uint32_t c1, uint32
 // One replication over the THREADS = GRID * GRID / 32 / N threads of a
 // workgroup, N consecutive words of a row each. Bound: vector-ALU issue (one
 // instruction per four cycles per SIMD), so the step is written for few
-// instructions per cell: 11.4 where lightning is rare, 13.6 before.
+// instructions per cell: 11.7 where lightning is rare, 13.6 before.
 //  * Round 1 of Philox is the same for a thread's blocks up to an xor with
 //    the block's number; rounds 2 and 3 share their products with word 2 and
 //    word 0 across the blocks of a step. The round keys sit in vector
